@@ -540,7 +540,7 @@ def measure_nodes(ldni, torch, mg, reps):
     n_samples = sum(L[a].n for a in range(3))
     alg = 3 * 4 * (w * w + 1) + 4 * n_samples + 4 * bits.numel()
     # the vote kernel's own algorithmic share: the bit volume it writes (the
-    # span codes it reads are implementation traffic of the two-pass design)
+    # toggles and start bits it reads are implementation traffic of the two-pass design)
     vote_alg = 4 * bits.numel()
     roof = None
     if "classify_nodes" in ks and ks["classify_nodes"][1] > 0:
@@ -550,7 +550,7 @@ def measure_nodes(ldni, torch, mg, reps):
                 "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
                 "traffic": read_traffic("nodes-2048", "classify_nodes", "ldni_nodes.hip"),
                 "avg_launch_us": round(k_ms * 1e3, 2), "algorithmic_bytes_per_launch": vote_alg}
-    kern = {k: round(v[1] / reps, 4) for k, v in ks.items() if k in ("node_codes", "classify_nodes")}
+    kern = {k: round(v[1] / reps, 4) for k, v in ks.items() if k in ("node_bins", "classify_nodes")}
     return {
         "workload": "nodes-2048",
         "description": "inside/outside of the 2048^3 grid nodes of the scene64 (seed 1) LDNIs by the "

@@ -290,8 +290,9 @@ ldni_status ldni_boolean(const ldni_axis_view *a, const ldni_axis_view *b, int32
  *   n_words at least ldni_node_words(w).
  *   stats   HOST u64 [2] or NULL: nodes inside, and nodes whose three
  *           votes are not all equal (the disagreements the vote repairs).
- * Workspace: about 3 w^3 / 32 bytes (w = 2048: 0.8 GB) of span codes from
- * the stream-ordered pool, kept for reuse like the other calls' buffers.
+ * Workspace: about 3 w^3 / 240 bytes and 2 bytes per sample (w = 2048: 0.1
+ * GB and the samples' share) from the stream-ordered pool, kept for reuse
+ * like the other calls' buffers.
  * One host synchronisation (the totals and the status).
  */
 ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[6], uint32_t *bits,

@@ -1270,14 +1270,22 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
   prepare_pool(device);
   uint32_t* rb = pinned_readback();
   if (!rb) return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
-  // workspace: [0] status word, [64..80) the two totals, [256..) per-workgroup
-  // sums, then the span codes of the three axes
-  const uint32_t n_wg = node_workgroups(w);
-  const int32_t n_spans = (w + 63) / 64;
-  const size_t o_codes = align_up(256 + 16 * (size_t)n_wg);
+  // workspace: [0] status word, [128] the number of mixed bricks, [256..) the vote's
+  // partial totals; then per axis and brick its range, kind and start bits,
+  // and the three toggle lists
+  const size_t nb = (size_t)(w + 31) / 32, bricks = 3 * nb * nb * nb;
+  const size_t o_range = align_up(256 + 16 * (size_t)kNodeSlots);
+  const size_t o_kind = align_up(o_range + sizeof(uint2) * bricks);
+  const size_t o_parity = align_up(o_kind + bricks);
+  const size_t o_mixed = align_up(o_parity + 32 * sizeof(uint32_t) * bricks);
+  size_t o_toggles[3], bytes = align_up(o_mixed + sizeof(uint32_t) * (bricks / 3));
+  for (int d = 0; d < 3; ++d) {
+    o_toggles[d] = bytes;
+    bytes = align_up(bytes + sizeof(uint16_t) * (size_t)views[d].n_samples);
+  }
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  hipError_t e = cache_get(&ws, o_codes + node_code_bytes(w), stream, &ws_bytes);
+  hipError_t e = cache_get(&ws, bytes, stream, &ws_bytes);
   if (e != hipSuccess) return hip_fail(e, "workspace allocation");
   char* wb = static_cast<char*>(ws);
   NodeArgs g{};
@@ -1286,28 +1294,39 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
     g.axis[d] = AxisArrays{v.n_samples, v.offsets, v.depth, nullptr, nullptr};
     g.lo[d] = (double)bbox[d];
     g.h[d] = ((double)bbox[3 + d] - (double)bbox[d]) / (double)w;
+    g.inv_h[d] = 1.0 / g.h[d];
+    // a node depth f32(f32(lo + (t + 0.5) h) - lo) is within 2^-24 (|lo| +
+    // 2 (w + 1) h) (1 + 2^-20) of (t + 0.5) h, and the estimate of t carries
+    // a float64 error of a few 2^-53 (w + 1); twice their sum, in pixels
+    g.slack[d] = 2.0 * (std::ldexp(std::fabs(g.lo[d]) + 2.0 * ((double)w + 1.0) * g.h[d], -24) *
+                            (1.0 + std::ldexp(1.0, -20)) / g.h[d] +
+                        std::ldexp((double)w + 1.0, -48));
+    // fma(s, f32(1 / h), -0.5) in float32 adds at most (2 w + 3) 2^-24 within
+    // the grid; twice that, rounded up
+    g.inv_hf[d] = (float)g.inv_h[d];
+    g.slackf[d] = (float)(1.0001 * (g.slack[d] + std::ldexp((double)w + 2.0, -22)));
+    g.toggles[d] = reinterpret_cast<uint16_t*>(wb + o_toggles[d]);
   }
   g.w = w;
-  g.nb = (w + 31) / 32;
+  g.nb = (int32_t)nb;
   g.bits = bits;
   g.status = reinterpret_cast<uint32_t*>(wb);
-  g.stats = reinterpret_cast<uint64_t*>(wb + 64);
+  g.n_mixed = reinterpret_cast<uint32_t*>(wb + 128);
   g.partial = reinterpret_cast<uint64_t*>(wb + 256);
-  g.codes = reinterpret_cast<uint16_t*>(wb + o_codes);
-  g.n_spans = n_spans;
+  g.range = reinterpret_cast<uint2*>(wb + o_range);
+  g.kind = reinterpret_cast<uint8_t*>(wb + o_kind);
+  g.parity = reinterpret_cast<uint32_t*>(wb + o_parity);
+  g.mixed = reinterpret_cast<uint32_t*>(wb + o_mixed);
   auto run = [&]() -> ldni_status {
 #define NSTEP(expr, what)                       \
   do {                                          \
     hipError_t e_ = (expr);                     \
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
-    NSTEP(launch_fill_u32(g.status, 0u, 1, stream), "fill");
-    NSTEP(timed("node_codes", stream, [&] { return launch_node_codes(g, stream); }), "span code kernel");
+    NSTEP(launch_fill_u32(g.status, 0u, 64 + 4 * (int64_t)kNodeSlots, stream), "fill");
+    NSTEP(timed("node_bins", stream, [&] { return launch_node_bins(g, stream); }), "node binning kernel");
     NSTEP(timed("classify_nodes", stream, [&] { return launch_classify_nodes(g, stream); }), "classify kernel");
-    NSTEP(launch_node_stats(g, stream), "node totals");
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(g.stats);
-    const uint32_t* src[5] = {g.status, words, words + 1, words + 2, words + 3};
-    NSTEP(launch_gather(src, 5, rb, stream), "readback");
+    NSTEP(launch_node_stats(g, rb, stream), "node totals");
     NSTEP(hipStreamSynchronize(stream), "synchronise");
 #undef NSTEP
     if (rb[0] & kStatusMismatch)

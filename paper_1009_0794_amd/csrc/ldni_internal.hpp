@@ -263,28 +263,36 @@ struct BooleanArgs {
 };
 hipError_t launch_boolean(const BooleanArgs& g, bool write, hipStream_t s);
 
-// Copies n (<= 16) device words into pinned, device-visible host memory.
 // Grid-node classification of three LDNIs of one box and resolution
-// (ldni_nodes.hip).  axis[a] is the a-LDNI; lo/h the node origin and
-// spacing per world axis; bits holds nb^3 bricks of 1024 words (nb =
-// ceil(w/32)); partial 2 words per workgroup (node_workgroups); stats[0..1]
-// = nodes inside, nodes whose three votes differ.
+// (ldni_nodes.hip).  axis[a] is the a-LDNI; lo/h the node origin and spacing
+// per world axis (inv_h = 1 / h, slack the node depths' float32 roundings in
+// pixels); bits holds nb^3 bricks of 1024 words (nb = ceil(w/32)).  The bin
+// pass sorts every axis's toggles by brick: toggles[a] (as
+// many entries as a's samples), and per axis and brick (axis * nb^3
+// + brick number) the range of the list, the kind of its start bits and,
+// where they are mixed, 32 words of them.  partial (zeroed) takes the
+// vote's totals, two words in each of kNodeSlots slots.
 struct NodeArgs {
   AxisArrays axis[3];
   int32_t w, nb;
-  double lo[3], h[3];
+  double lo[3], h[3], inv_h[3], slack[3];
+  float inv_hf[3], slackf[3];  // the same for a float32 estimate
   uint32_t* bits;
   uint32_t* status;   // kStatusMismatch: offsets of an input out of order
+  uint32_t* n_mixed;  // bricks listed in mixed (zeroed)
   uint64_t* partial;
-  uint64_t* stats;
-  uint16_t* codes;    // node_code_bytes(w): span codes of the three axes (launch_node_codes)
-  int32_t n_spans;    // ceil(w / 64)
+  uint2* range;       // [3 nb^3] (first, number of toggles)
+  uint8_t* kind;      // [3 nb^3]
+  uint32_t* parity;   // [3 nb^3][32]
+  uint16_t* toggles[3];
+  uint32_t* mixed;    // [nb^3] bricks that are not one value
 };
-uint32_t node_workgroups(int32_t w);
-size_t node_code_bytes(int32_t w);
-hipError_t launch_node_codes(const NodeArgs& g, hipStream_t s);
+constexpr uint32_t kNodeSlots = 256;  // (one pair would take an atomic from every workgroup)
+hipError_t launch_node_bins(const NodeArgs& g, hipStream_t s);
 hipError_t launch_classify_nodes(const NodeArgs& g, hipStream_t s);
-hipError_t launch_node_stats(const NodeArgs& g, hipStream_t s);
+// totals and status to five words of pinned host memory: status, inside (low,
+// high), nodes whose three votes differ (low, high)
+hipError_t launch_node_stats(const NodeArgs& g, uint32_t* host, hipStream_t s);
 
 // Offsetting (ldni_offset.hip): the three input LDNIs, their box (lo, h per
 // world axis), |r| and eps, the sphere centres (3 doubles per sample,

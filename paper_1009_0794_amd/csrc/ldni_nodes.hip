@@ -1,4 +1,4 @@
-// ldni_nodes.hip -- gfx950 kernel classifying the grid nodes of three LDNIs.
+// ldni_nodes.hip -- gfx950 kernels classifying the grid nodes of three LDNIs.
 //
 // The rays of the x-, y- and z-LDNI of one box and resolution w meet at the
 // nodes of a w x w x w grid (Definition 3).  Along each of its rays a node is
@@ -19,21 +19,19 @@
 // i = 32 bi .. 32 bi + 31 of row (j, k), node i in bit i%32.  Bits of nodes
 // beyond w are zero.
 //
-// Work decomposition.  A workgroup owns the 64 x 64 rows (j, k) of a block of
-// 2 x 2 brick columns and walks along i one brick (32 nodes) at a time:
-//  * its 4096 x-rays run along i, so each is streamed once: per thread 16 ray
-//    states (next sample, end, parity) in registers, advanced a brick per step;
-//  * the y-rays (i, k) and z-rays (i, j) of the step are cut to the block's
-//    64 nodes along j (resp. k): each such span is a 64-bit mask built from the
-//    samples at or before its last node (a parity fill toggled at each sample),
-//    2 x 2048 spans per step;
-//  * the spans come out with bits along j (resp. k), the output wants bits
-//    along i: each thread transposes one 32 x 32 bit matrix in registers
-//    (five block-swap stages), the blocks exchanged through LDS;
-//  * majority of the three words, stored as 2 x 128 contiguous bytes per wave.
-// The output write (w^3 / 8 bytes) is the dominant HBM traffic; the inputs
-// are read once (x) or a few times through the caches (y, z spans of the
-// step's 32 rays of each column).  No contraction: nothing for MFMA.
+// A sample changes the inside state of its ray at one node, the first at or
+// behind it (a toggle); between samples nothing changes, so most bricks hold
+// no toggle and are one value.  Two passes:
+//  * bin: a workgroup owns 32 x 32 rays of one LDNI, the rays through nb
+//    bricks, and sorts their toggles by brick (one 16-bit word each), with
+//    each ray's inside state at the start of every brick as 32 words of bits
+//    (left out where all 1024 rays agree);
+//  * vote: a wave owns a brick.  The toggles of an axis are XORed into a
+//    cleared 4 KB LDS matrix in the orientation of the output; a prefix XOR
+//    along the axis and the start bits give the axis's inside words, and the
+//    majority of the three is stored.  A brick without toggles takes its
+//    words from the start bits alone.
+// Nothing here is a contraction: nothing for MFMA.
 #pragma clang fp contract(off)
 
 #include "ldni_internal.hpp"
@@ -42,381 +40,519 @@ namespace ldni {
 namespace {
 
 constexpr int kNodeBlock = 256;
-constexpr int kSpan = 64;     // nodes of a workgroup's block along j and along k
-// a vote step covers 2 x 32 nodes along i (two bricks) for the block's 64 x 64 (j, k) nodes
-constexpr int kRow = 33;      // LDS stride of a 32-word bit matrix (no bank conflicts)
-constexpr int kVoteBlock = 512;  // threads of a classification workgroup
-static_assert(kSpan * kSpan / kVoteBlock == 8, "the vote kernel gives each thread 8 x-rays of its block");
+constexpr int kNodeWaves = kNodeBlock / 64;
+constexpr int kUniformBlock = 512;
+constexpr int kUniformWaves = kUniformBlock / 64;
+constexpr int kParityStride = 33;  // LDS words per brick of the start bits (no bank conflicts)
 
-// Depth of node t on an axis with origin lo and pixel size h; nodes past the
-// grid get +inf so that the tables stay sorted.
-__device__ __forceinline__ float node_depth(double lo, double h, int t, int w) {
-  if (t >= w) return __int_as_float(0x7f800000);
+// What a brick's 1024 rays of one axis are at the brick's first node.
+constexpr uint32_t kAllOutside = 0, kAllInside = 1, kMixed = 2;
+
+// Depth of node t on an axis with origin lo and pixel size h.
+__device__ __forceinline__ float node_depth(double lo, double h, int t) {
   const float c = (float)(lo + ((double)t + 0.5) * h);
   return (float)((double)c - lo);
 }
 
-// Number of entries of the sorted table T[0..n) below s, given T[0] < s.
-template <int N>
-__device__ __forceinline__ int count_below(const float* T, float s) {
-  int lo = 1, hi = N;
+// The first node whose depth is at or above s (w if none, as for NaN).  The
+// estimate s / h - 0.5 is exact when it is farther than the axis's slack (the
+// float32 roundings of the node depths, in pixels, and the estimate's own)
+// from every integer: in float32 for nearly all samples, else in float64, else
+// a binary search over the node depths decides.
+__device__ __forceinline__ int first_node(const NodeArgs& g, int f, float s) {
+  const float t = fmaf(s, g.inv_hf[f], -0.5f), c = ceilf(t);
+  if (c - t > g.slackf[f] && c - t < 1.0f - g.slackf[f]) return (int)fminf(fmaxf(c, 0.0f), (float)g.w);
+  const double td = (double)s * g.inv_h[f] - 0.5, cd = ceil(td);
+  if (cd - td > g.slack[f] && cd - td < 1.0 - g.slack[f]) return (int)fmin(fmax(cd, 0.0), (double)g.w);
+  int lo = 0, hi = g.w;
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
-    if (T[mid] < s) lo = mid + 1; else hi = mid;
+    if (node_depth(g.lo[f], g.h[f], mid) >= s) hi = mid; else lo = mid + 1;
   }
   return lo;
 }
 
-// Inside mask of the 64 nodes whose depths are T[0..64) along the ray of
-// pixel p (bit t = node t): parity of the paired samples at or before each
-// node.  Offsets outside [0, n] or decreasing set *bad and give an empty ray.
-__device__ __forceinline__ uint64_t span_mask(const AxisArrays& ax, size_t p, const float* T, float t_first,
-                                              float t_last, bool& bad) {
-  const uint32_t o0 = ax.offsets[p], o1 = ax.offsets[p + 1];
-  if (o1 < o0 || (uint64_t)o1 > ax.n) {
-    bad = true;
-    return 0;
-  }
-  const uint32_t end = o0 + ((o1 - o0) & ~1u);
-  uint64_t m = 0;
-  for (uint32_t q = o0; q < end; ++q) {
-    const float s = ax.depth[q];
-    if (!(s <= t_last)) break;  // this and every later sample lies beyond the span
-    const int c = s <= t_first ? 0 : count_below<kSpan>(T, s);
-    m ^= c >= 64 ? 0ull : (~0ull << c);
-  }
-  return m;
-}
+// One workgroup per 32 x 32 rays (u, v) of axis f = blockIdx.y; a wave takes
+// a row of 32 rays at a time, whose samples are one contiguous range, a
+// sample per lane (with a ray per lane, a 333^3 grid whose deepest ray has 160
+// samples took 296 us here).  A first pass over the samples counts the toggles
+// per brick and keeps the first kKept of them in LDS, a second places them
+// (and reads what was not kept again).  Half bound by VALU issue (170 instructions
+// per wave of 64 samples over both passes), half by the latency of a patch's
+// few serial steps: 0.32 ms for the 38.6 M samples of scene64 at w = 2048, 50 us
+// for the flower at w = 333; the span codes it replaced took 0.46 ms and 103 us.
+constexpr int kBinBlock = 512;
+constexpr int kBinWaves = kBinBlock / 64;
+constexpr uint32_t kKept = 3072;
+constexpr int kSegs = kBinBlock / 32;
 
-// 32 x 32 bit matrix transpose in registers: afterwards a[j] bit i is the
-// former a[i] bit j.  Stage s swaps the off-diagonal s x s blocks of every
-// 2s x 2s block.
-template <int S, uint32_t M>
-__device__ __forceinline__ void swap_stage(uint32_t (&a)[32]) {
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    if ((i & S) == 0) {
-      const uint32_t t = ((a[i] >> S) ^ a[i + S]) & M;
-      a[i + S] ^= t;
-      a[i] ^= t << S;
-    }
-  }
-}
-
-__device__ __forceinline__ void transpose32(uint32_t* row) {
-  uint32_t a[32];
-#pragma unroll
-  for (int i = 0; i < 32; ++i) a[i] = row[i];
-  swap_stage<16, 0x0000ffffu>(a);
-  swap_stage<8, 0x00ff00ffu>(a);
-  swap_stage<4, 0x0f0f0f0fu>(a);
-  swap_stage<2, 0x33333333u>(a);
-  swap_stage<1, 0x55555555u>(a);
-#pragma unroll
-  for (int i = 0; i < 32; ++i) row[i] = a[i];
-}
-
-// Span codes.  For every ray of the three LDNIs and every span of 64 nodes
-// along it (span s holds nodes 64 s .. 64 s + 63), one 16-bit code:
-//   bit 12      parity of the ray's paired samples at or before the span's
-//               first node (inside at that node),
-//   bits 0..5   t1, bits 6..11 t2: the samples after the first node and at or
-//               before the span's last node flip the nodes from position
-//               t (1..63) on; 0 means none,
-//   bit 13      more than two such samples: bits 0..11 then hold the number
-//               of the ray's paired samples before them (4095: that many or
-//               more), and the vote pass walks the span's samples.
-// Codes are grouped so that one step of one vote workgroup reads 4096
-// consecutive codes per axis (index = block * 4096 + v):
-//   x-ray (j, k), span s along i:  block ((s*S + k/64)*S + j/64),  v = (k%64)*64 + j%64
-//   y-ray (i, k), span s along j:  block ((s*S + k/64)*S + i/64),  v = (i%64)*64 + k%64
-//   z-ray (i, j), span s along k:  block ((s*S + j/64)*S + i/64),  v = (j%64)*64 + i%64
-// with S = ceil(w/64) spans per axis; one axis's codes fill S^3 * 4096 words.
-constexpr uint32_t kCodeParity = 1u << 12;
-constexpr uint32_t kCodeWalk = 1u << 13;
-constexpr uint32_t kRankMax = 4095u;  // bits 0..11 of a walk code: samples before the span (4095: or more)
-
-__device__ __forceinline__ size_t code_index(int f, int iu, int iv, int s, int S) {
-  // (iu, iv) = pixel of the f-LDNI; the frame is cyclic: x (j, k), y (k, i), z (i, j)
-  const int a = f == 1 ? iv : iu;  // the coordinate whose 64-block is the inner block index
-  const int b = f == 1 ? iu : iv;  // the other one (outer block index, and the row of v)
-  // x: a = j, b = k -> v = (k%64)*64 + j%64, block (s, k/64, j/64)
-  // y: a = i, b = k -> v = (i%64)*64 + k%64, block (s, k/64, i/64)
-  // z: a = i, b = j -> v = (j%64)*64 + i%64, block (s, j/64, i/64)
-  const size_t block = ((size_t)s * S + (b >> 6)) * S + (a >> 6);
-  const uint32_t v = f == 1 ? (uint32_t)((a & 63) * 64 + (b & 63)) : (uint32_t)((b & 63) * 64 + (a & 63));
-  return block * 4096 + v;
-}
-
-// One thread per ray: walks the ray's paired samples once and writes the
-// code of each of its spans.  Grid (ceil(w*w/256), 3): blockIdx.y is the axis.
-__global__ __launch_bounds__(kNodeBlock) void node_codes_kernel(NodeArgs g) {
-  extern __shared__ float s_t[];  // the w node depths along this axis
+__global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
+  extern __shared__ uint32_t s_node[];
+  __shared__ uint32_t s_off[32][33];  // the rays' first samples
+  __shared__ uint32_t s_bad;          // rows whose offsets decrease
+  __shared__ uint32_t s_at[33];       // samples of the rows before
+  __shared__ uint32_t s_keep[kKept];  // brick << 15 | toggle, or ~0
+  __shared__ uint32_t s_seg[kSegs][kParityStride];
+  __shared__ uint32_t s_scan[kBinWaves];
+  __shared__ unsigned long long s_base;
   const int f = blockIdx.y;
-  const int w = g.w, S = g.n_spans;
-  for (int t = threadIdx.x; t < w; t += kNodeBlock) s_t[t] = node_depth(g.lo[f], g.h[f], t, w);
-  __syncthreads();
-  const size_t npix = (size_t)w * w;
-  const size_t p = (size_t)blockIdx.x * kNodeBlock + threadIdx.x;
-  if (p >= npix) return;
-  const int iu = (int)(p % (size_t)w), iv = (int)(p / (size_t)w);
+  const int w = g.w, nb = g.nb;
+  uint32_t* s_cur = s_node;          // [nb] toggles per brick, then list positions
+  uint32_t* s_par = s_node + nb;     // [nb][kParityStride] start bits: toggles of the brick before, then their prefix
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pu = (int)(blockIdx.x % (uint32_t)nb), pv = (int)(blockIdx.x / (uint32_t)nb);
   const AxisArrays& ax = g.axis[f];
-  uint16_t* C = g.codes + (size_t)f * ((size_t)S * S * S * 4096);
-  const uint32_t o0 = ax.offsets[p], o1 = ax.offsets[p + 1];
-  uint32_t cnt = 0;
-  if (o1 < o0 || (uint64_t)o1 > ax.n) atomicOr(g.status, kStatusMismatch);
-  else cnt = (o1 - o0) & ~1u;
-  // the samples are read four at a time (independent loads), q indexes them
-  const float* dep = ax.depth + o0;
-  float b0 = 0.0f, b1 = 0.0f, b2 = 0.0f, b3 = 0.0f;
-  auto fill = [&](uint32_t from) {
-    if (from < cnt) b0 = dep[from];
-    if (from + 1 < cnt) b1 = dep[from + 1];
-    if (from + 2 < cnt) b2 = dep[from + 2];
-    if (from + 3 < cnt) b3 = dep[from + 3];
-  };
-  uint32_t q = 0, parity = 0;
-  fill(0);
-  float d = b0;
-  auto next = [&]() {
-    ++q;
-    if ((q & 3u) == 0) fill(q);
-    const uint32_t r = q & 3u;
-    d = r == 0 ? b0 : r == 1 ? b1 : r == 2 ? b2 : b3;
-  };
-  // consecutive spans of one ray are S*S blocks apart
-  uint16_t* c = C + code_index(f, iu, iv, 0, S);
-  const size_t span_step = (size_t)S * S * 4096;
-  for (int s = 0; s < S; ++s, c += span_step) {
-    const int base = s * kSpan, last = min(base + kSpan - 1, w - 1);
-    const float t_first = s_t[base], t_last = s_t[last];
-    while (q < cnt && d <= t_first) {
-      parity ^= 1u;
-      next();
-    }
-    uint32_t code = parity ? kCodeParity : 0u;
-    if (q < cnt && d <= t_last) {
-      const uint32_t rank = q;
-      int n_t = 0;
-      do {
-        // d lies after node base and at or before node last: it flips nodes c.. (c in 1..last-base)
-        int lo = 1, hi = last - base;
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (s_t[base + mid] < d) lo = mid + 1; else hi = mid;
-        }
-        if (n_t == 0) code |= (uint32_t)lo;
-        else if (n_t == 1) code |= (uint32_t)lo << 6;
-        ++n_t;
-        parity ^= 1u;
-        next();
-      } while (q < cnt && d <= t_last);
-      // more than two: the code keeps the rank of the span's first sample instead
-      if (n_t > 2) code = (code & kCodeParity) | kCodeWalk | (rank < kRankMax ? rank : kRankMax);
-    }
-    *c = (uint16_t)code;
+  const int cols = min(32, w - 32 * pu), rows = min(32, w - 32 * pv);
+
+  // brick number and its step along the axis
+  const size_t nb2 = (size_t)nb * nb;
+  const size_t brick0 = f == 0 ? (size_t)pv * nb2 + (size_t)pu * nb
+                      : f == 1 ? (size_t)pu * nb2 + (size_t)pv
+                               : (size_t)pv * nb + (size_t)pu;
+  const size_t step = f == 0 ? 1 : f == 1 ? (size_t)nb : nb2;
+  const size_t axis0 = (size_t)f * nb2 * nb;
+
+  if (tid == 0) s_bad = 0u;
+  uint32_t band = 0;  // first sample of the image's row
+  if (tid < rows) band = ax.offsets[(size_t)(32 * pv + tid) * w];
+  for (int q = tid; q < 32 * 33; q += kBinBlock) {
+    const int r = q / 33, c = q - 33 * r;
+    // (rays beyond the grid are empty)
+    s_off[r][c] = r < rows ? ax.offsets[(size_t)(32 * pv + r) * w + 32 * pu + min(c, cols)] : 0u;
   }
-}
-
-// The rare span with more than two samples inside: from its code's rank, the
-// parity at its first node and a walk over its own samples (from the ray's
-// start when the rank saturated).
-__device__ __forceinline__ uint64_t span_walk(const AxisArrays* ax, size_t p, uint32_t code, const float* T,
-                                              uint32_t* bad) {
-  const uint32_t rank = code & kRankMax;
-  if (rank == kRankMax) {
-    bool b = false;
-    const uint64_t m = span_mask(*ax, p, T, T[0], T[kSpan - 1], b);
-    if (b) *bad = 1u;
-    return m;
-  }
-  const uint32_t o0 = ax->offsets[p], o1 = ax->offsets[p + 1];
-  if (o1 < o0 || (uint64_t)o1 > ax->n) {
-    *bad = 1u;
-    return 0;
-  }
-  const uint32_t end = o0 + ((o1 - o0) & ~1u);
-  const float t_first = T[0], t_last = T[kSpan - 1];
-  uint64_t m = (code & kCodeParity) ? ~0ull : 0ull;
-  for (uint32_t q = o0 + rank; q < end; ++q) {
-    const float s = ax->depth[q];
-    if (!(s <= t_last)) break;
-    const int c = s <= t_first ? 0 : count_below<kSpan>(T, s);
-    m ^= c >= 64 ? 0ull : (~0ull << c);
-  }
-  return m;
-}
-
-// Inside mask of a span from its code (bit t = node t of the span).
-__device__ __forceinline__ uint64_t decode_span(uint32_t code) {
-  uint64_t m = (code & kCodeParity) ? ~0ull : 0ull;
-  const uint32_t t1 = code & 63u, t2 = (code >> 6) & 63u;
-  if (t1) m ^= ~0ull << t1;
-  if (t2) m ^= ~0ull << t2;
-  return m;
-}
-
-__device__ __forceinline__ uint32_t code_at(const uint4& c, int m) {
-  const uint32_t word = m < 2 ? c.x : m < 4 ? c.y : m < 6 ? c.z : c.w;
-  return (m & 1) ? word >> 16 : word & 0xffffu;
-}
-
-// LDS bit matrices of one step: y matrix (k, j-half, i-half) and z matrix
-// (j, k-half, i-half), 32 rows of kRow words.
-__device__ __forceinline__ int ymat(int kl, int jh, int ih) { return (ih * 2 + jh) * kSpan + kl; }
-__device__ __forceinline__ int zmat(int jl, int kh, int ih) { return 4 * kSpan + (ih * 2 + kh) * kSpan + jl; }
-
-// The vote.  A workgroup owns the 64 x 64 rows (j, k) of one block and walks
-// along i one span (two bricks) per step.  Thread t handles the 8 consecutive
-// codes v = 8t .. 8t + 7 of each axis (one 16-byte load each, issued a step
-// ahead).
-__global__ __launch_bounds__(kVoteBlock, 4) void classify_nodes_kernel(NodeArgs g) {
-  __shared__ uint32_t s_m[8 * kSpan * kRow];  // 256 y and 256 z matrices
-  __shared__ float s_ty[kSpan], s_tz[kSpan];
-  __shared__ float s_tx[2][kSpan];  // node depths of the current and the next span along i
-  __shared__ uint64_t s_sum[2][kVoteBlock / 64];
-
-  const int tid = threadIdx.x;
-  const int w = g.w, nb = g.nb, S = g.n_spans;
-  const int J = (int)(blockIdx.x % S), K = (int)(blockIdx.x / S);
-  const int j0 = J * kSpan, k0 = K * kSpan;
-  const AxisArrays& X = g.axis[0];
-  const AxisArrays& Y = g.axis[1];
-  const AxisArrays& Z = g.axis[2];
-  const size_t per_axis = (size_t)S * S * S * 4096;
-  // x codes of this block: v = kl*64 + jl; thread t takes jl = t % 64 and kl = (t / 64)*8 + m
-  const uint16_t* cx = g.codes + ((size_t)K * S + J) * 4096 + (size_t)(tid >> 6) * 512 + (tid & 63);
-  const uint4* cy = reinterpret_cast<const uint4*>(g.codes + per_axis) + ((size_t)J * S + K) * S * 512 + tid;
-  const uint4* cz = reinterpret_cast<const uint4*>(g.codes + 2 * per_axis) + ((size_t)K * S + J) * S * 512 + tid;
-  const size_t x_step = (size_t)S * S * 4096;  // codes per x span step
-
-  if (tid < kSpan) s_ty[tid] = node_depth(g.lo[1], g.h[1], j0 + tid, w);
-  else if (tid < 2 * kSpan) s_tz[tid - kSpan] = node_depth(g.lo[2], g.h[2], k0 + tid - kSpan, w);
-  else if (tid < 3 * kSpan) s_tx[0][tid - 2 * kSpan] = node_depth(g.lo[0], g.h[0], tid - 2 * kSpan, w);
-  // this thread's rays: 8 consecutive v = 8 tid + m
-  const int hi6 = tid >> 3, lo6 = (tid & 7) * 8;  // v / 64, v % 64 - m
-  uint32_t nx[8];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) nx[m] = cx[m * 64];
-  uint4 ny = cy[0], nz = cz[0];
+  for (int q = tid; q < nb * (1 + kParityStride); q += kBinBlock) s_node[q] = 0u;
   __syncthreads();
-  uint32_t n_inside = 0, n_split = 0;
-  uint32_t bad = 0;
-
-  for (int it = 0; it < S; ++it) {
-    uint32_t ux[8];
+  for (int q = tid; q < 1024; q += kBinBlock) {
+    const int r = q >> 5, c = q & 31;
+    if (s_off[r][c] > s_off[r][c + 1]) atomicOr(&s_bad, 1u << r);
+  }
+  __syncthreads();
+  // a row whose offsets decrease or pass the sample count is an error and
+  // counts as empty, and so do all rows that name more samples than there are
+  if (tid < 64) {
+    const int r = tid & 31;
+    const bool ok = s_off[r][32] <= ax.n && !((s_bad >> r) & 1u);
+    uint64_t incl = (ok && tid < 32) ? s_off[r][32] - s_off[r][0] : 0u;
+    uint64_t before = tid < rows ? (uint64_t)s_off[r][0] - band : 0u;
 #pragma unroll
-    for (int m = 0; m < 8; ++m) ux[m] = nx[m];
-    const uint4 uy = ny, uz = nz;
-    if (it + 1 < S) {
+    for (int o = 1; o < 32; o <<= 1) {
+      const uint64_t y = __shfl_up((unsigned long long)incl, o, 64);
+      if (tid >= o) incl += y;
+    }
 #pragma unroll
-      for (int m = 0; m < 8; ++m) nx[m] = cx[(size_t)(it + 1) * x_step + m * 64];
-      ny = cy[(size_t)(it + 1) * 512];
-      nz = cz[(size_t)(it + 1) * 512];
+    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor((unsigned long long)before, o, 64);
+    const uint64_t total = __shfl((unsigned long long)incl, 31, 64);
+    const bool fits = total <= ax.n;
+    if (tid < 32) {
+      if (!ok || !fits) atomicOr(g.status, kStatusMismatch);
+      s_at[r + 1] = fits ? (uint32_t)incl : 0u;
     }
-    const int i0 = it * kSpan;
-    const float* TX = s_tx[it & 1];
-    // y spans: v = il*64 + kl (il = hi6, kl = lo6 + m); z spans: v = jl*64 + il (jl = hi6, il = lo6 + m)
-#pragma unroll 1
-    for (int m = 0; m < 8; ++m) {
-      {
-        const int il = hi6, kl = lo6 + m;
-        const int i = i0 + il, k = k0 + kl;
-        uint64_t mk = 0;
-        if (i < w && k < w) {
-          const uint32_t c = code_at(uy, m);
-          mk = (c & kCodeWalk) ? span_walk(&Y, (size_t)i * w + k, c, s_ty, &bad) : decode_span(c);
-        }
-        s_m[ymat(kl, 0, il >> 5) * kRow + (il & 31)] = (uint32_t)mk;
-        s_m[ymat(kl, 1, il >> 5) * kRow + (il & 31)] = (uint32_t)(mk >> 32);
+    // The patch's part of its axis's list: the samples of the band's 32 rows
+    // are one range, and the patches of the band share it in their order,
+    // each as many entries as it has samples.
+    if (tid == 0) {
+      s_at[0] = 0u;
+      uint64_t base = (uint64_t)band + before;
+      if (base > ax.n || base + total > ax.n) {  // (offsets that decrease somewhere: an empty patch)
+        atomicOr(g.status, kStatusMismatch);
+        base = ~0ull;
       }
-      {
-        const int jl = hi6, il = lo6 + m;
-        const int i = i0 + il, j = j0 + jl;
-        uint64_t mk = 0;
-        if (i < w && j < w) {
-          const uint32_t c = code_at(uz, m);
-          mk = (c & kCodeWalk) ? span_walk(&Z, (size_t)j * w + i, c, s_tz, &bad) : decode_span(c);
-        }
-        s_m[zmat(jl, 0, il >> 5) * kRow + (il & 31)] = (uint32_t)mk;
-        s_m[zmat(jl, 1, il >> 5) * kRow + (il & 31)] = (uint32_t)(mk >> 32);
-      }
+      s_base = base;
     }
-    __syncthreads();
-    // one 32 x 32 transpose per thread; a spare wave fills the next span's depths
-    transpose32(s_m + tid * kRow);
-    __syncthreads();
-    if (tid >= kVoteBlock - kSpan)
-      s_tx[(it + 1) & 1][tid - (kVoteBlock - kSpan)] = node_depth(g.lo[0], g.h[0], i0 + kSpan + tid - (kVoteBlock - kSpan), w);
-    // majority of the three words: x-ray (jl, kl), jl = t % 64, kl = (t / 64)*8 + m;
-    // a wave stores 64 consecutive words of two brick rows per instruction.
-    // For m = 0..7 the y word moves by one matrix (kRow words), the z word by
-    // one row and the output by one brick row (32 words).
-    const int jl = tid & 63, j = j0 + jl;
-    const int kl0 = (tid >> 6) * 8;
-    const uint32_t* yp = s_m + ymat(kl0, jl >> 5, 0) * kRow + (jl & 31);
-    const uint32_t* zp = s_m + zmat(jl, kl0 >> 5, 0) * kRow + (kl0 & 31);
-    constexpr int kYHalf = 2 * kSpan * kRow;  // the i-half step of a y matrix index (ih * 2 * 64 matrices)
-    const int bj = 2 * J + (jl >> 5), bk = 2 * K + (kl0 >> 5);
-    uint32_t valid[2];
-#pragma unroll
-    for (int ih = 0; ih < 2; ++ih) {
-      const int ib = i0 + 32 * ih;
-      valid[ih] = (ib >= w || j >= w) ? 0u : (w - ib >= 32) ? 0xffffffffu : ((1u << (w - ib)) - 1u);
+  }
+  __syncthreads();
+  if (s_at[32] == 0u) {  // no sample: all outside
+    if (tid < nb) {
+      g.range[axis0 + brick0 + (size_t)tid * step] = make_uint2(0u, 0u);
+      g.kind[axis0 + brick0 + (size_t)tid * step] = kAllOutside;
     }
-    const bool store[2] = {2 * it < nb && bj < nb && bk < nb, 2 * it + 1 < nb && bj < nb && bk < nb};
-    uint32_t* op[2] = {g.bits + (((size_t)bk * nb + bj) * nb + 2 * it) * 1024 + (kl0 & 31) * 32 + (jl & 31),
-                       g.bits + (((size_t)bk * nb + bj) * nb + 2 * it + 1) * 1024 + (kl0 & 31) * 32 + (jl & 31)};
-#pragma unroll 1
-    for (int m = 0; m < 8; ++m) {
-      const int k = k0 + kl0 + m;
-      uint64_t xm = 0;
-      if (j < w && k < w) {
-        const uint32_t c = ux[m];
-        xm = (c & kCodeWalk) ? span_walk(&X, (size_t)k * w + j, c, TX, &bad) : decode_span(c);
-      }
-      const bool krow = k < w;
-#pragma unroll
-      for (int ih = 0; ih < 2; ++ih) {
-        const uint32_t xw = (uint32_t)(xm >> (32 * ih));
-        const uint32_t yw = yp[m * kRow + ih * kYHalf];
-        const uint32_t zw = zp[m + ih * kYHalf];
-        // rows past the grid hold no node (their y or z words may carry fill bits)
-        const uint32_t row = krow ? valid[ih] : 0u;
-        const uint32_t in = ((xw & yw) | (xw & zw) | (yw & zw)) & row;
-        n_inside += __popc(in);
-        n_split += __popc(((xw | yw | zw) & ~(xw & yw & zw)) & row);
-        if (store[ih]) op[ih][m * 32] = in;
-      }
-    }
-    __syncthreads();  // the next step rewrites the matrices
+    return;
   }
 
-  if (bad) atomicOr(g.status, kStatusMismatch);
+  // calls on(place in the patch, row, column, brick, node in the brick, live)
+  // for the samples of the row; live: paired and in front of some node
+  auto walk_row = [&](int r, auto&& on) {
+    const uint32_t* off = s_off[r];
+    const uint32_t len = s_at[r + 1] - s_at[r], row0 = off[0];
+    if (len == 0) return;
+    const float* dep = ax.depth + row0;
+    for (uint32_t s0 = 0;; s0 += 256) {  // four loads in flight
+      const uint32_t rest = len - s0;
+      float d[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d[j] = 64u * j + lane < rest ? dep[s0 + 64 * j + lane] : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) {  // two at a time: their chains of LDS reads overlap
+        if (64u * j >= rest) break;
+        uint32_t s[2];
+        int c[2] = {0, 0}, t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) s[i] = min(s0 + 64 * (j + i) + lane, len - 1);
+        // the ray: the last column whose samples start at or before s
+#pragma unroll
+        for (int h = 16; h >= 1; h >>= 1)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) c[i] += off[c[i] + h] <= row0 + s[i] ? h : 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) t[i] = first_node(g, f, d[j + i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bool here = 64u * (j + i) + lane < rest;
+          const bool live = t[i] < w && row0 + s[i] - off[c[i]] < ((off[c[i] + 1] - off[c[i]]) & ~1u);
+          if (here) on(s_at[r] + s[i], c[i], t[i] >> 5, t[i] & 31, live);
+        }
+      }
+      if (rest <= 256) break;
+    }
+  };
+
+  for (int r = wave; r < rows; r += kBinWaves)
+    walk_row(r, [&](uint32_t at, int c, int b, int t, bool live) {
+      if (at < kKept) s_keep[at] = live ? (uint32_t)(b << 15 | t | (c << 5) | (r << 10)) : ~0u;
+      if (!live) return;
+      atomicAdd(&s_cur[b], 1u);
+      // x- and z-rays: a word per row, bits along the columns; y-rays: a word
+      // per column (k), bits along the rows (i)
+      if (b + 1 < nb) atomicXor(&s_par[(b + 1) * kParityStride + (f == 1 ? c : r)], 1u << (f == 1 ? r : c));
+    });
+  __syncthreads();
+
+  // list positions: exclusive prefix of the bricks' counts from the range
+  // this workgroup takes of the axis's list; nb <= 256
+  const uint32_t n_b = tid < nb ? s_cur[tid] : 0u;
+  uint32_t incl = n_b;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
+    if (lane >= o) incl += y;
+  }
+  if (lane == 63) s_scan[tid >> 6] = incl;
+  __syncthreads();
+  const bool any = s_at[32] != 0u && s_base != ~0ull;
+  uint32_t first = (uint32_t)s_base;
+  for (int k = 0; k < wave; ++k) first += s_scan[k];
+  first += incl - n_b;
+  if (tid < nb) s_cur[tid] = first;
+
+  // start bits: prefix XOR over the bricks, kSegs segments of each of the 32 words
+  const int col = tid & 31, seg = tid >> 5, len = (nb + kSegs - 1) / kSegs;
+  const int b_lo = min(seg * len, nb), b_hi = min(b_lo + len, nb);
+  uint32_t acc = 0;
+  for (int b = b_lo; b < b_hi; ++b) {
+    acc ^= s_par[b * kParityStride + col];
+    s_par[b * kParityStride + col] = acc;
+  }
+  s_seg[seg][col] = acc;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int k = 0; k < seg; ++k) before ^= s_seg[k][col];
+  for (int b = b_lo; b < b_hi; ++b) {
+    const uint32_t word = s_par[b * kParityStride + col] ^ before;
+    const uint64_t zero = __ballot(word == 0u), one = __ballot(word == ~0u);
+    const int half = (lane >> 5) * 32;
+    const bool all0 = (uint32_t)(zero >> half) == ~0u, all1 = (uint32_t)(one >> half) == ~0u;
+    const size_t brick = axis0 + brick0 + (size_t)b * step;
+    if (!all0 && !all1) g.parity[brick * 32 + col] = word;
+    if (col == 0) g.kind[brick] = all0 ? kAllOutside : all1 ? kAllInside : kMixed;
+  }
+  if (tid < nb) g.range[axis0 + brick0 + (size_t)tid * step] = make_uint2(any ? first : 0u, any ? n_b : 0u);
+  if (!any) return;
+  __syncthreads();
+
+  uint16_t* list = g.toggles[f];
+  const uint32_t kept = min(s_at[32], kKept);
+  for (uint32_t q = tid; q < kept; q += kBinBlock) {
+    const uint32_t x = s_keep[q];
+    if (x != ~0u) list[atomicAdd(&s_cur[x >> 15], 1u)] = (uint16_t)(x & 0x7fffu);
+  }
+  if (kept == s_at[32]) return;
+  for (int r = wave; r < rows; r += kBinWaves)
+    if (s_at[r + 1] > kKept)
+      walk_row(r, [&](uint32_t at, int c, int b, int t, bool live) {
+        if (live && at >= kKept) list[atomicAdd(&s_cur[b], 1u)] = (uint16_t)(t | (c << 5) | (r << 10));
+      });
+}
+
+// One axis's part of a brick for the vote.
+struct BrickAxis {
+  uint32_t first, n, kind;
+};
+__device__ __forceinline__ BrickAxis brick_axis(const NodeArgs& g, size_t at) {
+  const uint2 r = g.range[at];
+  return BrickAxis{r.x, r.y, g.kind[at]};
+}
+// (the same in every lane)
+__device__ __forceinline__ BrickAxis uniform(const BrickAxis& a) {
+  return BrickAxis{(uint32_t)__builtin_amdgcn_readfirstlane((int)a.first), (uint32_t)__builtin_amdgcn_readfirstlane((int)a.n),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)a.kind)};
+}
+
+// Stores four words of a brick as one 16-byte vector at any 4-byte address
+// (the caller's buffer; gfx950 takes such a store whole.  A branch on the
+// alignment was merged into four scattered words: 303 against 156 us below).
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store4(uint32_t* out, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  *reinterpret_cast<Words4*>(out) = Words4{a, b, c, d};
+}
+
+// Adds a wave's nodes (by lane 0) to one of the kNodeSlots pairs of totals.
+__device__ __forceinline__ void add_totals(const NodeArgs& g, uint32_t wave_no, uint32_t inside, uint32_t split) {
+  unsigned long long* slot = (unsigned long long*)g.partial + 2 * (wave_no % kNodeSlots);
+  if (__lane_id() == 0 && inside != 0) atomicAdd(slot, (unsigned long long)inside);
+  if (__lane_id() == 0 && split != 0) atomicAdd(slot + 1, (unsigned long long)split);
+}
+
+// Bricks that are one value: a wave looks at 64 consecutive bricks at once, a
+// brick per lane, so that one round of loads is waited for before 64 bricks
+// of stores; what remains is the writing: 0.96 GiB at w = 2048 in 156 us, the
+// rate of a plain fill.  The others are listed for classify_nodes_kernel.
+__global__ void __launch_bounds__(kUniformBlock) uniform_nodes_kernel(NodeArgs g, uint32_t per) {
+  __shared__ uint32_t s_n[kUniformWaves], s_at;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nb = (uint32_t)g.nb, n_bricks = nb * nb * nb;
+  const uint32_t wave_no = blockIdx.x * kUniformWaves + wave;
+  const uint32_t first = min(wave_no * per, n_bricks), end = min(first + per, n_bricks), brick = first + lane;
+  bool in = false, split = false, plain = false;
+  if (brick < end) {
+    const BrickAxis x = brick_axis(g, brick), y = brick_axis(g, (size_t)n_bricks + brick),
+                    z = brick_axis(g, 2 * (size_t)n_bricks + brick);
+    const uint32_t bi = brick % nb, bj = brick / nb % nb, bk = brick / (nb * nb);
+    in = x.kind + y.kind + z.kind >= 2;
+    split = x.kind != y.kind || x.kind != z.kind;
+    // (bricks that reach beyond the grid are masked: listed unless outside)
+    plain = (x.n | y.n | z.n) == 0 && x.kind != kMixed && y.kind != kMixed && z.kind != kMixed &&
+            ((!in && !split) || (32 * bi + 32 <= (uint32_t)g.w && 32 * bj + 32 <= (uint32_t)g.w && 32 * bk + 32 <= (uint32_t)g.w));
+  }
+  const uint64_t m_plain = __ballot(plain), m_in = __ballot(plain && in);
+  const uint64_t m_list = __ballot(brick < end && !plain);
+  // one atomic per workgroup: they queue at the counter
+  if (lane == 0) s_n[wave] = (uint32_t)__popcll(m_list);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t n = 0;
+    for (int k = 0; k < kUniformWaves; ++k) {
+      const uint32_t c = s_n[k];
+      s_n[k] = n;
+      n += c;
+    }
+    s_at = n != 0 ? atomicAdd(g.n_mixed, n) : 0u;
+  }
+  __syncthreads();
+  if ((m_list >> lane) & 1u)
+    g.mixed[s_at + s_n[wave] + (uint32_t)__popcll(m_list & ((1ull << lane) - 1ull))] = brick;
+  add_totals(g, wave_no, 32768u * (uint32_t)__popcll(m_in), 32768u * (uint32_t)__popcll(__ballot(plain && split)));
+  // (waves start at different bricks of theirs: in step they would all write
+  // addresses a power of two apart, the same memory channels)
+  const uint32_t turn = (wave_no * 5u) & 63u;
+  for (uint64_t todo = turn ? m_plain >> turn | m_plain << (64 - turn) : m_plain; todo != 0; todo &= todo - 1) {
+    const uint32_t b = ((uint32_t)__ffsll((unsigned long long)todo) - 1u + turn) & 63u;
+    const uint32_t v = (m_in >> b) & 1u ? ~0u : 0u;
+    uint32_t* out = g.bits + (size_t)(first + b) * 1024 + 4 * lane;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) store4(out + 256 * m, v, v, v, v);
+  }
+}
+
+// The listed bricks, a wave each in turn; lane l holds the 16 words
+// 4 l + 256 m + c (m, c = 0..3): rows k = 8 m + l / 8, j = 4 (l % 8) + c.
+// One LDS matrix per wave serves the three axes in turn, four waves per SIMD
+// (123 registers; held to 80 they spill: 0.70 ms for all bricks against 0.47).
+// Bound by the latency of the list reads: 27,000 of scene64's 262,144 bricks
+// at w = 2048 in 0.10 ms.  The vote it replaced transposed a 32 x 32 bit matrix
+// per thread of every brick: 0.93 ms, and 1.05 ms for the flower at w = 333 (now 29
+// us), whose spans with more than two samples it walked.
+__global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs g) {
+  __shared__ uint4 s_mat[kNodeWaves][256];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = g.w, nb = g.nb;
+  const uint32_t n_bricks = (uint32_t)nb * nb * nb;
+  const int jq = lane & 7, kk = lane >> 3;
+  uint4* mat = s_mat[wave];
+  uint32_t* mat1 = reinterpret_cast<uint32_t*>(mat);
+  auto sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // The first toggles of an axis, loaded ahead of their use.
+  struct Ahead {
+    uint32_t x[2];
+  };
+  auto ahead = [&](const BrickAxis& a, const uint16_t* list) {
+    Ahead r;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) r.x[q] = 64u * q + lane < a.n ? list[(size_t)a.first + 64 * q + lane] : 0u;
+    return r;
+  };
+  // XORs an axis's toggles into the matrix: bit(t, col, row) gives the word
+  // and its bits
+  auto scatter = [&](const BrickAxis& a, const Ahead& r, const uint16_t* list, auto&& bit) {
+    auto put = [&](uint32_t e, uint32_t x) {
+      uint32_t word, bits;
+      bit(x & 31u, (x >> 5) & 31u, x >> 10, word, bits);
+      if (e < a.n) atomicXor(&mat1[word], bits);
+    };
+#pragma unroll
+    for (int q = 0; q < 2; ++q) put(64 * q + lane, r.x[q]);
+    for (uint32_t e0 = 128; e0 < a.n; e0 += 256) {  // four loads in flight
+      uint32_t x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = e0 + 64 * q + lane < a.n ? list[(size_t)a.first + e0 + 64 * q + lane] : 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) put(e0 + 64 * q + lane, x[q]);
+    }
+    sync();
+  };
+  // takes the lane's words out of the matrix and clears them
+  auto take = [&](uint32_t (&v)[4][4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const uint4 x = mat[64 * m + lane];
+      v[m][0] = x.x; v[m][1] = x.y; v[m][2] = x.z; v[m][3] = x.w;
+      mat[64 * m + lane] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    sync();
+  };
+  // the start word of this lane (lane % 32) of an axis
+  auto start = [&](const BrickAxis& a, size_t at) -> uint32_t {
+    return a.kind == kMixed ? g.parity[at * 32 + (lane & 31)] : a.kind == kAllInside ? ~0u : 0u;
+  };
+
+  const uint32_t wave_no = blockIdx.x * kNodeWaves + wave, stride = gridDim.x * kNodeWaves;
+  const uint32_t n_listed = *g.n_mixed;
+  uint32_t n_inside = 0, n_split = 0;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) mat[64 * m + lane] = make_uint4(0u, 0u, 0u, 0u);
+  sync();
+  for (uint32_t at = wave_no; at < n_listed; at += stride) {
+    const uint32_t brick = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.mixed[at]);
+    const BrickAxis vx = brick_axis(g, brick), vy = brick_axis(g, (size_t)n_bricks + brick),
+                    vz = brick_axis(g, 2 * (size_t)n_bricks + brick);
+    const BrickAxis x = uniform(vx), y = uniform(vy), z = uniform(vz);
+    const int bi = (int)(brick % (uint32_t)nb), bj = (int)(brick / (uint32_t)nb % (uint32_t)nb),
+              bk = (int)(brick / ((uint32_t)nb * nb));
+    // bits along i of nodes of the grid
+    const int wi = w - 32 * bi;
+    const uint32_t ibits = wi >= 32 ? ~0u : (1u << wi) - 1u;
+    uint32_t* out = g.bits + (size_t)brick * 1024 + 4 * lane;
+    const Ahead list_x = ahead(x, g.toggles[0]), list_y = ahead(y, g.toggles[1]), list_z = ahead(z, g.toggles[2]);
+    uint32_t xw[4][4], yw[4][4];
+    const uint32_t px = start(x, brick), py = start(y, (size_t)n_bricks + brick),
+                   pz = start(z, 2 * (size_t)n_bricks + brick);
+    // x: a ray is a word; its toggles flip the nodes from theirs on
+    if (x.n > 0) {
+      scatter(x, list_x, g.toggles[0], [](uint32_t t, uint32_t col, uint32_t row, uint32_t& word, uint32_t& bits) {
+        word = row * 32 + col;
+        bits = ~0u << t;
+      });
+      take(xw);
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) xw[m][c] = 0u;
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const uint32_t row = (uint32_t)__shfl((int)px, 8 * m + kk, 64) >> (4 * jq);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) xw[m][c] ^= 0u - ((row >> c) & 1u);
+    }
+    // y: prefix along j, in the lane's four words and over the 8 lanes of a row
+    if (y.n > 0) {
+      scatter(y, list_y, g.toggles[1], [](uint32_t t, uint32_t col, uint32_t row, uint32_t& word, uint32_t& bits) {
+        word = col * 32 + t;
+        bits = 1u << row;
+      });
+      take(yw);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        yw[m][1] ^= yw[m][0];
+        yw[m][2] ^= yw[m][1];
+        yw[m][3] ^= yw[m][2];
+        uint32_t s = yw[m][3];
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) {
+          const uint32_t q = (uint32_t)__shfl_up((int)s, o, 64);
+          if (jq >= o) s ^= q;
+        }
+        s ^= yw[m][3];  // the lanes before
+#pragma unroll
+        for (int c = 0; c < 4; ++c) yw[m][c] ^= s;
+      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) yw[m][c] = 0u;
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const uint32_t p = (uint32_t)__shfl((int)py, 8 * m + kk, 64);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) yw[m][c] ^= p;
+    }
+    // z: prefix along k, over the 8 lanes of a column and then the groups m,
+    // straight into the majority of the three words; rays beyond the grid are
+    // outside, so only the disagreements need the mask of the grid's nodes
+    if (z.n > 0)
+      scatter(z, list_z, g.toggles[2], [](uint32_t t, uint32_t col, uint32_t row, uint32_t& word, uint32_t& bits) {
+        word = t * 32 + row;
+        bits = 1u << col;
+      });
+    uint32_t p[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) p[c] = (uint32_t)__shfl((int)pz, 4 * jq + c, 64);
+    uint32_t ni = 0, ns = 0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      uint32_t zw[4] = {p[0], p[1], p[2], p[3]};
+      if (z.n > 0) {
+        const uint4 v = mat[64 * m + lane];
+        mat[64 * m + lane] = make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          uint32_t s = u[c];
+#pragma unroll
+          for (int o = 8; o < 64; o <<= 1) {
+            const uint32_t q = (uint32_t)__shfl_up((int)s, o, 64);
+            if (lane >= o) s ^= q;
+          }
+          zw[c] = s ^ p[c];
+          p[c] ^= (uint32_t)__shfl((int)s, 56 + jq, 64);
+        }
+      }
+      uint32_t in[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t a = xw[m][c], b = yw[m][c], d = zw[c];
+        const uint32_t live = (32 * bj + 4 * jq + c < w && 32 * bk + 8 * m + kk < w) ? ibits : 0u;
+        in[c] = ((a & b) | (d & (a | b))) & live;
+        ni += __popc(in[c]);
+        ns += __popc(((a ^ b) | (a ^ d)) & live);
+      }
+      store4(out + 256 * m, in[0], in[1], in[2], in[3]);
+    }
+    n_inside += ni;
+    n_split += ns;
+  }
+  // (a lane sees fewer than 2^32 nodes: 512 of each brick)
   uint64_t a = n_inside, b = n_split;
   for (int o = 32; o > 0; o >>= 1) {
-    a += __shfl_xor(a, o);
-    b += __shfl_xor(b, o);
+    a += __shfl_xor((unsigned long long)a, o);
+    b += __shfl_xor((unsigned long long)b, o);
   }
-  if ((tid & 63) == 0) {
-    s_sum[0][tid >> 6] = a;
-    s_sum[1][tid >> 6] = b;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t sa = 0, sb = 0;
-    for (int q = 0; q < kVoteBlock / 64; ++q) {
-      sa += s_sum[0][q];
-      sb += s_sum[1][q];
-    }
-    g.partial[2 * blockIdx.x] = sa;
-    g.partial[2 * blockIdx.x + 1] = sb;
-  }
+  unsigned long long* slot = (unsigned long long*)g.partial + 2 * (wave_no % kNodeSlots);
+  if (lane == 0 && a != 0) atomicAdd(slot, (unsigned long long)a);
+  if (lane == 0 && b != 0) atomicAdd(slot + 1, (unsigned long long)b);
 }
 
-// Sums the workgroups' (inside, split) counts into stats[0..1] (one block).
-__global__ __launch_bounds__(kNodeBlock) void node_stats_kernel(const uint64_t* partial, uint32_t n, uint64_t* stats) {
-  __shared__ uint64_t s_sum[2][kNodeBlock / 64];
+// Sums the (inside, split) counts of the kNodeSlots slots and writes the status word and
+// both sums (low, high word each) to pinned host memory (one block).
+__global__ void __launch_bounds__(kNodeBlock) node_stats_kernel(const uint64_t* partial, uint32_t n, const uint32_t* status,
+                                                                uint32_t* host) {
+  __shared__ uint64_t s_sum[2][kNodeWaves];
   uint64_t a = 0, b = 0;
   for (uint32_t q = threadIdx.x; q < n; q += kNodeBlock) {
     a += partial[2 * q];
@@ -433,41 +569,42 @@ __global__ __launch_bounds__(kNodeBlock) void node_stats_kernel(const uint64_t* 
   __syncthreads();
   if (threadIdx.x == 0) {
     uint64_t sa = 0, sb = 0;
-    for (int q = 0; q < kNodeBlock / 64; ++q) {
+    for (int q = 0; q < kNodeWaves; ++q) {
       sa += s_sum[0][q];
       sb += s_sum[1][q];
     }
-    stats[0] = sa;
-    stats[1] = sb;
+    host[0] = *status;
+    host[1] = (uint32_t)sa;
+    host[2] = (uint32_t)(sa >> 32);
+    host[3] = (uint32_t)sb;
+    host[4] = (uint32_t)(sb >> 32);
   }
+  __threadfence_system();
 }
 
 }  // namespace
 
-uint32_t node_workgroups(int32_t w) {
-  const uint32_t S = (uint32_t)((w + kSpan - 1) / kSpan);
-  return S * S;
-}
-
-size_t node_code_bytes(int32_t w) {
-  const size_t S = (size_t)((w + kSpan - 1) / kSpan);
-  return 3 * S * S * S * 4096 * sizeof(uint16_t);
-}
-
-hipError_t launch_node_codes(const NodeArgs& g, hipStream_t s) {
-  const int64_t npix = (int64_t)g.w * g.w;
-  hipLaunchKernelGGL(node_codes_kernel, dim3((unsigned)((npix + kNodeBlock - 1) / kNodeBlock), 3), dim3(kNodeBlock),
-                     sizeof(float) * (size_t)g.w, s, g);
+hipError_t launch_node_bins(const NodeArgs& g, hipStream_t s) {
+  const uint32_t lds = sizeof(uint32_t) * (uint32_t)g.nb * (1 + kParityStride);  // 34 KB at w = 8192
+  hipLaunchKernelGGL(node_bin_kernel, dim3((uint32_t)g.nb * g.nb, 3), dim3(kBinBlock), lds, s, g);
   return hipGetLastError();
 }
 
 hipError_t launch_classify_nodes(const NodeArgs& g, hipStream_t s) {
-  hipLaunchKernelGGL(classify_nodes_kernel, dim3(node_workgroups(g.w)), dim3(kVoteBlock), 0, s, g);
+  const uint32_t bricks = (uint32_t)g.nb * g.nb * g.nb;
+  // bricks per wave: up to 64, fewer where that leaves under 4096 waves (16 per CU)
+  const uint32_t per = bricks / 4096 < 1 ? 1 : bricks / 4096 > 64 ? 64 : bricks / 4096;
+  const uint32_t group = per * kUniformWaves;
+  hipLaunchKernelGGL(uniform_nodes_kernel, dim3((bricks + group - 1) / group), dim3(kUniformBlock), 0, s, g, per);
+  // as many workgroups as stay resident (four per CU), at most one wave a brick
+  const uint32_t blocks = (bricks + kNodeWaves - 1) / kNodeWaves;
+  hipLaunchKernelGGL(classify_nodes_kernel, dim3(blocks < 1024 ? blocks : 1024), dim3(kNodeBlock), 0, s, g);
   return hipGetLastError();
 }
 
-hipError_t launch_node_stats(const NodeArgs& g, hipStream_t s) {
-  hipLaunchKernelGGL(node_stats_kernel, dim3(1), dim3(kNodeBlock), 0, s, g.partial, node_workgroups(g.w), g.stats);
+hipError_t launch_node_stats(const NodeArgs& g, uint32_t* host, hipStream_t s) {
+  hipLaunchKernelGGL(node_stats_kernel, dim3(1), dim3(kNodeBlock), 0, s, g.partial, kNodeSlots, g.status,
+                     host);
   return hipGetLastError();
 }
 
