@@ -1448,6 +1448,24 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   g.n_saved = use_saved ? n_saved : 0u;
   g.deep = reinterpret_cast<uint32_t*>(wb + o_deep);
   g.n_deep = 0;
+  // Depth cells of half a radius, or of three quarters where those are too
+  // many (more chords are then shorter than a cell); with more than
+  // kUnionCells even so, every ray is swept over all its events.
+  g.rest = g.ray_cursor;  // (free once the spheres are binned)
+  for (const double part : {0.5, 0.75}) {
+    const double cell = part * g.r;
+    double most = 0.0;
+    for (int d = 0; d < 3; ++d) most = std::max(most, ((double)bbox[3 + d] - (double)bbox[d]) / cell);
+    if (!(most + 1.0 <= (double)kUnionCells)) continue;
+    g.n_cells = (int32_t)std::floor(most) + 1;
+    g.inv_cell = 1.0 / cell;
+    // (more than a cell, so that a chord covers its cell whatever the float64
+    // rounding of its centre, its ends and the cell's number)
+    double far = 0.0;
+    for (int d = 0; d < 6; ++d) far = std::max(far, std::fabs((double)bbox[d]));
+    g.long_chord = cell * (1.0 + std::ldexp(1.0, -20)) + std::ldexp(far, -48);
+    break;
+  }
   void* scr = wb + o_scratch;
 #define OSTEP(expr, what)                                  \
   do {                                                     \

@@ -306,6 +306,8 @@ constexpr int kOffsetKeep = 896;              // a full window is cut back to fe
 constexpr int kOffsetEmit = 128;              // end points of one ray's result before small volumes go
 constexpr int kOffsetSavedMax = 64;           // most end points per ray the count pass keeps for the write pass
 constexpr int kOffsetDeep = 512;              // a ray with more spheres than this is started first
+constexpr int kUnionEvents = 192;             // events of a ray that the count pass takes after merging chords
+constexpr int kUnionCells = 768;              // most depth cells of a ray (12 KB of LDS per wave)
 constexpr uint32_t kMaxSpheres = 1u << 30;    // sphere numbers fit 30 bits of the sort key
 struct OffsetArgs {
   AxisArrays in[3];
@@ -332,6 +334,12 @@ struct OffsetArgs {
   // the ray passes; status[16] counts them on the device)
   uint32_t* deep;
   uint32_t n_deep;
+  // depth cells of the count pass (n_cells = 0: every ray is swept over all its
+  // events): 1 / cell size, the half length from which a chord covers its cell,
+  // and the rays left to the sweep (status[17] of them)
+  int32_t n_cells;
+  double inv_cell, long_chord;
+  uint32_t* rest;
   uint32_t* status;  // kStatusMismatch: bad input offsets; kStatusOutFull: a ray's window or end points overflow
 };
 hipError_t launch_offset_centres(const OffsetArgs& g, hipStream_t s);

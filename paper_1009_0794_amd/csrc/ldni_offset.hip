@@ -21,11 +21,15 @@
 //
 // Passes: the sphere centres (one thread per pixel); binning of the spheres
 // into the lists of the rays they hit (count, scan, scatter); then one wave
-// per ray, twice (count, write): the ray's events go to a wave-private LDS
-// buffer as 64-bit keys (orderable depth, order), window by window in depth
-// when they do not fit, a bitonic sort orders them, and a sweep in chunks of
-// 64 (wave prefix sums of H's parity and of the open spheres, group starts by
-// a max-scan) finds the result's end points.
+// per ray, twice.  The count pass (offset_union_kernel) merges the chords of a
+// ray into the few intervals they cover together before it sorts anything, and
+// keeps the result's end points for the write pass.  Rays that this leaves with
+// too many events, and rays with more end points than are kept, go through the
+// sweep over all events (sweep_ray): they go to a wave-private LDS buffer as
+// 64-bit keys (orderable depth, order), window by window in depth when they do
+// not fit, a bitonic sort orders them, and a sweep in chunks of 64 (wave prefix
+// sums of H's parity and of the open spheres, group starts by a max-scan) finds
+// the result's end points.
 // Nothing is a contraction: the work is the exact chord tests and the sorts.
 #pragma clang fp contract(off)
 
@@ -356,36 +360,37 @@ __device__ __forceinline__ void write_event(const OffsetArgs& g, int a, int64_t 
 // window's (exclusive) upper bound.  Windows end between groups of equal
 // depth, and the sweep carries H's parity, the open spheres and the result
 // state from one window to the next.
-template <bool kWrite>
-__global__ __launch_bounds__(kOffBlock) void offset_ray_kernel(OffsetArgs g) {
-  __shared__ uint64_t s_key[kOffWaves][kOffsetBuf];
-  __shared__ uint64_t s_emit[kOffWaves][kOffsetEmit];
-  __shared__ uint32_t s_rbit[kOffWaves][kOffsetBuf / 32];
-  __shared__ uint32_t s_hist[kOffWaves][32];
+struct RayLds {
+  uint64_t key[kOffWaves][kOffsetBuf];
+  uint64_t emit[kOffWaves][kOffsetEmit];
+  uint32_t rbit[kOffWaves][kOffsetBuf / 32];
+  uint32_t hist[kOffWaves][32];
+};
 
+// The ray of a wave: waves take the deep rays first (workgroups start in
+// index order, so the longest rays do not end up as the launch's tail), then
+// every ray in order, skipping the deep ones (-1: none).
+__device__ __forceinline__ int64_t ray_of_wave(const OffsetArgs& g, int64_t wave_no) {
+  if (wave_no < (int64_t)g.n_deep) return g.deep[wave_no];
+  const int64_t ray = wave_no - g.n_deep;
+  if (ray >= 3 * (int64_t)g.w * g.w) return -1;
+  if (g.n_deep > 0 && g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep) return -1;
+  return ray;
+}
+
+template <bool kWrite>
+__device__ void sweep_ray(const OffsetArgs& g, int64_t ray, RayLds& lds) {
   const int wv = threadIdx.x >> 6;
   const uint32_t lane = lane_id();
   const int64_t npix = (int64_t)g.w * g.w;
-  // Waves take the deep rays first (workgroups start in index order, so the
-  // longest rays do not end up as the launch's tail), then every ray in
-  // order, skipping the deep ones.
-  const int64_t wave_no = (int64_t)blockIdx.x * kOffWaves + wv;
-  int64_t ray;
-  if (wave_no < (int64_t)g.n_deep) {
-    ray = g.deep[wave_no];
-  } else {
-    ray = wave_no - g.n_deep;
-    if (ray >= 3 * npix) return;
-    if (g.n_deep > 0 && g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep) return;
-  }
   const int a = (int)(ray / npix);
   const int64_t p = ray - a * npix;
   const int u = (a + 1) % 3, v = (a + 2) % 3;
   const int iu = (int)(p % g.w), iv = (int)(p / g.w);
   const double cu = centre_of(g, u, iu), cv = centre_of(g, v, iv);
-  uint64_t* key = s_key[wv];
-  uint64_t* emit = s_emit[wv];
-  uint32_t* rbit = s_rbit[wv];
+  uint64_t* key = lds.key[wv];
+  uint64_t* emit = lds.emit[wv];
+  uint32_t* rbit = lds.rbit[wv];
   const AxisArrays& H = g.in[a];
 
   // the write pass's slot of the ray: out .. out + cnt
@@ -530,7 +535,7 @@ __global__ __launch_bounds__(kOffBlock) void offset_ray_kernel(OffsetArgs g) {
       if (n + total > (uint32_t)kOffsetBuf) {
         // the depth of the kOffsetKeep-th smallest event becomes the bound;
         // the events before it are compacted to the front (unsorted)
-        const uint32_t cut = select_depth(key, n, (uint32_t)kOffsetKeep, s_hist[wv]);
+        const uint32_t cut = select_depth(key, n, (uint32_t)kOffsetKeep, lds.hist[wv]);
         uint32_t m = 0;
         for (uint32_t c0 = 0; c0 < n; c0 += 64) {
           const uint32_t q = c0 + lane;
@@ -656,6 +661,398 @@ __global__ __launch_bounds__(kOffBlock) void offset_ray_kernel(OffsetArgs g) {
   if (kWrite && lane == 0 && 2 * kept != cnt) atomicOr(g.status, kStatusMismatch);
 }
 
+template <bool kWrite>
+__global__ __launch_bounds__(kOffBlock) void offset_ray_kernel(OffsetArgs g) {
+  __shared__ RayLds lds;
+  const int64_t ray = ray_of_wave(g, (int64_t)blockIdx.x * kOffWaves + (threadIdx.x >> 6));
+  if (ray >= 0) sweep_ray<kWrite>(g, ray, lds);
+}
+
+// The rays that offset_union_kernel left (g.rest), wave after wave.
+__global__ __launch_bounds__(kOffBlock) void offset_rest_kernel(OffsetArgs g) {
+  __shared__ RayLds lds;
+  const uint32_t n = min(g.status[17], (uint32_t)(3 * (int64_t)g.w * g.w));
+  for (uint32_t q = blockIdx.x * kOffWaves + (threadIdx.x >> 6); q < n; q += gridDim.x * kOffWaves) {
+    sweep_ray<false>(g, g.rest[q], lds);
+    wave_sync();
+  }
+}
+
+// 64-bit words of LDS for a wave's cells: enter and leave keys (n + 4 each), a
+// bit and a 16-bit list entry per cell.
+__host__ __device__ constexpr int union_words(int n_cells) {
+  return 2 * (n_cells + 4) + (n_cells / 64 + 1) + (n_cells / 4 + 1);
+}
+
+// The count pass of a ray, one wave: most of the spheres that hit a ray lie
+// along the few places where the ray crosses or grazes the surface and overlap
+// there, and only the ends of their union matter.  The ray's depth range is
+// divided into cells of half a radius.  A chord at least a cell to either side
+// of its centre (long) covers its whole cell, so the long chords of a cell
+// together are one interval, and so are those of a run of neighbouring cells:
+// nothing inside it can change the state of the spheres, which stays "one is
+// open" throughout.  A cell keeps its first enter (depth, then order) and its
+// last exit (depth, then the least order at that depth) by LDS min / max; a run
+// of cells becomes two events, its first enter and its last exit.  The other
+// chords (short, or outside the cells) are dropped when they lie strictly
+// inside the interval of their cell and its neighbours and are events of their
+// own otherwise.  An event that is dropped lies strictly inside an interval
+// that is kept, so it could neither change the result nor be the first event of
+// a group that does: the end points are those of the sweep over all events.
+// The few events left are sorted (each finds its rank among at most 64 by
+// reading them all, more by wave_sort) and swept as in sweep_ray.  A ray with
+// more than kUnionEvents of them is listed for offset_rest_kernel.
+// Bound by the latency of a ray's dependent loads (starts, list, centres) at the
+// 20 waves that its LDS leaves a CU.  On the flower, r = 2 pixels: 0.27 ms at w =
+// 256 and 0.075 at 128, where sweeping every ray over all its events (one LDS
+// sort of up to 1,024 keys a window) took 1.60 and 0.74 ms.  Cells of three
+// quarters of a radius: 0.31 and 0.096 (more short chords); 128 or 256 events:
+// 0.27 / 0.36 ms at w = 256, but with 128 one polar ray of w = 128 is left to the
+// sweep, 0.02 ms.
+__global__ __launch_bounds__(kOffBlock) void offset_union_kernel(OffsetArgs g) {
+  extern __shared__ uint64_t s_union[];
+  __shared__ uint64_t s_buf[kOffWaves][2][kUnionEvents];
+  __shared__ uint32_t s_rbit[kOffWaves][kUnionEvents / 32 + 2];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = lane_id();
+  const int64_t ray = ray_of_wave(g, (int64_t)blockIdx.x * kOffWaves + wv);
+  if (ray < 0) return;
+  const int64_t npix = (int64_t)g.w * g.w;
+  const int a = (int)(ray / npix);
+  const int64_t p = ray - a * npix;
+  const int u = (a + 1) % 3, v = (a + 2) % 3;
+  const AxisArrays& H = g.in[a];
+  const uint32_t o0 = H.offsets[p], o1 = H.offsets[p + 1];
+  const uint32_t l0 = g.ray_start[ray], l1 = g.ray_start[ray + 1];
+  uint32_t nh = 0;
+  if (o1 < o0 || (uint64_t)o1 > H.n) {
+    if (lane == 0) atomicOr(g.status, kStatusMismatch);
+  } else {
+    nh = (o1 - o0) & ~1u;
+  }
+  if (nh == 0 && l0 == l1) {
+    if (lane == 0) g.counts[a][p] = 0u;
+    return;
+  }
+  auto give_up = [&] {
+    if (lane == 0) g.rest[atomicAdd(&g.status[17], 1u)] = (uint32_t)ray;
+  };
+  const double cu = centre_of(g, u, (int)(p % g.w)), cv = centre_of(g, v, (int)(p / g.w));
+  const double r2 = g.r * g.r, lo_a = g.lo[a];
+  // cell c at index c + 1, empty cells before the first and behind the last
+  const int n_cells = g.n_cells, n_slots = n_cells + 4;
+  uint64_t* enter = s_union + (size_t)wv * union_words(n_cells);
+  uint64_t* leave = enter + n_slots;
+  uint64_t* taken = leave + n_slots;                             // bit c: cell c holds a chord
+  uint16_t* cells = reinterpret_cast<uint16_t*>(taken + n_cells / 64 + 1);  // the cells that do, in any order
+  uint32_t n_taken = 0;
+  uint64_t* buf = s_buf[wv][0];
+  uint64_t* buf2 = s_buf[wv][1];
+  uint32_t n = 0;  // keys in buf
+  const uint64_t below = (1ull << lane) - 1ull;
+
+  if (l0 != l1) {
+    for (int c = (int)lane; c < n_slots; c += 64) {
+      enter[c] = ~0ull;
+      leave[c] = 0ull;
+    }
+    if ((int)lane <= n_cells / 64) taken[lane] = 0ull;
+    wave_sync();
+    // whether the chord [d0, d1] (orderable depths) lies strictly inside the
+    // interval of the cell of its middle and the cells beside it
+    auto inside = [&](uint32_t d0, uint32_t d1) -> bool {
+      auto depth = [](uint32_t b) -> double {
+        return (double)__uint_as_float((b & 0x80000000u) ? (b & 0x7fffffffu) : ~b);
+      };
+      const double mid = 0.5 * (depth(d0) + depth(d1)) * g.inv_cell;
+      if (!(mid >= 0.0 && mid < (double)n_cells)) return false;
+      const int c = (int)mid + 1;
+      const uint32_t e0 = (uint32_t)(enter[c - 1] >> 32), e1 = (uint32_t)(enter[c] >> 32), e2 = (uint32_t)(enter[c + 1] >> 32);
+      const uint32_t x0 = (uint32_t)(leave[c - 1] >> 32), x1 = (uint32_t)(leave[c] >> 32), x2 = (uint32_t)(leave[c + 1] >> 32);
+      // an empty cell's interval is (~0, 0) and holds nothing; a cell between
+      // two joins them
+      if (leave[c] != 0ull) return min(min(e0, e1), e2) < d0 && max(max(x0, x1), x2) > d1;
+      return (e0 < d0 && x0 > d1) || (e2 < d0 && x2 > d1);
+    };
+    // drops the chords of buf that lie inside (pairs of keys), keeping order
+    auto filter = [&] {
+      wave_sync();
+      uint32_t m = 0;
+      for (uint32_t q0 = 0; q0 < n; q0 += 128) {
+        const uint32_t q = q0 + 2 * lane;
+        uint64_t k0 = 0, k1 = 0;
+        bool keep = false;
+        if (q < n) {
+          k0 = buf[q];
+          k1 = buf[q + 1];
+          keep = !inside((uint32_t)(k0 >> 32), (uint32_t)(k1 >> 32));
+        }
+        const uint64_t bal = __ballot(keep);
+        wave_sync();
+        if (keep) {
+          const uint32_t at = m + 2 * (uint32_t)__popcll(bal & below);
+          buf[at] = k0;
+          buf[at + 1] = k1;
+        }
+        m += 2 * (uint32_t)__popcll(bal);
+      }
+      n = m;
+      wave_sync();
+    };
+    // Calls on(live, long, cell, enter key, exit key) for the chords of the
+    // ray's spheres, 64 at a time; loads run ahead (list entries two chunks,
+    // centres one chunk) so that a chunk's tests do not wait for them.
+    auto chords = [&](auto&& on) {
+      uint32_t sph1 = 0, sph2 = 0;
+      double cu1 = 0.0, cv1 = 0.0, ca1 = 0.0;
+      if (l0 + lane < l1) {
+        sph1 = g.list[l0 + lane];
+        const double* c = g.centres + 3 * (size_t)sph1;
+        cu1 = c[u];
+        cv1 = c[v];
+        ca1 = c[a];
+      }
+      if (l0 + 64 + lane < l1) sph2 = g.list[l0 + 64 + lane];
+      for (uint32_t base = l0; base < l1; base += 64) {
+        const uint32_t e = base + lane;
+        const uint32_t sph = sph1;
+        const double pu = cu1, pv = cv1, pa = ca1;
+        if (e + 64 < l1) {
+          const double* c = g.centres + 3 * (size_t)sph2;
+          cu1 = c[u];
+          cv1 = c[v];
+          ca1 = c[a];
+        }
+        sph1 = sph2;
+        if (e + 128 < l1) sph2 = g.list[e + 128];
+        const double du = cu - pu, dv = cv - pv;
+        const double rho2 = du * du + dv * dv;
+        const bool live = e < l1 && rho2 < r2;
+        const double t = sqrt(live ? r2 - rho2 : 0.0);
+        const float d0 = (float)((pa - t) - lo_a), d1 = (float)((pa + t) - lo_a);
+        const uint64_t ka = ((uint64_t)orderable(d0) << 32) | kSphereOrder | (sph << 1),
+                       kb = ((uint64_t)orderable(d1) << 32) | kSphereOrder | (sph << 1) | 1u;
+        const double cell = (pa - lo_a) * g.inv_cell;
+        const bool whole = t >= g.long_chord && cell >= 0.0 && cell < (double)n_cells && (ka >> 32) < (kb >> 32);
+        on(live, whole, (int)cell, ka, kb);
+      }
+    };
+    // appends a pair of keys; false: they do not fit
+    auto append = [&](bool own, uint64_t ka, uint64_t kb) -> bool {
+      const uint64_t bal = __ballot(own);
+      const uint32_t more = 2 * (uint32_t)__popcll(bal);
+      if (n + more > (uint32_t)kUnionEvents) return false;
+      if (own) {
+        const uint32_t at = n + 2 * (uint32_t)__popcll(bal & below);
+        buf[at] = ka;
+        buf[at + 1] = kb;
+      }
+      n += more;
+      return true;
+    };
+    bool again = false;  // too many chords that are not long: taken once the cells are complete
+    chords([&](bool live, bool whole, int c, uint64_t ka, uint64_t kb) {
+      bool fresh = false;
+      if (live && whole) {
+        fresh = atomicMin((unsigned long long*)&enter[c + 1], (unsigned long long)ka) == ~0ull;
+        // (the depth, then the complement of the order: the maximum has the least order)
+        atomicMax((unsigned long long*)&leave[c + 1], (unsigned long long)(kb ^ 0xffffffffull));
+      }
+      const uint64_t bal = __ballot(fresh);
+      if (fresh) {
+        atomicOr((unsigned long long*)&taken[c >> 6], 1ull << (c & 63));
+        cells[n_taken + (uint32_t)__popcll(bal & below)] = (uint16_t)c;
+      }
+      n_taken += (uint32_t)__popcll(bal);
+      if (!again && !append(live && !whole, ka, kb)) again = true;
+    });
+    wave_sync();
+    bool fits = true;
+    if (again) {
+      n = 0;
+      chords([&](bool live, bool whole, int, uint64_t ka, uint64_t kb) {
+        const bool own = live && !whole && !inside((uint32_t)(ka >> 32), (uint32_t)(kb >> 32));
+        if (fits && !append(own, ka, kb)) fits = false;
+      });
+    } else {
+      filter();
+    }
+    if (!fits) {
+      give_up();
+      return;
+    }
+    wave_sync();
+    // runs of cells; the first enter of a run lies in one of its first three
+    // cells and the last exit in one of its last three (a chord reaches at most
+    // two cells beyond its own, and the run's end cells are covered whole)
+    for (uint32_t q0 = 0; q0 < n_taken; q0 += 64) {
+      bool first = false, last = false;
+      uint64_t ke = 0, kx = 0;
+      if (q0 + lane < n_taken) {
+        const int c = (int)cells[q0 + lane] + 1;
+        first = leave[c - 1] == 0ull;
+        last = leave[c + 1] == 0ull;
+        if (first) {
+          ke = enter[c];
+          if (!last) {
+            ke = min(ke, enter[c + 1]);
+            if (leave[c + 2] != 0ull) ke = min(ke, enter[c + 2]);
+          }
+        }
+        if (last) {
+          kx = leave[c];
+          if (!first) {
+            kx = max(kx, leave[c - 1]);
+            if (leave[c - 2] != 0ull) kx = max(kx, leave[c - 2]);  // (c - 1 is a cell)
+          }
+          kx ^= 0xffffffffull;
+        }
+      }
+      const uint64_t m0 = __ballot(first), m1 = __ballot(last);
+      const uint32_t more = (uint32_t)__popcll(m0) + (uint32_t)__popcll(m1);
+      if (more == 0) continue;
+      if (n + more > (uint32_t)kUnionEvents) {
+        give_up();
+        return;
+      }
+      uint32_t at = n + (uint32_t)__popcll(m0 & below) + (uint32_t)__popcll(m1 & below);
+      if (first) buf[at++] = ke;
+      if (last) buf[at] = kx;
+      n += more;
+    }
+  }
+  wave_sync();
+  // The solid's samples.  Strictly inside a run the result does not depend on
+  // the solid (and every sample is, as a rule, inside the run of its own
+  // sphere), so of consecutive samples inside one run only the parity counts:
+  // one is kept if they are odd, none if they are even.
+  {
+    // the cell of a sample strictly inside the interval of its cell, else -1
+    auto cell_of = [&](uint32_t k) -> int {
+      if (k >= nh || l0 == l1) return -1;
+      const float d = H.depth[o0 + k];
+      const uint32_t b = orderable(d);
+      const double cell = (double)d * g.inv_cell;
+      if (!(cell >= 0.0 && cell < (double)n_cells)) return -1;
+      const int c = (int)cell;
+      return (uint32_t)(enter[c + 1] >> 32) < b && (uint32_t)(leave[c + 1] >> 32) > b ? c : -1;
+    };
+    // whether two such samples' cells are of one run: no empty cell between
+    auto joined = [&](int c, int d) -> bool {
+      if (c < 0 || d < 0) return false;
+      if (c > d) {
+        const int x = c;
+        c = d;
+        d = x;
+      }
+      for (int q = c >> 6; q <= d >> 6; ++q) {
+        uint64_t gaps = ~taken[q];
+        if (q == c >> 6) gaps &= ~0ull << (c & 63);
+        if (q == d >> 6) gaps &= ~0ull >> (63 - (d & 63));
+        if (gaps != 0) return false;
+      }
+      return true;
+    };
+    uint32_t start = 0;     // first sample of the group of the sample before the chunk
+    int cell_before = -1;
+    for (uint32_t k0 = 0; k0 < nh; k0 += 64) {
+      const uint32_t k = k0 + lane;
+      const int cell = cell_of(k), next = cell_of(k + 1);
+      int prev = __shfl_up(cell, 1, 64);
+      if (lane == 0) prev = cell_before;
+      const bool head = !joined(prev, cell);
+      const uint64_t heads = __ballot(head) & (below | (1ull << lane));
+      const uint32_t first = heads ? k0 + 63u - (uint32_t)__clzll((long long)heads) : start;
+      const bool keep = k < nh && (cell < 0 || (!joined(cell, next) && ((k - first) & 1u) == 0u));
+      const uint64_t m = __ballot(keep);
+      if (n + (uint32_t)__popcll(m) > (uint32_t)kUnionEvents) {
+        give_up();
+        return;
+      }
+      if (keep) buf[n + (uint32_t)__popcll(m & below)] = ((uint64_t)orderable(H.depth[o0 + k]) << 32) | k;
+      n += (uint32_t)__popcll(m);
+      start = (uint32_t)__shfl((int)first, 63);
+      cell_before = __shfl(cell, 63);
+    }
+  }
+  wave_sync();
+  if (n == 0) {
+    if (lane == 0) g.counts[a][p] = 0u;
+    return;
+  }
+  uint64_t* key = buf;
+  uint64_t* emit = buf2;
+  if (n <= 64) {
+    const uint64_t mine = lane < n ? buf[lane] : ~0ull;
+    uint32_t rank = 0;
+    for (uint32_t q = 0; q < n; ++q) rank += buf[q] < mine ? 1u : 0u;
+    if (lane < n) buf2[rank] = mine;  // (every event has an order of its own)
+    key = buf2;
+    emit = buf;
+    wave_sync();
+  } else {
+    wave_sort(buf, n);
+  }
+  // the sweep of sweep_ray, over one window that holds all events
+  uint32_t* rbit = s_rbit[wv];
+  int carry_h = 0, carry_s = 0, carry_first = -1;
+  uint32_t n_emit = 0;
+  for (uint32_t c0 = 0; c0 < n; c0 += 64) {
+    const uint32_t q = c0 + lane;
+    const bool valid = q < n;
+    const uint64_t kq = valid ? key[q] : ~0ull;
+    const bool is_h = valid && !(kq & kSphereOrder);
+    const uint64_t hm = __ballot(is_h), xm = __ballot(valid && !is_h && (kq & 1u)), sm = __ballot(valid && !is_h);
+    const uint64_t upto = below | (1ull << lane);
+    const int ph = carry_h + __popcll(hm & upto);
+    const int ps = carry_s + __popcll(sm & upto) - 2 * __popcll(xm & upto);
+    const uint32_t dq = (uint32_t)(kq >> 32);
+    const bool first = valid && (q == 0 || (uint32_t)(key[q - 1] >> 32) != dq);
+    const bool last = valid && (q + 1 == n || (uint32_t)(key[q + 1] >> 32) != dq);
+    const uint64_t fm = __ballot(first) & upto;
+    const int fq = fm ? (int)c0 + 63 - __clzll((long long)fm) : carry_first;
+    const bool res = g.union_op ? ((ph & 1) != 0 || ps > 0) : ((ph & 1) != 0 && ps <= 0);
+    const uint64_t rm = __ballot(valid && res);
+    if (lane == 0) rbit[c0 >> 5] = (uint32_t)rm;
+    if (lane == 32) rbit[(c0 >> 5) + 1] = (uint32_t)(rm >> 32);
+    wave_sync();
+    const bool prev = fq > 0 && ((rbit[(fq - 1) >> 5] >> ((fq - 1) & 31)) & 1u) != 0;
+    const bool end = last && prev != res;
+    const uint64_t em = __ballot(end);
+    if (end) emit[n_emit + (uint32_t)__popcll(em & below)] = key[fq];
+    n_emit += (uint32_t)__popcll(em);
+    carry_h = __shfl(ph, 63);
+    carry_s = __shfl(ps, 63);
+    carry_first = __shfl(fq, 63);
+  }
+  wave_sync();
+  // small interval removal (a key holds its event's depth)
+  uint32_t kept = 0;
+  for (uint32_t m0 = 0; m0 < n_emit / 2; m0 += 64) {
+    const uint32_t m = m0 + lane;
+    bool keep = false;
+    uint64_t ea = 0, eb = 0;
+    if (m < n_emit / 2) {
+      ea = emit[2 * m];
+      eb = emit[2 * m + 1];
+      auto depth = [](uint64_t k) -> double {
+        const uint32_t b = (uint32_t)(k >> 32);
+        return (double)__uint_as_float((b & 0x80000000u) ? (b & 0x7fffffffu) : ~b);
+      };
+      const double th = depth(eb) - depth(ea);
+      keep = th > 0.0 && th >= g.eps;
+    }
+    const uint64_t km = __ballot(keep);
+    const uint32_t rank = kept + (uint32_t)__popcll(km & below);
+    if (keep && g.saved && 2 * rank + 1 < g.n_saved) {
+      g.saved[(size_t)ray * g.n_saved + 2 * rank] = ea;
+      g.saved[(size_t)ray * g.n_saved + 2 * rank + 1] = eb;
+    }
+    kept += (uint32_t)__popcll(km);
+  }
+  if (lane == 0) g.counts[a][p] = 2 * kept;
+}
+
 }  // namespace
 
 hipError_t launch_offset_centres(const OffsetArgs& g, hipStream_t s) {
@@ -676,7 +1073,15 @@ hipError_t launch_offset_bin(const OffsetArgs& g, bool scatter, hipStream_t s) {
 __global__ __launch_bounds__(kOffBlock) void offset_deep_kernel(OffsetArgs g) {
   const int64_t ray = (int64_t)blockIdx.x * kOffBlock + threadIdx.x;
   if (ray >= 3 * (int64_t)g.w * g.w) return;
-  if (g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep) g.deep[atomicAdd(&g.status[16], 1u)] = (uint32_t)ray;
+  // (one atomic per wave: they queue at the counter)
+  const bool deep = g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep;
+  const uint64_t m = __ballot(deep);
+  if (m == 0) return;
+  uint32_t at = 0;
+  const int lead = __ffsll((unsigned long long)m) - 1;
+  if ((int)lane_id() == lead) at = atomicAdd(&g.status[16], (uint32_t)__popcll(m));
+  at = (uint32_t)__shfl((int)at, lead, 64);
+  if (deep) g.deep[at + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = (uint32_t)ray;
 }
 
 hipError_t launch_offset_deep(const OffsetArgs& g, hipStream_t s) {
@@ -689,8 +1094,16 @@ hipError_t launch_offset_deep(const OffsetArgs& g, hipStream_t s) {
 hipError_t launch_offset_rays(const OffsetArgs& g, bool write, hipStream_t s) {
   const int64_t rays = 3 * (int64_t)g.w * g.w + g.n_deep;
   const dim3 grid((unsigned)((rays + kOffWaves - 1) / kOffWaves));
-  if (write) hipLaunchKernelGGL(offset_ray_kernel<true>, grid, dim3(kOffBlock), 0, s, g);
-  else hipLaunchKernelGGL(offset_ray_kernel<false>, grid, dim3(kOffBlock), 0, s, g);
+  if (write) {
+    hipLaunchKernelGGL(offset_ray_kernel<true>, grid, dim3(kOffBlock), 0, s, g);
+  } else if (g.n_cells > 0) {
+    const size_t lds = kOffWaves * sizeof(uint64_t) * (size_t)union_words(g.n_cells);
+    hipLaunchKernelGGL(offset_union_kernel, grid, dim3(kOffBlock), lds, s, g);
+    // (four workgroups of it fit a CU)
+    hipLaunchKernelGGL(offset_rest_kernel, dim3(grid.x < 1024 ? grid.x : 1024), dim3(kOffBlock), 0, s, g);
+  } else {
+    hipLaunchKernelGGL(offset_ray_kernel<false>, grid, dim3(kOffBlock), 0, s, g);
+  }
   return hipGetLastError();
 }
 
