@@ -255,7 +255,8 @@ struct BooleanArgs {
   double eps;             // volumes thinner than this are removed
   uint32_t* counts;       // [npix + 1]: kept samples per pixel (count pass),
                           // scanned in place into the result offsets (write pass)
-  uint32_t* refs;         // [a.n + b.n]: sources of the kept samples (count pass)
+  uint32_t* refs;         // [a.n + b.n]: sources of the kept samples (count pass), per
+                          // 64 pixels from the first's samples in a and b on
   uint32_t* status;       // kStatusMismatch: offsets of an input out of order
   float* out_depth;
   float* out_normal;
