@@ -162,11 +162,10 @@ uint32_t* pinned_readback() {
   return p;
 }
 
-// Status words of finished results.  The last kernel of a call copies the
-// call's device status word into one pinned host slot and an event is
-// recorded after it; the result's first ldni_result_axis waits for the event
-// and reports what the write pass found (a write pass that disagrees with
-// its count pass).  Slots and events are reused.
+// Status words of finished results: the write pass of a call raises what it
+// finds (that it disagrees with its count pass) in a pinned host slot, and an
+// event is recorded after it; the result's first ldni_result_axis waits for
+// the event and reports the slot.  Slots and events are reused.
 struct StatusSlot {
   uint32_t* host = nullptr;  // pinned word
   hipEvent_t done = nullptr;
@@ -375,7 +374,6 @@ struct ldni_plan {
   void* stage = nullptr;  // hits staged by the sampling pass
   size_t stage_bytes = 0;
   uint32_t n_walk = 0;    // tiles the write pass walks again
-  uint32_t* status = nullptr;  // the call's device status word
   uint64_t n[3] = {0, 0, 0};
   uint32_t max_layers[3] = {0, 0, 0};
 };
@@ -411,30 +409,53 @@ ldni_status write_verdict(uint32_t bits) {
   return LDNI_OK;
 }
 
-// After the last kernel of a call: the device status word goes to the
-// result's pinned slot, stream-ordered, and the result remembers to check it.
-// Without a free slot the call waits and checks at once.
-ldni_status arm_status(ldni_result* r, const uint32_t* dev_status, hipStream_t s) {
+// The pinned word in which a call's write pass raises its status bits: a slot
+// that the result keeps until it is first read, or, without a free slot, a word
+// of the thread's readback buffer, for which the call waits.
+struct FailWord {
   StatusSlot slot;
-  if (slot_get(&slot)) {
-    const uint32_t* src[1] = {dev_status};
-    hipError_t e = launch_gather(src, 1, slot.host, s);
-    if (e == hipSuccess) e = hipEventRecord(slot.done, s);
+  bool own = false;  // a slot of its own
+  uint32_t* host = nullptr;
+};
+constexpr size_t kFailReadback = 1023;  // (the last word of the readback buffer)
+
+// Before the write pass: a cleared word.  shared: not a slot.
+bool fail_word(FailWord* f, bool shared) {
+  if (!shared && slot_get(&f->slot)) {
+    f->own = true;
+    f->host = f->slot.host;
+  } else {
+    uint32_t* rb = pinned_readback();
+    if (!rb) return false;
+    f->host = rb + kFailReadback;
+  }
+  *static_cast<volatile uint32_t*>(f->host) = 0u;
+  return true;
+}
+
+void drop_fail_word(FailWord* f) {
+  if (f->own) slot_put(f->slot);
+  f->own = false;
+}
+
+// After the write pass: the result remembers to check its word, or the call
+// waits for it here.
+ldni_status settle_later(ldni_result* r, FailWord* f, hipStream_t s) {
+  if (f->own && r) {
+    const hipError_t e = hipEventRecord(f->slot.done, s);
     if (e != hipSuccess) {
-      slot_put(slot);
-      return hip_fail(e, "status readback");
+      (void)hipStreamSynchronize(s);  // (the slot is not reused under the pass)
+      drop_fail_word(f);
+      return hip_fail(e, "status event");
     }
-    r->slot = slot;
+    r->slot = f->slot;
     r->pending = true;
     return LDNI_OK;
   }
-  uint32_t* rb = pinned_readback();
-  if (!rb) return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
-  const uint32_t* src[1] = {dev_status};
-  HIP_TRY(launch_gather(src, 1, rb, s), "status readback");
   HIP_TRY(hipStreamSynchronize(s), "synchronise");
-  r->verdict = write_verdict(rb[0]);
-  return LDNI_OK;
+  const ldni_status st = write_verdict(*static_cast<volatile uint32_t*>(f->host));
+  if (r) r->verdict = st;
+  return st;
 }
 
 // The result's status, waiting for its write pass if that is still running.
@@ -447,16 +468,6 @@ ldni_status settle(ldni_result* r) {
     r->verdict = e != hipSuccess ? hip_fail(e, "waiting for the write pass") : write_verdict(bits);
   }
   return r->verdict;
-}
-
-// Without a result to carry the check: wait for the stream and check now.
-ldni_status check_now(const uint32_t* dev_status, hipStream_t s) {
-  uint32_t* rb = pinned_readback();
-  if (!rb) return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
-  const uint32_t* src[1] = {dev_status};
-  HIP_TRY(launch_gather(src, 1, rb, s), "status readback");
-  HIP_TRY(hipStreamSynchronize(s), "synchronise");
-  return write_verdict(rb[0]);
 }
 
 }  // namespace
@@ -576,7 +587,6 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
   // [0] status, [1..3] max layers, [12..13] write-pass work counters,
   // [18] tiles to walk again
   uint32_t* status = reinterpret_cast<uint32_t*>(ws + o_status);
-  p->status = status;
   uint32_t* walk_count = status + 18;
 
   MeshSetup ms{};
@@ -819,15 +829,25 @@ ldni_status finish_plan(ldni_plan* p, float* const depth[3], float* const normal
     p->set.img[k].normal_rgb8 = rgb8 ? rgb8[a] : nullptr;
     p->set.img[k].tri = tri[a];
   }
+  FailWord word;
+  if (!fail_word(&word, owner == nullptr)) {
+    release_plan(p);
+    return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
+  }
+  for (int k = 0; k < p->set.n; ++k) p->set.img[k].host_fail = word.host;
   hipError_t e = hipSuccess;
   if (p->n_tris > 0)
     e = timed("place", p->stream, [&] {
       return launch_place(p->set, p->items, p->n_items, p->write_counter, p->n_walk, p->stream);
     });
   ldni_status st = LDNI_OK;
-  if (e != hipSuccess) st = hip_fail(e, "write kernel");
-  else if (owner) st = arm_status(owner, p->status, p->stream);
-  else st = check_now(p->status, p->stream);
+  if (e != hipSuccess) {
+    st = hip_fail(e, "write kernel");
+    (void)hipStreamSynchronize(p->stream);  // (the word is not reused under kernels that did start)
+    drop_fail_word(&word);
+  } else {
+    st = settle_later(owner, &word, p->stream);
+  }
   release_plan(p);
   return st;
 }
@@ -1200,14 +1220,13 @@ ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32
   BSTEP(launch_fill_u32(status, 0u, 64, stream), "fill");
   BSTEP(timed("boolean_count", stream, [&] { return launch_boolean(g, false, stream); }), "Boolean count kernel");
   BSTEP(timed("boolean_scan", stream, [&] {
-          return launch_scan(counts, counts, npix, static_cast<char*>(ws) + 256, status, stream, status + 1);
+          return launch_scan(counts, counts, npix, static_cast<char*>(ws) + 256, status, stream, status + 1, rb);
         }), "Boolean scan");
-  const uint32_t* src[3] = {status, status + 1, counts + npix};
-  BSTEP(launch_gather(src, 3, rb, stream), "readback");
   BSTEP(hipStreamSynchronize(stream), "synchronise");
   if (rb[0] & kStatusMismatch) return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
-  if (rb[0] & kStatusOverflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples"));
-  const uint64_t n = rb[2];
+  if (rb[3]) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples"));
+  const uint64_t n = rb[1];
+  const uint32_t max_layers = rb[2];
   size_t o_normal = align_up(sizeof(float) * n), o_tri = align_up(o_normal + sizeof(float) * 3 * n);
   e = cache_get(&r->samples_buf, o_tri + sizeof(int32_t) * n, stream, &r->samples_bytes);
   if (e != hipSuccess) {
@@ -1218,16 +1237,23 @@ ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32
   g.out_depth = reinterpret_cast<float*>(sb);
   g.out_normal = reinterpret_cast<float*>(sb + o_normal);
   g.out_tri = reinterpret_cast<int32_t*>(sb + o_tri);
-  BSTEP(timed("boolean_write", stream, [&] { return launch_boolean(g, true, stream); }), "Boolean write kernel");
+  FailWord word;
+  if (!fail_word(&word, false)) return bail(fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer"));
+  g.host_fail = word.host;
+  e = timed("boolean_write", stream, [&] { return launch_boolean(g, true, stream); });
+  if (e != hipSuccess) {
+    drop_fail_word(&word);
+    return bail(hip_fail(e, "Boolean write kernel"));
+  }
   {
-    const ldni_status st = arm_status(r, status, stream);
+    const ldni_status st = settle_later(r, &word, stream);
     if (st != LDNI_OK) return bail(st);
   }
 #undef BSTEP
   cache_put(ws, ws_bytes, stream);
   ldni_axis_view& v = r->view[axis];
   v.w = w;
-  v.max_layers = rb[1];
+  v.max_layers = max_layers;
   v.n_samples = n;
   v.offsets = counts;
   v.depth = g.out_depth;
@@ -1497,18 +1523,13 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   OSTEP(timed("offset_count", stream, [&] { return launch_offset_rays(g, false, stream); }), "offset count kernel");
   uint32_t* max_slot = g.status + 8;  // [8..10]: largest count per axis
   uint32_t* maxes[3] = {max_slot, max_slot + 1, max_slot + 2};
-  OSTEP(launch_scan_segments(g.counts, g.counts, 3, npix, scr, g.status, stream, maxes), "offset scan");
-  {
-    const uint32_t* src[7] = {g.status, g.counts[0] + npix, g.counts[1] + npix, g.counts[2] + npix,
-                              maxes[0], maxes[1], maxes[2]};
-    OSTEP(launch_gather(src, 7, rb, stream), "readback");
-    OSTEP(hipStreamSynchronize(stream), "synchronise");
-  }
+  OSTEP(launch_scan_segments(g.counts, g.counts, 3, npix, scr, g.status, stream, maxes, rb), "offset scan");
+  OSTEP(hipStreamSynchronize(stream), "synchronise");
   if (rb[0] & kStatusMismatch)
     return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
-  if (rb[0] & kStatusOverflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples on one axis"));
-  const uint64_t n_out[3] = {rb[1], rb[2], rb[3]};
-  const uint32_t max_layers[3] = {rb[4], rb[5], rb[6]};
+  if (rb[3] | rb[6] | rb[9]) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples on one axis"));
+  const uint64_t n_out[3] = {rb[1], rb[4], rb[7]};
+  const uint32_t max_layers[3] = {rb[2], rb[5], rb[8]};
   size_t o_ax[3][3], total = 0;
   for (int d = 0; d < 3; ++d) {
     o_ax[d][0] = total;
@@ -1527,9 +1548,16 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
     g.out_normal[d] = reinterpret_cast<float*>(sb + o_ax[d][1]);
     g.out_tri[d] = reinterpret_cast<int32_t*>(sb + o_ax[d][2]);
   }
-  OSTEP(timed("offset_write", stream, [&] { return launch_offset_rays(g, true, stream); }), "offset write kernel");
+  FailWord word;
+  if (!fail_word(&word, false)) return bail(fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer"));
+  g.host_fail = word.host;
+  e = timed("offset_write", stream, [&] { return launch_offset_rays(g, true, stream); });
+  if (e != hipSuccess) {
+    drop_fail_word(&word);
+    return bail(hip_fail(e, "offset write kernel"));
+  }
   {
-    const ldni_status st = arm_status(res, g.status, stream);
+    const ldni_status st = settle_later(res, &word, stream);
     if (st != LDNI_OK) return bail(st);
   }
 #undef OSTEP

@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_write_kernel(BooleanArgs g
     for (int u = 0; u < 4; ++u)
       if (ok[u]) put(g, (uint64_t)k0 + lane + 64u * u, from_b[u], x[u]);
     // (inputs that changed between the passes do not lead out of bounds)
-    if (bad) atomicOr(g.status, kStatusMismatch);
+    if (bad) raise_mismatch(g.status, g.host_fail);
     if (R1 - k0 <= 4 * 64) break;
   }
 }

@@ -68,6 +68,7 @@ struct Image {
   uint32_t* normal_rgb8;  // [n] 8-bit normal codes, or null for float normals
   int32_t* tri;       // [n]
   uint32_t* status;   // shared status word
+  uint32_t* host_fail;  // pinned word that a write pass raises status bits in, or null
   // Hits of the sampling pass, grouped by tile.  With stage_key null every
   // tile with hits is walked again by the place pass.
   uint64_t* stage_key;               // (depth key, triangle) of each hit
@@ -125,6 +126,14 @@ struct MeshSetup {
 // Triangles per binning chunk and the size of its LDS table of tiles.
 constexpr int kBinChunkTris = 512;
 constexpr int kBinSlots = 1024;
+
+// Raises the mismatch bit in the device status word and, in a write pass, in
+// the pinned word that the host reads once the pass is over.
+__device__ __forceinline__ void raise_mismatch(uint32_t* status, uint32_t* host_fail) {
+  atomicOr(status, (uint32_t)kStatusMismatch);
+  if (host_fail != nullptr)
+    __hip_atomic_store(host_fail, (uint32_t)kStatusMismatch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Fills the derived fields of an image (inverse steps, centre slack, tile
 // shifts) from w, the tile shape and lo/h of both image axes.
@@ -258,6 +267,7 @@ struct BooleanArgs {
   uint32_t* refs;         // [a.n + b.n]: sources of the kept samples (count pass), per
                           // 64 pixels from the first's samples in a and b on
   uint32_t* status;       // kStatusMismatch: offsets of an input out of order
+  uint32_t* host_fail;    // pinned word for the write pass's status bits
   float* out_depth;
   float* out_normal;
   int32_t* out_tri;
@@ -341,7 +351,8 @@ struct OffsetArgs {
   int32_t n_cells;
   double inv_cell, long_chord;
   uint32_t* rest;
-  uint32_t* status;  // kStatusMismatch: bad input offsets; kStatusOutFull: a ray's window or end points overflow
+  uint32_t* status;  // kStatusMismatch: bad input offsets
+  uint32_t* host_fail;  // pinned word for the write pass's status bits
 };
 hipError_t launch_offset_centres(const OffsetArgs& g, hipStream_t s);
 hipError_t launch_offset_bin(const OffsetArgs& g, bool scatter, hipStream_t s);
@@ -357,14 +368,18 @@ hipError_t launch_gather(const uint32_t* const* src, int n, uint32_t* host_dst, 
 // 2^32 or more raise kStatusOverflow.  scratch: scan_scratch_bytes(n, 1).
 // max_out (if given) receives the largest value.
 size_t scan_scratch_bytes(int64_t n, int nseg = 1);
+// host (if given) receives kScanHost words of pinned memory behind the scan:
+// status as the kernels before it left it, then per segment the total, the
+// largest value (0 without max_out) and whether the total overflowed.
+constexpr int kScanHost = 1 + 3 * kMaxImages;
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, int64_t n, void* scratch,
-                       uint32_t* status, hipStream_t s, uint32_t* max_out = nullptr);
+                       uint32_t* status, hipStream_t s, uint32_t* max_out = nullptr, uint32_t* host = nullptr);
 // nseg <= kMaxImages such scans of n values each, in one set of launches
 // (in place allowed); scratch: scan_scratch_bytes(n, nseg); max_out[k] as
 // above per segment.
 hipError_t launch_scan_segments(const uint32_t* const* in, uint32_t* const* out, int nseg, int64_t n,
                                 void* scratch, uint32_t* status, hipStream_t s,
-                                uint32_t* const* max_out = nullptr);
+                                uint32_t* const* max_out = nullptr, uint32_t* host = nullptr);
 // The tile scan: entry counts -> list offsets (as launch_scan, into
 // tile_cnt), and in the same launches candidate counts -> staging regions
 // (tile_region), each tile's count capped at region_cap and the prefix

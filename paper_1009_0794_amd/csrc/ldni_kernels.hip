@@ -581,7 +581,7 @@ __device__ __forceinline__ EntryRect entry_rect(const Image& im, const TileGeom&
   r.width = ((gm >> 16) & 255) + 1;
   r.y1 = r.y0 + (int)(gm >> 24) + 1;
   if ((uint32_t)ent.x >= (uint64_t)im.n_tris || r.x0 + r.width > g.cw || r.y1 > g.ch) {
-    atomicOr(im.status, kStatusMismatch);
+    raise_mismatch(im.status, im.host_fail);
     r.x0 = 0;
     r.y0 = 0;
     r.width = 1;
@@ -1155,7 +1155,7 @@ __device__ void write_tile(const Image& im, int tile, int part = 0, int parts = 
                               if (q < q0 || q >= q1) return;
                               const uint32_t slot = atomicAdd(&s_cur[q], 1u);
                               if (slot >= s_pre[q + 1] - s_pre[q]) {  // count/write disagree
-                                atomicOr(im.status, kStatusMismatch);
+                                raise_mismatch(im.status, im.host_fail);
                                 return;
                               }
                               const float4 z = L.z[e];
@@ -1258,7 +1258,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
     }
     tile_prefix(im, g, s_off, s_pre, nullptr, s_wave);
     if (s_pre[npix] != hits) {  // staging and counts disagree
-      if (threadIdx.x == 0) atomicOr(im.status, kStatusMismatch);
+      if (threadIdx.x == 0) raise_mismatch(im.status, im.host_fail);
       return;
     }
 #pragma unroll
@@ -1267,7 +1267,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
       const int q = (int)(rq[u] & 1023u);
       const uint32_t slot = rq[u] >> 10;
       if (q >= npix || slot >= s_pre[q + 1] - s_pre[q]) {
-        atomicOr(im.status, kStatusMismatch);
+        raise_mismatch(im.status, im.host_fail);
         continue;
       }
       s_keys[s_pre[q] + slot] = rk[u];
@@ -1280,7 +1280,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
 
   tile_prefix(im, g, s_off, s_pre, nullptr, s_wave);
   if (s_pre[npix] != hits) {
-    if (threadIdx.x == 0) atomicOr(im.status, kStatusMismatch);
+    if (threadIdx.x == 0) raise_mismatch(im.status, im.host_fail);
     return;
   }
   int q0 = 0;
@@ -1317,7 +1317,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
           const uint32_t slot = xs[u] >> 10;
           if (i >= hits || q < q0 || q >= q1) continue;
           if (slot >= s_pre[q + 1] - s_pre[q]) {
-            atomicOr(im.status, kStatusMismatch);
+            raise_mismatch(im.status, im.host_fail);
             continue;
           }
           const uint64_t key = ks[u];
@@ -1444,6 +1444,9 @@ struct ScanSegs {
   int64_t n;
   int64_t nb;
   int32_t nseg;
+  uint32_t* status;  // overflow bit, or null
+  uint32_t* host;    // kScanHost words of pinned memory, or null: status, then per
+                     // segment its total, largest value and whether it overflowed
 };
 
 __global__ void __launch_bounds__(kBlock) scan_reduce_kernel(ScanSegs sg, uint64_t* partial) {
@@ -1504,6 +1507,11 @@ __global__ void __launch_bounds__(kBlock) scan_spine_kernel(ScanSegs sg, uint64_
   }
 }
 
+// A tile's prefixes: kDirect, the partial sums of the tiles before it are
+// added up here, by every workgroup for itself (up to kDirectTiles of them, 16 KB
+// from L2), and the segment's last workgroup reports its total and maximum;
+// else the spine has scanned them.
+template <bool kDirect>
 __global__ void __launch_bounds__(kBlock) scan_apply_kernel(ScanSegs sg, const uint64_t* partial) {
   __shared__ uint64_t s_w[kWaves];
   const int seg = (int)(blockIdx.x / sg.nb);
@@ -1516,12 +1524,21 @@ __global__ void __launch_bounds__(kBlock) scan_apply_kernel(ScanSegs sg, const u
     load16_pack(sg.pack, sg.pack_add, n, i, seg, sg.cap[seg], v);
   else
     load16(sg.in[seg], n, i, sg.cap[seg], v);
+  uint64_t before = 0;
+  if (kDirect) {
+    uint64_t x = 0;
+    for (int64_t q = threadIdx.x; q < b; q += kBlock) x += partial[(int64_t)seg * sg.nb + q];
+    block_exclusive_scan<uint64_t>(x, s_w, before);
+  } else {
+    before = partial[blockIdx.x];
+  }
   uint64_t s = 0;
 #pragma unroll
   for (int k = 0; k < 16; ++k) s += v[k];
   uint64_t total;
-  uint64_t run = block_exclusive_scan<uint64_t>(s, s_w, total) + partial[blockIdx.x];
-  const uint64_t top = ((sg.sat >> seg) & 1u) ? 0xffffffffull : ~0ull;
+  uint64_t run = block_exclusive_scan<uint64_t>(s, s_w, total) + before;
+  const bool sat = (sg.sat >> seg) & 1u;
+  const uint64_t top = sat ? 0xffffffffull : ~0ull;
   uint32_t o[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
@@ -1536,6 +1553,30 @@ __global__ void __launch_bounds__(kBlock) scan_apply_kernel(ScanSegs sg, const u
 #pragma unroll
     for (int k = 0; k < 16; ++k)
       if (i + k < n) out[i + k] = o[k];
+  }
+  if (kDirect && b + 1 == sg.nb) {
+    const uint64_t all = before + total;
+    uint32_t m = 0;
+    if (sg.max_out[seg] != nullptr) {
+      __shared__ uint32_t s_m[kWaves];
+      const uint64_t* pmax = partial + (int64_t)sg.nb * sg.nseg + 2 + (int64_t)seg * sg.nb;
+      for (int64_t q = threadIdx.x; q < sg.nb; q += kBlock) m = max(m, (uint32_t)pmax[q]);
+      m = block_max(m, s_m);
+    }
+    if (threadIdx.x == 0) {
+      const bool over = all > 0xffffffffull && !sat;
+      *sg.total[seg] = (uint32_t)min(all, 0xffffffffull);
+      if (sg.max_out[seg] != nullptr) *sg.max_out[seg] = m;
+      if (sg.host != nullptr) {
+        if (seg == 0) sg.host[0] = sg.status ? *sg.status : 0u;
+        uint32_t* h = sg.host + 1 + 3 * seg;
+        h[0] = (uint32_t)min(all, 0xffffffffull);
+        h[1] = m;
+        h[2] = over ? 1u : 0u;
+        __threadfence_system();
+      }
+      if (over && sg.status) atomicOr(sg.status, kStatusOverflow);
+    }
   }
 }
 
@@ -1760,6 +1801,20 @@ __global__ void __launch_bounds__(kBlock) batch_finish_counts_kernel(BatchDevice
   __threadfence_system();
 }
 
+// The report of scans whose spine was a launch of its own (status holds the
+// overflow bit of any of them).
+__global__ void scan_report_kernel(ScanSegs sg, const uint32_t* status, uint32_t* host) {
+  const int k = threadIdx.x;
+  if (k == 0) host[0] = status ? *status : 0u;
+  if (k < sg.nseg) {
+    uint32_t* h = host + 1 + 3 * k;
+    h[0] = *sg.total[k];
+    h[1] = sg.max_out[k] ? *sg.max_out[k] : 0u;
+    h[2] = status && (*status & kStatusOverflow) ? 1u : 0u;
+  }
+  __threadfence_system();
+}
+
 struct GatherArgs {
   const uint32_t* src[kMaxGather];
   int n;
@@ -1966,18 +2021,34 @@ size_t scan_scratch_bytes(int64_t n, int nseg) {
   return (size_t)(2 * (nb > 0 ? nb : 1) * (nseg > 0 ? nseg : 1) + 2) * sizeof(uint64_t);
 }
 
-static hipError_t run_scan(const ScanSegs& sg, void* scratch, uint32_t* status, hipStream_t s) {
+// Tiles up to which the apply pass adds up the partial sums itself, which
+// saves the spine's launch (about 5 us); beyond, every workgroup would read more
+// partial sums than values.
+constexpr int64_t kDirectTiles = 2048;
+
+static hipError_t run_scan(ScanSegs sg, void* scratch, uint32_t* status, hipStream_t s, uint32_t* host = nullptr) {
   uint64_t* partial = static_cast<uint64_t*>(scratch);
   const unsigned blocks = (unsigned)(sg.nb * sg.nseg);
+  const bool direct = sg.nb <= kDirectTiles;
+  sg.status = status;
+  sg.host = direct ? host : nullptr;
   hipLaunchKernelGGL(scan_reduce_kernel, dim3(blocks), dim3(kBlock), 0, s, sg, partial);
+  if (direct) {
+    hipLaunchKernelGGL(scan_apply_kernel<true>, dim3(blocks), dim3(kBlock), 0, s, sg, partial);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(scan_spine_kernel, dim3((unsigned)sg.nseg), dim3(kBlock), 0, s, sg, partial, status);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3(blocks), dim3(kBlock), 0, s, sg, partial);
+  hipLaunchKernelGGL(scan_apply_kernel<false>, dim3(blocks), dim3(kBlock), 0, s, sg, partial);
+  if (host != nullptr) {
+    hipLaunchKernelGGL(scan_report_kernel, dim3(1), dim3(64), 0, s, sg, status, host);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_scan_segments(const uint32_t* const* in, uint32_t* const* out, int nseg, int64_t n,
-                                void* scratch, uint32_t* status, hipStream_t s, uint32_t* const* max_out) {
-  if (nseg < 1 || nseg > kMaxImages) return hipErrorInvalidValue;
+                                void* scratch, uint32_t* status, hipStream_t s, uint32_t* const* max_out,
+                                uint32_t* host) {
+  if (nseg < 1 || nseg > kMaxImages || (host && n <= 0)) return hipErrorInvalidValue;
   if (n <= 0) {
     for (int k = 0; k < nseg; ++k) {
       hipError_t e = launch_fill_u32(out[k], 0u, 1, s);
@@ -1996,7 +2067,7 @@ hipError_t launch_scan_segments(const uint32_t* const* in, uint32_t* const* out,
   sg.n = n;
   sg.nb = (n + kScanTile - 1) / kScanTile;
   sg.nseg = nseg;
-  return run_scan(sg, scratch, status, s);
+  return run_scan(sg, scratch, status, s, host);
 }
 
 hipError_t launch_tile_scan(const uint64_t* tile_pack, const uint32_t* tile_ovf, uint32_t* tile_cnt,
@@ -2025,8 +2096,8 @@ hipError_t launch_tile_scan(const uint64_t* tile_pack, const uint32_t* tile_ovf,
 }
 
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, int64_t n, void* scratch,
-                       uint32_t* status, hipStream_t s, uint32_t* max_out) {
-  return launch_scan_segments(&in, &out, 1, n, scratch, status, s, max_out ? &max_out : nullptr);
+                       uint32_t* status, hipStream_t s, uint32_t* max_out, uint32_t* host) {
+  return launch_scan_segments(&in, &out, 1, n, scratch, status, s, max_out ? &max_out : nullptr, host);
 }
 
 }  // namespace ldni

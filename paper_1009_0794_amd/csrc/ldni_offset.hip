@@ -408,7 +408,7 @@ __device__ void sweep_ray(const OffsetArgs& g, int64_t ray, RayLds& lds) {
   const uint32_t o0 = H.offsets[p], o1 = H.offsets[p + 1];
   uint32_t nh = 0;
   if (o1 < o0 || (uint64_t)o1 > H.n) {
-    if (lane == 0) atomicOr(g.status, kStatusMismatch);
+    if (lane == 0) raise_mismatch(g.status, g.host_fail);
   } else {
     nh = (o1 - o0) & ~1u;
   }
@@ -658,7 +658,7 @@ __device__ void sweep_ray(const OffsetArgs& g, int64_t ray, RayLds& lds) {
   if (!kWrite && lane == 0) g.counts[a][p] = 2 * kept;
   // more or fewer end points than the count pass kept: slots unwritten or
   // surplus ones dropped, so the call fails
-  if (kWrite && lane == 0 && 2 * kept != cnt) atomicOr(g.status, kStatusMismatch);
+  if (kWrite && lane == 0 && 2 * kept != cnt) raise_mismatch(g.status, g.host_fail);
 }
 
 template <bool kWrite>
