@@ -545,11 +545,15 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     if ((axis_mask >> a) & 1u) p->axis_of[nimg++] = a;
   const int64_t n_all = nimg * n_tiles;  // tiles of all images, numbered image after image
   size_t off = 0;
-  // status words, tile entry counts (all images, then their total), tile
-  // candidate counts (16-byte aligned for the scan) and scatter cursors are
-  // adjacent and cleared by one fill
+  // status words, samples and largest counts per row of tiles, tile entry
+  // counts (all images, then their total), tile candidate counts (16-byte
+  // aligned for the scan) and scatter cursors are adjacent and cleared by one
+  // fill
   const size_t o_status = off; off += 256;
-  const size_t o_tcnt = off; off += sizeof(uint32_t) * (size_t)(n_all + 1);
+  const size_t n_bands = (size_t)nimg * nty;
+  const size_t o_band = off; off += sizeof(Band) * n_bands;
+  const int64_t n_again = (int64_t)(off / sizeof(uint32_t)) - 16;  // status + 16 up to here: cleared for a second attempt
+  const size_t o_tcnt = (off + 15) & ~(size_t)15; off = o_tcnt + sizeof(uint32_t) * (size_t)(n_all + 1);
   const size_t o_treg = (off + 15) & ~(size_t)15; off = o_treg + sizeof(uint32_t) * (size_t)(n_all + 1);
   const size_t o_tcur = off; off += sizeof(uint32_t) * (size_t)n_all;
   const size_t o_tovf = off; off += sizeof(uint32_t) * (size_t)n_all;
@@ -557,7 +561,7 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
   const size_t o_tpack = off; off += sizeof(uint64_t) * (size_t)n_all;
   const int64_t n_clear = (int64_t)(off / sizeof(uint32_t));
   off = align_up(off);
-  const int64_t n_chunks = (n_tris + kBinChunkTris - 1) / kBinChunkTris;
+  const int64_t n_chunks = (n_tris + kBinChunkTris - 1) / kBinChunkTris * bin_split(n_tris, nimg);
   const size_t o_brec = off; off = align_up(off + sizeof(uint4) * kBinSlots * (size_t)n_chunks);
   const size_t o_bnrec = off; off = align_up(off + sizeof(uint32_t) * (size_t)n_chunks);
   const size_t o_soup = off; off = align_up(off + sizeof(float) * 9 * (size_t)n_tris);
@@ -570,12 +574,30 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     o_thits[k] = off; off = align_up(off + sizeof(uint32_t) * (size_t)n_tiles);
   }
   const size_t o_walk = off; off = align_up(off + sizeof(uint32_t) * (size_t)n_all);
+  // Staging buffer for the hits of the sampling pass: what the last call of
+  // the same shape asked for (the candidate total of its tile scan), else a
+  // first guess (16 entries per triangle and image, which covers small
+  // triangles' rectangles rounded to 4-entry groups, plus four per pixel for
+  // large ones).  A tile whose region does not fit is walked again by the
+  // place pass, so a short buffer costs time, never results.  Never more
+  // than stage_layers entries per pixel, which is all the tiles can ask for.
+  uint64_t stage_cap;
+  {
+    const double px = (double)npix * nimg;
+    const double want = have_seen ? (double)seen.demand * 1.1 + 65536.0
+                                  : 16.0 * (double)n_tris * nimg + 4.0 * px + 65536.0;
+    const double most = std::min((double)stage_layers * px + 65536.0, (double)kMaxStageEntries);
+    stage_cap = (uint64_t)std::min(want, most);
+    // test hook: a smaller buffer (0: none) forces tiles onto the walk path
+    if (const char* env = std::getenv("LDNI_STAGE_ENTRIES"))
+      stage_cap = std::min<uint64_t>(stage_cap, std::strtoull(env, nullptr, 10));
+    stage_cap &= ~(uint64_t)3;  // whole 4-entry groups: 16-byte aligned pixel/slot words
+  }
   const size_t o_items = off;
-  off = align_up(off + 16 * (size_t)max_place_items_per_tile(tw * th, stage_layers) * (size_t)n_all);
-  const size_t o_plan = off; off = align_up(off + sizeof(uint32_t) * (size_t)(2 * n_all + 1));
+  const uint32_t items_cap = (uint32_t)place_items_cap(stage_cap, (uint64_t)n_all);
+  off = align_up(off + 16 * (size_t)items_cap);
   const size_t o_scan = off;
-  off = align_up(off + std::max({scan_scratch_bytes(npix, nimg), scan_scratch_bytes(2 * n_all, 1),
-                                  scan_scratch_bytes(n_all, 2)}));
+  off = align_up(off + scan_scratch_bytes(n_all, 2));
 
   hipError_t e = cache_get(&p->ws, off, stream, &p->ws_bytes);
   if (e != hipSuccess) {
@@ -584,7 +606,8 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     return hip_fail(e, "workspace allocation");
   }
   char* ws = static_cast<char*>(p->ws);
-  // [0] status, [1..3] max layers, [12..13] write-pass work counters,
+  // [0] status, [12..13] write-pass work counters, [32..41] the offsets pass's
+  // totals,
   // [18] tiles to walk again
   uint32_t* status = reinterpret_cast<uint32_t*>(ws + o_status);
   uint32_t* walk_count = status + 18;
@@ -632,8 +655,9 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     im.tile_region = reinterpret_cast<uint32_t*>(ws + o_treg) + k * n_tiles;
     im.tile_list = nullptr;
     im.counts = reinterpret_cast<uint32_t*>(ws + o_counts[k]);
-    im.max_layers = nullptr;  // the pixel scan writes status[1 + k]
+    im.max_layers = nullptr;
     im.tile_max = nullptr;
+    im.band = reinterpret_cast<Band*>(ws + o_band) + (size_t)k * nty;
     im.offsets = offsets[a];
     im.status = status;
     im.tile_stage = reinterpret_cast<uint32_t*>(ws + o_tstage[k]);
@@ -642,23 +666,7 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     im.walk_count = walk_count;
     set.tile_start[k + 1] = set.tile_start[k] + (uint32_t)n_tiles;
   }
-  // Staging buffer for the hits of the sampling pass: what the last call of
-  // the same shape asked for (the candidate total of its tile scan), else a
-  // first guess (16 entries per triangle and image, which covers small
-  // triangles' rectangles rounded to 4-entry groups, plus four per pixel for
-  // large ones).  A tile whose region does not fit is walked again by the
-  // place pass, so a short buffer costs time, never results.  Never more
-  // than stage_layers entries per pixel, which is all the tiles can ask for.
   {
-    const double px = (double)npix * nimg;
-    const double want = have_seen ? (double)seen.demand * 1.1 + 65536.0
-                                  : 16.0 * (double)n_tris * nimg + 4.0 * px + 65536.0;
-    const double most = std::min((double)stage_layers * px + 65536.0, (double)kMaxStageEntries);
-    uint64_t stage_cap = (uint64_t)std::min(want, most);
-    // test hook: a smaller buffer (0: none) forces tiles onto the walk path
-    if (const char* env = std::getenv("LDNI_STAGE_ENTRIES"))
-      stage_cap = std::min<uint64_t>(stage_cap, std::strtoull(env, nullptr, 10));
-    stage_cap &= ~(uint64_t)3;  // whole 4-entry groups: 16-byte aligned pixel/slot words
     if (stage_cap == 0 ||
         cache_get(&p->stage, stage_cap * (sizeof(uint64_t) + sizeof(uint32_t)), stream, &p->stage_bytes) !=
             hipSuccess)
@@ -673,7 +681,6 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     }
   }
   void* scan_scratch = ws + o_scan;
-  set.plan = reinterpret_cast<uint32_t*>(ws + o_plan);
   set.place_cap = place_stage_cap(tw * th);
   p->write_counter = status + 12;
   p->items = ws + o_items;
@@ -725,49 +732,32 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     return hipSuccess;
   };
   STEP(alloc_lists(cap), "tile list allocation");
-  const uint32_t* gather_src[kMaxGather];
-  int n_gather = 0;
-  gather_src[n_gather++] = status;      // rb[0]: status, rb[1..3]: max layers
-  gather_src[n_gather++] = status + 1;
-  gather_src[n_gather++] = status + 2;
-  gather_src[n_gather++] = status + 3;
-  for (int k = 0; k < nimg; ++k) gather_src[n_gather++] = set.img[k].offsets + npix;  // rb[4+k]
-  const int rb_more = n_gather;
-  gather_src[n_gather++] = tile_cnt_all + n_all;     // list entries
-  gather_src[n_gather++] = tile_region_all + n_all;  // staging demand (saturated)
-  gather_src[n_gather++] = status + 18;              // tiles to walk again
-  gather_src[n_gather++] = set.plan + 2 * n_all;     // place items
-  const uint32_t* counts_k[kMaxImages];
-  uint32_t* offsets_k[kMaxImages];
-  uint32_t* max_k[kMaxImages];  // largest count of each image
-  for (int k = 0; k < nimg; ++k) {
-    counts_k[k] = set.img[k].counts;
-    offsets_k[k] = set.img[k].offsets;
-    max_k[k] = status + 1 + k;
-  }
+  // the offsets pass reports the sizes: status, per image (total, largest
+  // count, overflow), then list entries, staging demand (saturated), tiles to
+  // walk again, place items
+  OffsetsReport report;
+  report.host = rb;
+  report.found = reinterpret_cast<OffsetsReport::Found*>(status + 32);
+  report.extra[0] = tile_cnt_all + n_all;
+  report.extra[1] = tile_region_all + n_all;
+  report.extra[2] = walk_count;
+  const uint32_t* rb_more = rb + kScanHost;
   for (int attempt = 0; attempt < 2; ++attempt) {
     STEP(timed("bin_scatter", stream, [&] { return launch_bin_scatter(ms, set, stream); }), "bin scatter kernel");
     STEP(timed("sample", stream, [&] { return launch_sample(set, stream); }), "sampling kernel");
-    STEP(timed("scan_pixels", stream, [&] {
-           return launch_scan_segments(counts_k, offsets_k, nimg, npix, scan_scratch, status, stream, max_k);
-         }), "pixel scan");
-    STEP(timed("plan_items", stream, [&] {
-           return launch_plan_items(set, p->items, scan_scratch, status, stream);
-         }), "place plan");
-    // the single readback: status, max layers, sample and entry totals
-    STEP(launch_gather(gather_src, n_gather, rb, stream), "readback");
+    STEP(timed("scan_pixels", stream, [&] { return launch_offsets(set, p->items, items_cap, report, stream); }), "offsets kernel");
     STEP(hipStreamSynchronize(stream), "synchronise");
     if (rb[0] & kStatusBadIndex) return bail(fail(LDNI_ERR_INDEX, "triangle index outside [0, n_verts)"));
     if (rb[0] & kStatusNonFinite) return bail(fail(LDNI_ERR_NONFINITE, "non-finite vertex coordinate"));
     if (rb[0] & kStatusMismatch) return bail(fail(LDNI_ERR_DEVICE, "tile lists disagree with their counts"));
-    const uint64_t need = rb[rb_more];
+    const uint64_t need = rb_more[0];
     {
-      const uint64_t demand = rb[rb_more + 1];
+      const uint64_t demand = rb_more[1];
       uint32_t ml = 0;
-      for (int k = 0; k < nimg; ++k) ml = std::max(ml, rb[1 + k]);
+      for (int k = 0; k < nimg; ++k) ml = std::max(ml, rb[2 + 3 * k]);
       stage_seen_record(stage_key, StageSeen{demand, ml});
-      p->n_walk = rb[rb_more + 2];
-      p->n_items = rb[rb_more + 3];
+      p->n_walk = rb_more[2];
+      p->n_items = std::min(rb_more[3], items_cap);
     }
     if (n_tris > 0) {
       const double ratio = std::min(8.0, (double)need / ((double)n_tris * nimg) * 1.1);
@@ -779,16 +769,17 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     if (attempt == 1) return bail(fail(LDNI_ERR_DEVICE, "tile list sizing failed"));
     cap = need;
     STEP(alloc_lists(cap), "tile list allocation");
-    // cursors, max layers and walk count start again
+    // cursors, the counters and the rows' totals start again
     STEP(launch_fill_u32(tile_cur_all, 0u, n_all, stream), "fill");
-    STEP(launch_fill_u32(status + 1, 0u, 3, stream), "fill");
-    STEP(launch_fill_u32(walk_count, 0u, 1, stream), "fill");
+    STEP(launch_fill_u32(status + 16, 0u, n_again, stream), "fill");
   }
-  if (rb[0] & kStatusOverflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more samples on one axis"));
+  bool overflow = (rb[0] & kStatusOverflow) != 0;
+  for (int k = 0; k < nimg; ++k) overflow |= rb[3 + 3 * k] != 0;
+  if (overflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more samples on one axis"));
   for (int k = 0; k < nimg; ++k) {
     const int a = p->axis_of[k];
-    p->n[a] = rb[4 + k];
-    p->max_layers[a] = rb[1 + k];
+    p->n[a] = rb[1 + 3 * k];
+    p->max_layers[a] = rb[2 + 3 * k];
     n_samples[a] = p->n[a];
   }
 #undef STEP

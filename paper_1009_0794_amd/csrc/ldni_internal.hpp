@@ -24,6 +24,12 @@ enum : uint32_t {
   kStatusOutFull = 32u,  // batch: samples beyond the output capacity
 };
 
+// Sums over a row of tiles of one image.
+struct Band {
+  uint64_t samples;
+  uint64_t items;    // place items of tiles with several (high half) and with one
+};
+
 // Everything one image (one axis of one mesh) needs on the device.
 struct Image {
   // geometry
@@ -58,9 +64,10 @@ struct Image {
                         // | (height - 1) << 24, tile-local pixels)
   uint64_t list_cap;    // capacity of tile_list (entries beyond it are dropped)
   uint32_t* counts;     // [w*w] samples per pixel
-  uint32_t* max_layers; // [1] largest per-pixel count (atomic max per tile unless
-                        // tile_max is given), or null when the pixel scan takes it
-  uint32_t* tile_max;   // [n_tiles] largest count of each tile, or null
+  uint32_t* max_layers; // [1] largest per-pixel count (batches)
+  uint32_t* tile_max;   // [n_tiles] largest count of each tile (batches), or null
+  Band* band;           // [nty] what the sampling pass adds up per row of tiles
+                        // (zeroed; the images' one after the other), or null
   // outputs
   uint32_t* offsets;  // [w*w + 1]
   float* depth;       // [n]
@@ -98,10 +105,6 @@ struct ImageSet {
   Image img[kMaxImages];
   int32_t n;
   uint32_t tile_start[kMaxImages + 1];  // prefix of tile counts
-  // place-pass plan written by the sampling pass (null: none): items per
-  // tile, [0, n_tiles) for tiles of two or more items, [n_tiles, 2 n_tiles)
-  // for tiles of one, scanned in place into item positions
-  uint32_t* plan;
   int32_t place_cap;  // stage capacity of the place pass
 };
 
@@ -126,6 +129,11 @@ struct MeshSetup {
 // Triangles per binning chunk and the size of its LDS table of tiles.
 constexpr int kBinChunkTris = 512;
 constexpr int kBinSlots = 1024;
+// A mesh of fewer chunks than this (a workgroup per CU) is set up and binned
+// with a workgroup per chunk and image: bin_split workgroups per chunk, each with
+// records of its own.
+constexpr int64_t kBinSplitChunks = 256;
+int bin_split(int64_t n_tris, int nimg);
 
 // Raises the mismatch bit in the device status word and, in a write pass, in
 // the pinned word that the host reads once the pass is over.
@@ -151,16 +159,34 @@ hipError_t launch_setup(const MeshSetup& m, const ImageSet& set, hipStream_t s);
 hipError_t launch_bin_scatter(const MeshSetup& m, const ImageSet& set, hipStream_t s);
 // Sampling pass: per-pixel counts, and every hit staged by tile (see Image).
 hipError_t launch_sample(const ImageSet& set, hipStream_t s);
-// Work items of the place pass: scans the plan the sampling pass wrote and
-// writes the item records (16 bytes each, at most
-// max_place_items_per_tile(tw * th, stage_layers) per tile) in launch order.
 int max_place_items_per_tile(int tile_pix, uint32_t stage_layers);
 // Entries per pixel a tile may reserve in the staging buffer: the deepest
 // pixel seen, rounded up to a power of two, within [64, 1024].
 uint32_t stage_layers_for(uint32_t max_layers_seen);
 int place_stage_cap(int tile_pix);
-hipError_t launch_plan_items(const ImageSet& set, void* items, void* scratch, uint32_t* status,
-                             hipStream_t s);
+// Pixel counts -> offsets of all images and the place items (16 bytes each, in
+// launch order), from the bands that the sampling pass left; to pinned host
+// memory the kScanHost words of launch_scan_segments (segment = image), kExtra
+// more, and the number of items.
+struct OffsetsReport {
+  static constexpr int kExtra = 3;
+  struct Found {  // (zeroed)
+    uint64_t total[kMaxImages];
+    uint32_t deepest[kMaxImages];
+    uint32_t done;  // workgroups
+  };
+  Found* found;
+  const uint32_t* extra[kExtra];
+  uint32_t* host;
+};
+hipError_t launch_offsets(const ImageSet& set, void* items, uint32_t items_cap, const OffsetsReport& rp, hipStream_t s);
+// Items that a staging buffer of that many entries can ask for: a tile of
+// several has more hits than the place pass takes at once (2,048 at least), so
+// its items are fewer than 2 hits / 2,048, and the hits of staged tiles fit the
+// buffer; the other tiles have one.
+inline uint64_t place_items_cap(uint64_t stage_entries, uint64_t n_tiles) {
+  return 2 * stage_entries / 2048 + n_tiles + 16;
+}
 // Place pass: n_items workgroups place the staged tiles; the n_walk tiles of
 // walk_list are then walked again (persistent, counter[0]).
 hipError_t launch_place(const ImageSet& set, const void* items, uint32_t n_items, uint32_t* counter,
