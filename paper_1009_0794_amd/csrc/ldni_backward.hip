@@ -59,9 +59,30 @@ struct BackwardSet {
 // stores cost far less than global atomics), else with atomic additions.  A
 // sample that finds no free slot adds its own directly (its triangle then has
 // no slot in this tile, so nothing stores over it).
+// Bound by the chain of dependent loads per sample and by the atomics, which
+// go out to memory at 11 to 12 cache lines a nanosecond whatever they hold:
+// so six neighbouring lanes write a triangle's six sums, and a tile borrows no
+// pixel it need not (centres within the projection, not the pixels touched).
+// 261,120 triangles at w = 512, 1.6 M samples: 234 us with a lane per triangle
+// (1.7 M lines) and 256 threads, 125 us now; 512 threads because tiles at the
+// mesh's poles hold 7,900 samples (256: 149 us), tiles of 12 pixels 123, of 8
+// 154 us, 2,048 slots 161 us (fewer workgroups per CU), quartered deep tiles
+// 157 us.
 constexpr int kBwdTile = 16;
-constexpr int kBwdSlots = 1024;
-constexpr int kBwdProbe = 32;
+constexpr int kBwdBlock = 512;
+constexpr int kBwdSlotBits = 10;
+constexpr int kBwdSlots = 1 << kBwdSlotBits;
+constexpr int kBwdProbe = 8;  // (32 steps took 5 % longer in full tables)
+static_assert(kBwdSlots % kBwdBlock == 0, "the list of slots is made in whole steps of the workgroup");
+constexpr uint32_t kBwdInside = 1u << 31;  // flag of a key: the tile holds all of the triangle
+
+// The coordinates u and v of vertex i (its three floats in one load), clamped to the array.
+__device__ __forceinline__ void load_uv(const BackwardSet& bs, const BackwardImage& im, int32_t i, double& u, double& v) {
+  const float* P = bs.verts + 3 * (int64_t)min(max(i, 0), (int32_t)(bs.n_verts - 1));
+  const float p0 = P[0], p1 = P[1], p2 = P[2];
+  u = (double)(im.u == 0 ? p0 : im.u == 1 ? p1 : p2);
+  v = (double)(im.v == 0 ? p0 : im.v == 1 ? p1 : p2);
+}
 
 // Whether every pixel whose centre can lie in the projection of triangle t
 // on image im is a pixel of the tile (x0, y0, cw, ch): the centres within the
@@ -73,26 +94,30 @@ __device__ __forceinline__ bool projection_in_tile(const BackwardSet& bs, const 
   double umin = HUGE_VAL, umax = -HUGE_VAL, vmin = HUGE_VAL, vmax = -HUGE_VAL;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const float* P = bs.verts + 3 * (int64_t)min(max(fv[q], 0), (int32_t)(bs.n_verts - 1));
-    umin = fmin(umin, (double)P[im.u]);
-    umax = fmax(umax, (double)P[im.u]);
-    vmin = fmin(vmin, (double)P[im.v]);
-    vmax = fmax(vmax, (double)P[im.v]);
+    double u, v;
+    load_uv(bs, im, fv[q], u, v);
+    umin = fmin(umin, u);
+    umax = fmax(umax, u);
+    vmin = fmin(vmin, v);
+    vmax = fmax(vmax, v);
   }
   // pixel i has centre f32(lo + (i + 0.5) h); a centre in [mn, mx] has i
   // within [tmn - m, tmx + m] for t = (x - lo) / h - 0.5 and m the margin
-  const double iu0 = floor((umin - im.lo_u) / im.h_u - 0.5 - im.margin_u),
-               iu1 = ceil((umax - im.lo_u) / im.h_u - 0.5 + im.margin_u);
-  const double iv0 = floor((vmin - im.lo_v) / im.h_v - 0.5 - im.margin_v),
-               iv1 = ceil((vmax - im.lo_v) / im.h_v - 0.5 + im.margin_v);
-  return iu0 >= (double)x0 && iu1 < (double)(x0 + cw) && iv0 >= (double)y0 && iv1 < (double)(y0 + ch);
+  const double iu0 = (umin - im.lo_u) / im.h_u - 0.5 - im.margin_u,
+               iu1 = (umax - im.lo_u) / im.h_u - 0.5 + im.margin_u;
+  const double iv0 = (vmin - im.lo_v) / im.h_v - 0.5 - im.margin_v,
+               iv1 = (vmax - im.lo_v) / im.h_v - 0.5 + im.margin_v;
+  return iu0 > (double)(x0 - 1) && iu1 < (double)(x0 + cw) && iv0 > (double)(y0 - 1) && iv1 < (double)(y0 + ch);
 }
 
-__global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs) {
+__global__ void __launch_bounds__(kBwdBlock) backward_samples_kernel(BackwardSet bs) {
   __shared__ uint32_t s_row[kBwdTile + 1][kBwdTile + 1];  // offsets of the tile's rows
   __shared__ uint32_t s_pre[kBwdTile + 1];                // samples before each row
-  __shared__ uint32_t s_key[kBwdSlots];                   // triangle + 1, 0 = free
-  __shared__ float s_val[kBwdSlots][6];
+  __shared__ alignas(16) uint32_t s_key[kBwdSlots];       // triangle + 1, 0 = free
+  __shared__ alignas(16) float s_val[kBwdSlots][6];
+  __shared__ uint16_t s_used[kBwdSlots];
+  __shared__ uint32_t s_taken;
+  const int lane = threadIdx.x & 63;
   int k = 0;
   while (k + 1 < bs.n && blockIdx.x >= bs.block_start[k + 1]) ++k;
   const BackwardImage& im = bs.img[k];
@@ -100,30 +125,33 @@ __global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs
   const int tile = (int)(blockIdx.x - bs.block_start[k]);
   const int x0 = (tile % ntx) * kBwdTile, y0 = (tile / ntx) * kBwdTile;
   const int cw = min(kBwdTile, im.w - x0), ch = min(kBwdTile, im.w - y0);
-
-  for (int q = threadIdx.x; q < kBwdSlots; q += kBlock) {
-    s_key[q] = 0;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) s_val[q][c] = 0.0f;
+  // every wave by itself: the tile's samples, a row per lane
+  uint32_t row = 0;
+  if (lane < ch) {
+    const uint32_t* o = im.offsets + (int64_t)(y0 + lane) * im.w + x0;
+    row = o[cw] - o[0];
   }
-  for (int q = threadIdx.x; q < ch * (cw + 1); q += kBlock) {
+  uint32_t upto = row;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)upto, d, 64);
+    if (lane >= d) upto += y;
+  }
+  const uint32_t S = (uint32_t)__shfl((int)upto, 63, 64);
+  if (S == 0) return;
+
+  if (threadIdx.x < 64 && lane <= ch) s_pre[lane] = upto - row;  // (upto of the lanes from ch on: all)
+  for (int q = threadIdx.x; q < ch * (cw + 1); q += kBwdBlock) {
     const int r = q / (cw + 1), x = q - r * (cw + 1);
     s_row[r][x] = im.offsets[(int64_t)(y0 + r) * im.w + x0 + x];
   }
+  for (int q = threadIdx.x; q < kBwdSlots / 4; q += kBwdBlock) reinterpret_cast<uint4*>(s_key)[q] = make_uint4(0, 0, 0, 0);
+  for (int q = threadIdx.x; q < kBwdSlots * 6 / 4; q += kBwdBlock)
+    reinterpret_cast<float4*>(s_val)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (threadIdx.x == 0) s_taken = 0;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t acc = 0;
-    for (int r = 0; r < ch; ++r) {
-      s_pre[r] = acc;
-      acc += s_row[r][cw] - s_row[r][0];
-    }
-    s_pre[ch] = acc;
-  }
-  __syncthreads();
-  const uint32_t S = s_pre[ch];
   float* const accp = im.acc;
 
-  for (uint32_t f = threadIdx.x; f < S; f += kBlock) {
+  for (uint32_t f = threadIdx.x; f < S; f += kBwdBlock) {
     int r = 0;  // row of f: the last r with s_pre[r] <= f (binary search)
     for (int hi = ch - 1; r < hi;) {
       const int mid = (r + hi + 1) >> 1;
@@ -131,10 +159,21 @@ __global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs
     }
     const uint32_t s = s_row[r][0] + (f - s_pre[r]);
     const int32_t t = im.tri[s];
-    if (t < 0 || t >= bs.n_tris) continue;  // not a triangle of this mesh
-    float v[6] = {0, 0, 0, 0, 0, 0};
+    // all loads of a sample that do not hang on another are under way at once
     const float g = im.gd ? im.gd[s] : 0.0f;
+    float v[6] = {0, 0, 0, 0, 0, 0};
+    if (im.gn) {
+      const float* gv = im.gn + 3 * (int64_t)s;
+      v[3] = gv[0];
+      v[4] = gv[1];
+      v[5] = gv[2];
+    }
+    if (t < 0 || t >= bs.n_tris) continue;  // not a triangle of this mesh
     if (g != 0.0f) {
+      const int32_t* fv = bs.tris + 3 * (int64_t)t;
+      double xu[3], xv[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) load_uv(bs, im, fv[q], xu[q], xv[q]);
       int lo = 0, hi = cw - 1;  // pixel of s in the row: the last x with s_row[r][x] <= s
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -142,13 +181,10 @@ __global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs
       }
       const double cu = im.lo_u + ((double)(x0 + lo) + 0.5) * im.h_u;
       const double cv = im.lo_v + ((double)(y0 + r) + 0.5) * im.h_v;
-      const int32_t* fv = bs.tris + 3 * (int64_t)t;
-      double xu[3], xv[3];
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const float* P = bs.verts + 3 * (int64_t)min(max(fv[q], 0), (int32_t)(bs.n_verts - 1));
-        xu[q] = (double)P[im.u] - cu;
-        xv[q] = (double)P[im.v] - cv;
+        xu[q] -= cu;
+        xv[q] -= cv;
       }
       const double e_bc = xu[1] * xv[2] - xv[1] * xu[2];
       const double e_ca = xu[2] * xv[0] - xv[2] * xu[0];
@@ -161,19 +197,14 @@ __global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs
         v[2] = (float)(gs * e_ab);
       }
     }
-    if (im.gn) {
-      const float* gv = im.gn + 3 * (int64_t)s;
-      v[3] = gv[0];
-      v[4] = gv[1];
-      v[5] = gv[2];
-    }
     if (v[0] == 0.0f && v[1] == 0.0f && v[2] == 0.0f && v[3] == 0.0f && v[4] == 0.0f && v[5] == 0.0f)
       continue;
-    // slot of t in the table (linear probing, a bounded number of steps)
+    // slot of t in the table (linear probing, a bounded number of steps; none
+    // for the one triangle whose key would be the flag)
     const uint32_t key = (uint32_t)t + 1u;
-    uint32_t h = ((uint32_t)t * 2654435761u) >> 22;  // 10 bits
+    uint32_t h = ((uint32_t)t * 2654435761u) >> (32 - kBwdSlotBits);
     int slot = -1;
-    for (int step = 0; step < kBwdProbe; ++step) {
+    for (int step = key == kBwdInside ? kBwdProbe : 0; step < kBwdProbe; ++step) {
       const uint32_t old = atomicCAS(&s_key[h], 0u, key);
       if (old == 0u || old == key) {
         slot = (int)h;
@@ -193,19 +224,28 @@ __global__ void __launch_bounds__(kBlock) backward_samples_kernel(BackwardSet bs
     }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < kBwdSlots; q += kBlock) {
+  // list the slots taken and mark the triangles that the tile holds all of
+  for (int q0 = 0; q0 < kBwdSlots; q0 += kBwdBlock) {
+    const int q = q0 + (int)threadIdx.x;
     const uint32_t key = s_key[q];
-    if (key == 0u) continue;
-    const int64_t t = (int64_t)(key - 1u);
-    float* a6 = accp + 6 * t;
-    if (projection_in_tile(bs, im, t, x0, y0, cw, ch)) {
-#pragma unroll
-      for (int c = 0; c < 6; ++c) a6[c] = s_val[q][c];
-    } else {
-#pragma unroll
-      for (int c = 0; c < 6; ++c)
-        if (s_val[q][c] != 0.0f) atomicAdd(a6 + c, s_val[q][c]);
+    const uint64_t taken = __ballot(key != 0u);
+    uint32_t to = 0;
+    if (lane == 0 && taken != 0) to = atomicAdd(&s_taken, (uint32_t)__popcll(taken));
+    to = __shfl(to, 0, 64);
+    if (key != 0u) {
+      s_used[to + (uint32_t)__popcll(taken & ((1ull << lane) - 1))] = (uint16_t)q;
+      if (projection_in_tile(bs, im, (int64_t)(key - 1u), x0, y0, cw, ch)) s_key[q] = key | kBwdInside;
     }
+  }
+  __syncthreads();
+  const int n_sums = 6 * (int)s_taken;
+  for (int e = threadIdx.x; e < n_sums; e += kBwdBlock) {
+    const int q = s_used[e / 6], c = e % 6;
+    const uint32_t key = s_key[q];
+    const float x = s_val[q][c];
+    float* const to = accp + 6 * (int64_t)((key & ~kBwdInside) - 1u) + c;
+    if (key & kBwdInside) *to = x;
+    else if (x != 0.0f) atomicAdd(to, x);
   }
 }
 
@@ -273,21 +313,33 @@ __device__ bool triangle_gradient(const BackwardSet& bs, int64_t t, int32_t (&vi
   return true;
 }
 
-// One thread per triangle, adding to its three vertices with global atomics.
-// (Neighbouring lanes add to neighbouring vertices, so a wave's atomics meet
-// few cache lines; summing per vertex in an LDS table first was slower:
-// 80 against 30 us on the flower.)
+// One thread per triangle, adding to its three vertices with global atomics,
+// the bound: the nine values go through LDS so that neighbouring lanes add
+// neighbouring floats (each lane its own nine: 40 us for 261,120 triangles, now
+// 27; summing per vertex in an LDS table first was slower than either).
 __global__ void __launch_bounds__(kBlock) backward_triangles_kernel(BackwardSet bs, int64_t n_tris,
                                                                     float* grad) {
+  __shared__ float s_g[kBlock / 64][64 * 9];
+  __shared__ int32_t s_to[kBlock / 64][64 * 3];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   int32_t vid[3];
   double g[3][3];
-  if (t >= n_tris || !triangle_gradient(bs, t, vid, g)) return;
+  const bool any = t < n_tris && triangle_gradient(bs, t, vid, g);
 #pragma unroll
-  for (int q = 0; q < 3; ++q)
+  for (int q = 0; q < 3; ++q) {
+    s_to[wave][3 * lane + q] = any ? vid[q] : -1;
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-      if (g[q][c] != 0.0) atomicAdd(grad + 3 * (int64_t)vid[q] + c, (float)g[q][c]);
+    for (int c = 0; c < 3; ++c) s_g[wave][9 * lane + 3 * q + c] = any ? (float)g[q][c] : 0.0f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int e = 64 * k + lane;
+    const int32_t v = s_to[wave][e / 3];
+    const float x = s_g[wave][e];
+    if (v >= 0 && x != 0.0f) atomicAdd(grad + 3 * (int64_t)v + e % 3, x);
+  }
 }
 
 }  // namespace
@@ -328,7 +380,7 @@ hipError_t launch_backward(const BackwardArgs& args, hipStream_t s) {
     bs.block_start[k + 1] = bs.block_start[k] + nt * nt;
   }
   if (args.n > 0 && bs.block_start[args.n] > 0)
-    hipLaunchKernelGGL(backward_samples_kernel, dim3(bs.block_start[args.n]), dim3(kBlock), 0, s, bs);
+    hipLaunchKernelGGL(backward_samples_kernel, dim3(bs.block_start[args.n]), dim3(kBwdBlock), 0, s, bs);
   if (args.n_tris > 0)
     hipLaunchKernelGGL(backward_triangles_kernel, dim3(grid_for(args.n_tris, kBlock)), dim3(kBlock), 0, s,
                        bs, args.n_tris, args.grad);
