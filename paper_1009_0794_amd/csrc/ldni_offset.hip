@@ -19,9 +19,8 @@
 // are numbered over the x-, y-, z-LDNI in storage order; a sphere's sample
 // gets id -1 - g.
 //
-// Passes: the sphere centres (one thread per pixel); binning of the spheres
-// into the lists of the rays they hit (count, scan, scatter); then one wave
-// per ray, twice.  The count pass (offset_union_kernel) merges the chords of a
+// Passes: the sphere centres; binning of the spheres into the lists of the
+// rays they hit (count, scan, scatter); then one wave per ray, twice.  The count pass (offset_union_kernel) merges the chords of a
 // ray into the few intervals they cover together before it sorts anything, and
 // keeps the result's end points for the write pass.  Rays that this leaves with
 // too many events, and rays with more end points than are kept, go through the
@@ -53,27 +52,47 @@ __device__ __forceinline__ double centre_of(const OffsetArgs& g, int b, int i) {
   return (double)(float)(g.lo[b] + ((double)i + 0.5) * g.h[b]);
 }
 
-// Centres of the spheres: one thread per pixel of each LDNI writes the
-// centres of the pixel's samples (world order) at the sample's number.
+// Centres of the spheres (world order), at the sample's number: a wave takes
+// the samples of 64 pixels in a row, a sample per lane (a lane per pixel:
+// 31 us for 405,002 samples at w = 256, now 21).
 __global__ __launch_bounds__(kOffBlock) void offset_centres_kernel(OffsetArgs g) {
+  __shared__ uint32_t s_off[kOffWaves][65];
   const int64_t npix = (int64_t)g.w * g.w;
-  const int64_t t = (int64_t)blockIdx.x * kOffBlock + threadIdx.x;
-  if (t >= 3 * npix) return;
-  const int a = (int)(t / npix);
-  const int64_t p = t - a * npix;
+  const int lane = threadIdx.x & 63;
+  uint32_t* const off = s_off[threadIdx.x >> 6];
+  const int64_t groups = (npix + 63) / 64;
+  const int64_t group = (int64_t)blockIdx.x * kOffWaves + (threadIdx.x >> 6);
+  if (group >= 3 * groups) return;
+  const int a = (int)(group / groups);
+  const int64_t p0 = (group - a * groups) * 64;
+  const int n = (int)min((int64_t)64, npix - p0);
   const int u = (a + 1) % 3, v = (a + 2) % 3;
   const AxisArrays& ax = g.in[a];
-  const uint32_t o0 = ax.offsets[p], o1 = ax.offsets[p + 1];
-  if (o1 < o0 || (uint64_t)o1 > ax.n) {
-    atomicOr(g.status, kStatusMismatch);
+  uint32_t o0 = 0, o1 = 0;
+  if (lane < n) {
+    o0 = ax.offsets[p0 + lane];
+    o1 = ax.offsets[p0 + lane + 1];
+    off[lane] = o0;
+    if (lane == n - 1) off[n] = o1;
+  }
+  if (__ballot(lane < n && (o1 < o0 || (uint64_t)o1 > ax.n)) != 0) {
+    if (lane == 0) atomicOr(g.status, kStatusMismatch);
     return;
   }
-  const double cu = centre_of(g, u, (int)(p % g.w)), cv = centre_of(g, v, (int)(p / g.w));
-  for (uint32_t q = o0; q < o1; ++q) {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t first = off[0], last = off[n];
+  for (uint32_t q = first + (uint32_t)lane; q < last; q += 64) {
+    int k = 0;  // the last pixel with off[k] <= q
+    for (int hi = n - 1; k < hi;) {
+      const int mid = (k + hi + 1) >> 1;
+      if (off[mid] <= q) k = mid; else hi = mid - 1;
+    }
+    const int64_t p = p0 + k;
     double* c = g.centres + 3 * (g.base[a] + q);
     c[a] = g.lo[a] + (double)ax.depth[q];
-    c[u] = cu;
-    c[v] = cv;
+    c[u] = centre_of(g, u, (int)(p % g.w));
+    c[v] = centre_of(g, v, (int)(p / g.w));
   }
 }
 
@@ -83,7 +102,7 @@ __global__ __launch_bounds__(kOffBlock) void offset_centres_kernel(OffsetArgs g)
 // i0 > i1 if none.
 __device__ __forceinline__ void pixel_range(const OffsetArgs& g, int b, double x, int& i0, int& i1) {
   const double t0 = (x - g.r - g.lo[b]) / g.h[b] - 0.5, t1 = (x + g.r - g.lo[b]) / g.h[b] - 0.5;
-  const double f0 = floor(t0 - g.margin[b]), f1 = ceil(t1 + g.margin[b]);
+  const double f0 = ceil(t0 - g.margin[b]), f1 = floor(t1 + g.margin[b]);
   i0 = f0 < 0.0 ? 0 : f0 > (double)(g.w - 1) ? g.w : (int)f0;
   i1 = f1 < 0.0 ? -1 : f1 > (double)(g.w - 1) ? g.w - 1 : (int)f1;
 }
@@ -92,26 +111,53 @@ __device__ __forceinline__ void pixel_range(const OffsetArgs& g, int b, double x
 // that the sphere hits (rho^2 < r^2, the test of the ray pass); count
 // (kScatter false) or write the sphere into those rays' lists.  A workgroup
 // (256 consecutive spheres of one image, which mostly hit the same rays)
-// first adds its (sphere, ray) pairs per ray into an LDS table, one addition
-// per run of lanes holding the same ray, and then touches each ray's global
-// counter once: the count pass adds its pairs to ray_count; the scatter pass
-// reserves a range of the ray's list from ray_cursor and, in a second sweep
-// over the same pairs, places each run in its slot's range with an LDS
-// atomic.  A ray that finds no free slot (kBinProbe probes) is counted and
-// placed run by run with global atomics; slots never free, so it misses the
-// table in the second sweep as well.
-template <bool kScatter>
-__global__ __launch_bounds__(kOffBlock) void offset_bin_kernel(OffsetArgs g) {
-  __shared__ BinLds h;
-  for (int i = threadIdx.x; i < kBinSlots; i += kOffBlock) {
-    h.key[i] = kBinEmpty;
-    h.a[i] = 0u;
-    h.b[i] = 0u;
+// first adds its (sphere, ray) pairs per ray into an LDS table, and then
+// touches each ray's global counter once: the count pass adds its pairs to
+// ray_count; the scatter pass reserves a range of the ray's list from
+// ray_cursor and, in a second sweep over the same pairs, fills it.  A ray that
+// finds no free entry (kBinProbe probes) is counted and placed with global
+// atomics; entries never free, so it misses the table in the second sweep as
+// well.
+// Bound by the exact tests and by the global atomics, which go out to memory
+// a cache line each: an entry holds eight rays in a row, so that lanes in a row
+// add to one line (405,002 spheres at w = 256: 0.72 M lines instead of 2.6 M).
+// Count and scatter there: 169 and 264 us when every lane tested its next
+// pixel and added in the same step, 130 and 180 us with the hits as masks, 51
+// and 108 us with entries of eight rays (of sixteen: 61 and 171 us).
+constexpr int kRayGroup = 8;  // rays in a row that share a table entry
+constexpr int kRayGroupBits = 9;
+constexpr int kRayGroups = 1 << kRayGroupBits;
+struct RayTable {
+  uint32_t key[kRayGroups];            // first ray / kRayGroup, or kBinEmpty
+  uint32_t n[kRayGroups * kRayGroup];  // pairs counted; or the list position of the ray's next one
+};
+
+// The counter of a ray, its group claimed if new; -1 if no entry is free within kBinProbe probes.
+__device__ __forceinline__ int ray_slot(RayTable& h, uint32_t ray) {
+  const uint32_t k = ray / kRayGroup;
+  uint32_t s = (k * 2654435761u) >> (32 - kRayGroupBits);
+  for (int i = 0; i < kBinProbe; ++i) {
+    uint32_t was = h.key[s];
+    if (was == kBinEmpty) was = atomicCAS(&h.key[s], kBinEmpty, k);
+    if (was == kBinEmpty || was == k) return (int)(s * kRayGroup + ray % kRayGroup);
+    s = (s + 1) & (kRayGroups - 1);
   }
+  return -1;
+}
+
+// kSmall: no sphere's range has more than eight pixels a side, so that its hits
+// are a mask of 64 bits: the exact tests are made once, without a wave's other
+// lanes, and then every step takes a hit of each lane.
+template <bool kScatter, bool kSmall>
+__global__ __launch_bounds__(kOffBlock) void offset_bin_kernel(OffsetArgs g) {
+  __shared__ RayTable h;
+  constexpr int kPer = kRayGroups * kRayGroup / kOffBlock;
+  for (int i = threadIdx.x; i < kRayGroups; i += kOffBlock) h.key[i] = kBinEmpty;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) h.n[i * kOffBlock + threadIdx.x] = 0u;
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * kOffBlock + threadIdx.x;
-  const int lane = (int)__lane_id();
-  int a = 0, u = 0, v = 0, ni = 0, n_my = 0, iu0 = 0, iv0 = 0;
+  int a = 0, u = 0, v = 0, ni = 0, nj = 0, n_my = 0, iu0 = 0, iv0 = 0;
   uint32_t s = 0;
   double pu = 0.0, pv = 0.0;
   if (t < 3 * (int64_t)g.n_spheres) {
@@ -127,14 +173,40 @@ __global__ __launch_bounds__(kOffBlock) void offset_bin_kernel(OffsetArgs g) {
     pixel_range(g, v, pv, iv0, iv1);
     if (iu0 <= iu1 && iv0 <= iv1) {
       ni = iu1 - iu0 + 1;
-      n_my = ni * (iv1 - iv0 + 1);
+      nj = iv1 - iv0 + 1;
+      n_my = ni * nj;
     }
   }
   const double r2 = g.r * g.r;
   const int64_t npix = (int64_t)g.w * g.w;
-  // every lane's j-th pixel, j = 0, 1, ... while any lane has one; the ray
-  // it hits (or -1) and the runs of equal rays
-  auto sweep = [&](auto&& on_run) {
+  uint64_t hits = 0;  // kSmall: bit 8 j + i for pixel (iu0 + i, iv0 + j)
+  if (kSmall) {
+    double du2[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const double du = centre_of(g, u, iu0 + i) - pu;
+      du2[i] = du * du;
+    }
+    for (int j = 0; __ballot(j < nj) != 0; ++j) {
+      const double dv = centre_of(g, v, iv0 + j) - pv, dv2 = dv * dv;
+      uint32_t m = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m |= du2[i] + dv2 < r2 ? 1u << i : 0u;
+      if (j < nj) hits |= (uint64_t)(m & ((1u << ni) - 1u)) << (8 * j);
+    }
+  }
+  // kSmall: every lane's next hit while any lane has one; else every lane's
+  // j-th pixel, j = 0, 1, ...  The ray it hits (or -1) and the runs of equal
+  // rays
+  auto sweep = [&](auto&& on_ray) {
+    if (kSmall) {
+      for (uint64_t m = hits; __ballot(m != 0) != 0; m &= m - 1) {
+        const int j = __ffsll((unsigned long long)m) - 1;
+        const int my = m != 0 ? (int)(a * npix + (int64_t)(iv0 + (j >> 3)) * g.w + iu0 + (j & 7)) : -1;
+        on_ray(my);
+      }
+      return;
+    }
     for (int j = 0; __ballot(j < n_my) != 0; ++j) {
       int my = -1;
       if (j < n_my) {
@@ -142,34 +214,38 @@ __global__ __launch_bounds__(kOffBlock) void offset_bin_kernel(OffsetArgs g) {
         const double du = centre_of(g, u, iu) - pu, dv = centre_of(g, v, iv) - pv;
         if (du * du + dv * dv < r2) my = (int)(a * npix + (int64_t)iv * g.w + iu);
       }
-      on_run(my, lane_runs(my));
+      on_ray(my);
     }
   };
-  sweep([&](int my, const LaneRuns& r) {
-    if (my >= 0 && r.leader == lane) {
-      const int sl = bin_insert(h, (uint32_t)my);
-      if (sl >= 0) atomicAdd(&h.a[sl], r.group);
-      else if (!kScatter) atomicAdd(&g.ray_count[my], r.group);
-    }
+  sweep([&](int my) {
+    if (my < 0) return;
+    const int sl = ray_slot(h, (uint32_t)my);
+    if (sl >= 0) atomicAdd(&h.n[sl], 1u);
+    else if (!kScatter) atomicAdd(&g.ray_count[my], 1u);
   });
   __syncthreads();
-  for (int i = threadIdx.x; i < kBinSlots; i += kOffBlock) {
-    const uint32_t k = h.key[i];
-    if (k == kBinEmpty) continue;
-    if (!kScatter) atomicAdd(&g.ray_count[k], h.a[i]);
-    else h.a[i] = g.ray_start[k] + atomicAdd(&g.ray_cursor[k], h.a[i]);
+  uint32_t ray[kPer], n[kPer], at[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int q = i * kOffBlock + (int)threadIdx.x;
+    n[i] = h.n[q];
+    ray[i] = h.key[q / kRayGroup] * kRayGroup + (uint32_t)(q % kRayGroup);
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (n[i] == 0) continue;
+    if (!kScatter) atomicAdd(&g.ray_count[ray[i]], n[i]);
+    else at[i] = g.ray_start[ray[i]] + atomicAdd(&g.ray_cursor[ray[i]], n[i]);
   }
   if (!kScatter) return;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i)
+    if (n[i] != 0) h.n[i * kOffBlock + threadIdx.x] = at[i];
   __syncthreads();
-  sweep([&](int my, const LaneRuns& r) {
-    uint32_t lead_base = 0;
-    if (my >= 0 && r.leader == lane) {
-      const int sl = bin_find(h, (uint32_t)my);
-      lead_base = sl >= 0 ? h.a[sl] + atomicAdd(&h.b[sl], r.group)
-                          : g.ray_start[my] + atomicAdd(&g.ray_cursor[my], r.group);
-    }
-    const uint32_t base = (uint32_t)__shfl((int)lead_base, r.leader, 64);
-    if (my >= 0) g.list[base + r.rank] = s;
+  sweep([&](int my) {
+    if (my < 0) return;
+    const int sl = ray_slot(h, (uint32_t)my);
+    g.list[sl >= 0 ? atomicAdd(&h.n[sl], 1u) : g.ray_start[my] + atomicAdd(&g.ray_cursor[my], 1u)] = s;
   });
 }
 
@@ -1056,8 +1132,9 @@ __global__ __launch_bounds__(kOffBlock) void offset_union_kernel(OffsetArgs g) {
 }  // namespace
 
 hipError_t launch_offset_centres(const OffsetArgs& g, hipStream_t s) {
-  const int64_t n = 3 * (int64_t)g.w * g.w;
-  hipLaunchKernelGGL(offset_centres_kernel, dim3((unsigned)((n + kOffBlock - 1) / kOffBlock)), dim3(kOffBlock), 0, s, g);
+  const int64_t groups = 3 * (((int64_t)g.w * g.w + 63) / 64);
+  hipLaunchKernelGGL(offset_centres_kernel, dim3((unsigned)((groups + kOffWaves - 1) / kOffWaves)), dim3(kOffBlock), 0, s,
+                     g);
   return hipGetLastError();
 }
 
@@ -1065,8 +1142,13 @@ hipError_t launch_offset_bin(const OffsetArgs& g, bool scatter, hipStream_t s) {
   const int64_t n = 3 * (int64_t)g.n_spheres;
   if (n == 0) return hipSuccess;
   const dim3 grid((unsigned)((n + kOffBlock - 1) / kOffBlock));
-  if (scatter) hipLaunchKernelGGL(offset_bin_kernel<true>, grid, dim3(kOffBlock), 0, s, g);
-  else hipLaunchKernelGGL(offset_bin_kernel<false>, grid, dim3(kOffBlock), 0, s, g);
+  // a range lies within 2 (r / h + margin) pixels: less than eight of them hold
+  // at most eight centres
+  bool small = true;
+  for (int b = 0; b < 3; ++b) small = small && 2.0 * (g.r / g.h[b] + g.margin[b]) < 7.9;
+  const auto kernel = small ? (scatter ? offset_bin_kernel<true, true> : offset_bin_kernel<false, true>)
+                            : (scatter ? offset_bin_kernel<true, false> : offset_bin_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kOffBlock), 0, s, g);
   return hipGetLastError();
 }
 
