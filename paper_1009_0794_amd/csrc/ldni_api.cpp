@@ -1409,7 +1409,7 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   const size_t o_deep = align_up(o_scratch + scratch);
   const size_t o_centres = align_up(o_deep + sizeof(uint32_t) * (size_t)n_rays);
   // the end points the count pass keeps for the write pass: as many per ray
-  // (64, 32 or 16) as fit in 1 GiB, else none (the write pass recomputes)
+  // (128, 64, 32 or 16) as fit in 1 GiB, else none (the write pass recomputes)
   size_t saved_cap = (size_t)1 << 30;
   // test hook: a smaller budget for them (0: none kept)
   if (const char* env = std::getenv("LDNI_OFFSET_KEEP_BYTES")) saved_cap = std::strtoull(env, nullptr, 10);
@@ -1542,6 +1542,7 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   FailWord word;
   if (!fail_word(&word, false)) return bail(fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer"));
   g.host_fail = word.host;
+  g.most_out = std::max(max_layers[0], std::max(max_layers[1], max_layers[2]));
   e = timed("offset_write", stream, [&] { return launch_offset_rays(g, true, stream); });
   if (e != hipSuccess) {
     drop_fail_word(&word);

@@ -341,7 +341,7 @@ hipError_t launch_node_stats(const NodeArgs& g, uint32_t* host, hipStream_t s);
 constexpr int kOffsetBuf = 1024;              // events of one depth window of one ray, in LDS
 constexpr int kOffsetKeep = 896;              // a full window is cut back to fewer events than this
 constexpr int kOffsetEmit = 128;              // end points of one ray's result before small volumes go
-constexpr int kOffsetSavedMax = 64;           // most end points per ray the count pass keeps for the write pass
+constexpr int kOffsetSavedMax = 128;          // most end points per ray the count pass keeps for the write pass
 constexpr int kOffsetDeep = 512;              // a ray with more spheres than this is started first
 constexpr int kUnionEvents = 192;             // events of a ray that the count pass takes after merging chords
 constexpr int kUnionCells = 768;              // most depth cells of a ray (12 KB of LDS per wave)
@@ -366,6 +366,7 @@ struct OffsetArgs {
   int32_t* out_tri[3];
   uint64_t* saved;   // [3 * w * w][n_saved] kept end-point keys, or null (the write pass recomputes)
   uint32_t n_saved;  // end points kept per ray (at most kOffsetSavedMax)
+  uint32_t most_out; // the write pass: most end points of a ray
   // rays with more than kOffsetDeep spheres, listed (any order) so that the
   // ray passes start them first; n_deep of them (known to the host before
   // the ray passes; status[16] counts them on the device)
@@ -373,7 +374,8 @@ struct OffsetArgs {
   uint32_t n_deep;
   // depth cells of the count pass (n_cells = 0: every ray is swept over all its
   // events): 1 / cell size, the half length from which a chord covers its cell,
-  // and the rays left to the sweep (status[17] of them)
+  // and the rays left to the sweep (by the count pass, status[17] of them, and
+  // then by the write pass, status[18])
   int32_t n_cells;
   double inv_cell, long_chord;
   uint32_t* rest;

@@ -20,9 +20,11 @@
 // gets id -1 - g.
 //
 // Passes: the sphere centres; binning of the spheres into the lists of the
-// rays they hit (count, scan, scatter); then one wave per ray, twice.  The count pass (offset_union_kernel) merges the chords of a
+// rays they hit (count, scan, scatter); one wave per ray; and the result's
+// samples.  The count pass (offset_union_kernel) merges the chords of a
 // ray into the few intervals they cover together before it sorts anything, and
-// keeps the result's end points for the write pass.  Rays that this leaves with
+// keeps the result's end points for the write pass (offset_write_kernel, a
+// sample per lane).  Rays that this leaves with
 // too many events, and rays with more end points than are kept, go through the
 // sweep over all events (sweep_ray): they go to a wave-private LDS buffer as
 // 64-bit keys (orderable depth, order), window by window in depth when they do
@@ -379,8 +381,6 @@ __device__ __forceinline__ void wave_sort(uint64_t* key, uint32_t n) {
 static_assert(kOffsetKeep + 128 <= kOffsetBuf, "a cut window takes one more step of 128 events");
 // a sweep step appends up to 64 end points after a flush that leaves one
 static_assert(kOffsetEmit >= 65, "the emit buffer takes one step after a flush");
-// a ray's kept end points are expanded by one wave, one per lane
-static_assert(kOffsetSavedMax <= 64, "kept end points are written one per lane");
 __device__ __forceinline__ uint32_t select_depth(const uint64_t* key, uint32_t n, uint32_t rank, uint32_t* hist) {
   const uint32_t lane = lane_id();
   uint32_t prefix = 0, mask = 0;
@@ -475,11 +475,6 @@ __device__ void sweep_ray(const OffsetArgs& g, int64_t ray, RayLds& lds) {
     out = g.out_offsets[a][p];
     cnt = g.out_offsets[a][p + 1] - out;
     if (cnt == 0) return;
-    // a ray whose end points the count pass kept: expand them
-    if (g.saved && cnt <= g.n_saved) {
-      if (lane < cnt) write_event(g, a, p, cu, cv, g.saved[(size_t)ray * g.n_saved + lane], (size_t)out + lane);
-      return;
-    }
   }
   const uint32_t o0 = H.offsets[p], o1 = H.offsets[p + 1];
   uint32_t nh = 0;
@@ -744,13 +739,58 @@ __global__ __launch_bounds__(kOffBlock) void offset_ray_kernel(OffsetArgs g) {
   if (ray >= 0) sweep_ray<kWrite>(g, ray, lds);
 }
 
-// The rays that offset_union_kernel left (g.rest), wave after wave.
+// The rays that offset_union_kernel or offset_write_kernel left (g.rest), wave after wave.
+template <bool kWrite>
 __global__ __launch_bounds__(kOffBlock) void offset_rest_kernel(OffsetArgs g) {
   __shared__ RayLds lds;
-  const uint32_t n = min(g.status[17], (uint32_t)(3 * (int64_t)g.w * g.w));
+  const uint32_t n = min(g.status[kWrite ? 18 : 17], (uint32_t)(3 * (int64_t)g.w * g.w));
   for (uint32_t q = blockIdx.x * kOffWaves + (threadIdx.x >> 6); q < n; q += gridDim.x * kOffWaves) {
-    sweep_ray<false>(g, g.rest[q], lds);
+    sweep_ray<kWrite>(g, g.rest[q], lds);
     wave_sync();
+  }
+}
+
+// The write pass over the end points that the count pass kept: a wave takes
+// the result samples of 64 rays in a row, a sample per lane.  Rays with more
+// end points than are kept are listed for offset_rest_kernel.  Bound by the
+// gathers of kept end points and centres: 16 us at w = 256 (a wave per ray,
+// with most lanes idle: 124 us).
+__global__ __launch_bounds__(kOffBlock) void offset_write_kernel(OffsetArgs g) {
+  __shared__ uint32_t s_off[kOffWaves][65];
+  const int64_t npix = (int64_t)g.w * g.w, groups = (npix + 63) / 64;
+  const uint32_t lane = lane_id();
+  uint32_t* const off = s_off[threadIdx.x >> 6];
+  const int64_t group = (int64_t)blockIdx.x * kOffWaves + (threadIdx.x >> 6);
+  if (group >= 3 * groups) return;
+  const int a = (int)(group / groups), u = (a + 1) % 3, v = (a + 2) % 3;
+  const int64_t p0 = (group - a * groups) * 64;
+  const int n = (int)min((int64_t)64, npix - p0);
+  bool deep = false;
+  if ((int)lane < n) {
+    const uint32_t o0 = g.out_offsets[a][p0 + lane], o1 = g.out_offsets[a][p0 + lane + 1];
+    off[lane] = o0;
+    if ((int)lane == n - 1) off[n] = o1;
+    deep = o1 - o0 > g.n_saved;
+  }
+  const uint64_t m = __ballot(deep);
+  if (m != 0) {
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&g.status[18], (uint32_t)__popcll(m));
+    at = (uint32_t)__shfl((int)at, 0);
+    if (deep) g.rest[at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)(a * npix + p0 + lane);
+  }
+  wave_sync();
+  const uint32_t first = off[0], last = off[n];
+  for (uint32_t q = first + lane; q < last; q += 64) {
+    int k = 0;  // the last ray with off[k] <= q
+    for (int hi = n - 1; k < hi;) {
+      const int mid = (k + hi + 1) >> 1;
+      if (off[mid] <= q) k = mid; else hi = mid - 1;
+    }
+    if (off[k + 1] - off[k] > g.n_saved) continue;
+    const int64_t p = p0 + k;
+    write_event(g, a, p, centre_of(g, u, (int)(p % g.w)), centre_of(g, v, (int)(p / g.w)),
+                g.saved[(size_t)(a * npix + p) * g.n_saved + (q - off[k])], q);
   }
 }
 
@@ -1176,13 +1216,18 @@ hipError_t launch_offset_deep(const OffsetArgs& g, hipStream_t s) {
 hipError_t launch_offset_rays(const OffsetArgs& g, bool write, hipStream_t s) {
   const int64_t rays = 3 * (int64_t)g.w * g.w + g.n_deep;
   const dim3 grid((unsigned)((rays + kOffWaves - 1) / kOffWaves));
-  if (write) {
+  const dim3 rest(grid.x < 1024 ? grid.x : 1024);  // (four workgroups of it fit a CU)
+  if (write && g.saved) {
+    const int64_t groups = 3 * (((int64_t)g.w * g.w + 63) / 64);
+    hipLaunchKernelGGL(offset_write_kernel, dim3((unsigned)((groups + kOffWaves - 1) / kOffWaves)), dim3(kOffBlock), 0, s,
+                       g);
+    if (g.most_out > g.n_saved) hipLaunchKernelGGL(offset_rest_kernel<true>, rest, dim3(kOffBlock), 0, s, g);
+  } else if (write) {
     hipLaunchKernelGGL(offset_ray_kernel<true>, grid, dim3(kOffBlock), 0, s, g);
   } else if (g.n_cells > 0) {
     const size_t lds = kOffWaves * sizeof(uint64_t) * (size_t)union_words(g.n_cells);
     hipLaunchKernelGGL(offset_union_kernel, grid, dim3(kOffBlock), lds, s, g);
-    // (four workgroups of it fit a CU)
-    hipLaunchKernelGGL(offset_rest_kernel, dim3(grid.x < 1024 ? grid.x : 1024), dim3(kOffBlock), 0, s, g);
+    hipLaunchKernelGGL(offset_rest_kernel<false>, rest, dim3(kOffBlock), 0, s, g);
   } else {
     hipLaunchKernelGGL(offset_ray_kernel<false>, grid, dim3(kOffBlock), 0, s, g);
   }
