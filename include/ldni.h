@@ -129,6 +129,13 @@ ldni_status ldni_sample(const float *verts, int64_t n_verts, const int32_t *tris
  * pass counted -- the result must then not be used. */
 ldni_status ldni_result_axis(const ldni_result *r, int axis, ldni_axis_view *view);
 
+/* Copies the arrays of a view (offsets [w*w + 1], depth [n], normal [n][3] or
+ * the codes [n] of a view with 8-bit normals, tri [n]) into device memory of the
+ * caller's, behind the work on hip_stream.  LDNI_ERR_INVALID_ARG for NULL
+ * offsets, or NULL sample arrays where the view has samples. */
+ldni_status ldni_axis_copy(const ldni_axis_view *view, uint32_t *offsets, float *depth, void *normal,
+                           int32_t *tri, void *hip_stream);
+
 /* Release a result -- the LDNIs of Definition 3 it holds (NULL-safe).  Its
  * buffers are kept by the library for later calls on the stream the result
  * was made on (reused in that stream's order, like hipFreeAsync), which must

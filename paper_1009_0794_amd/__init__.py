@@ -430,16 +430,8 @@ def _copy_view(v: _lib.AxisView, axis: int, device) -> LDNI:
                (torch.empty(n, dtype=torch.int32, device=device) if rgb8 else
                 torch.empty((n, 3), dtype=torch.float32, device=device)),
                torch.empty(n, dtype=torch.int32, device=device))
-    H = _lib.hip()
-    st = _stream(device)
-    for dst, src, nbytes in ((out.offsets, v.offsets, 4 * out.offsets.numel()),
-                             (out.depth, v.depth, 4 * n),
-                             (out.normal, v.normal_rgb8 if rgb8 else v.normal, (4 if rgb8 else 12) * n),
-                             (out.tri, v.tri, 4 * n)):
-        if nbytes:
-            rc = H.hipMemcpyAsync(dst.data_ptr(), src, nbytes, 3, st)
-            if rc != 0:
-                raise RuntimeError(f"hipMemcpyAsync failed ({rc})")
+    _lib.check(_lib.lib().ldni_axis_copy(ctypes.byref(v), out.offsets.data_ptr(), out.depth.data_ptr(),
+                                         out.normal.data_ptr(), out.tri.data_ptr(), _stream(device)))
     return out
 
 

@@ -63,6 +63,8 @@ def lib():
     L.ldni_sample.restype = st
     L.ldni_result_axis.argtypes = [vp, ctypes.c_int, ctypes.POINTER(AxisView)]
     L.ldni_result_axis.restype = st
+    L.ldni_axis_copy.argtypes = [ctypes.POINTER(AxisView), vp, vp, vp, vp, vp]
+    L.ldni_axis_copy.restype = st
     L.ldni_free.argtypes = [vp]
     L.ldni_free.restype = None
     L.ldni_trim.argtypes = []
@@ -125,20 +127,6 @@ def check(code: int) -> None:
         raise LDNIError(int(code), detail)
 
 
-_hip = None
-
-
-def hip():
-    """The HIP runtime (for device-to-device copies of library-owned views)."""
-    global _hip
-    if _hip is None:
-        _hip = ctypes.CDLL("libamdhip64.so")
-        _hip.hipMemcpyAsync.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
-                                        ctypes.c_int, ctypes.c_void_p]
-        _hip.hipMemcpyAsync.restype = ctypes.c_int
-    return _hip
-
-
 def exported_symbols():
     """Names of the C ABI functions declared in include/ldni.h."""
     return ["ldni_sample", "ldni_result_axis", "ldni_free", "ldni_trim", "ldni_sample_begin",
@@ -147,4 +135,4 @@ def exported_symbols():
             "ldni_profile_enable", "ldni_profile_read", "ldni_backward", "ldni_batch_create",
             "ldni_batch_run", "ldni_batch_axis", "ldni_batch_free", "ldni_sample_batch",
             "ldni_boolean", "ldni_sample_finish_rgb8", "ldni_classify_nodes", "ldni_node_words",
-            "ldni_offset", "ldni_backward_noalloc"]
+            "ldni_offset", "ldni_backward_noalloc", "ldni_axis_copy"]

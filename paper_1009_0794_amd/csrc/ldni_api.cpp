@@ -1122,6 +1122,25 @@ ldni_status ldni_result_axis(const ldni_result* r, int axis, ldni_axis_view* vie
   return LDNI_OK;
 }
 
+ldni_status ldni_axis_copy(const ldni_axis_view* view, uint32_t* offsets, float* depth, void* normal, int32_t* tri,
+                           void* hip_stream) {
+  if (!view || !view->offsets || !offsets) return fail(LDNI_ERR_INVALID_ARG, "NULL view or offsets");
+  if (view->w < 1 || view->w > 16384) return fail(LDNI_ERR_INVALID_ARG, "w must be in [1, 16384]");
+  const bool rgb8 = view->normal_rgb8 != nullptr;
+  const void* from = rgb8 ? static_cast<const void*>(view->normal_rgb8) : view->normal;
+  const int64_t n = (int64_t)view->n_samples;
+  if (n > 0 && (!view->depth || !from || !view->tri || !depth || !normal || !tri))
+    return fail(LDNI_ERR_INVALID_ARG, "NULL sample array of a view with samples");
+  const CopyArrays c{{view->offsets, reinterpret_cast<const uint32_t*>(view->depth), static_cast<const uint32_t*>(from),
+                      reinterpret_cast<const uint32_t*>(view->tri)},
+                     {offsets, reinterpret_cast<uint32_t*>(depth), static_cast<uint32_t*>(normal),
+                      reinterpret_cast<uint32_t*>(tri)},
+                     {(int64_t)view->w * view->w + 1, n, rgb8 ? n : 3 * n, n},
+                     {}};
+  HIP_TRY(launch_copy_arrays(c, static_cast<hipStream_t>(hip_stream)), "copy kernel");
+  return LDNI_OK;
+}
+
 ldni_status ldni_trim(void) {
   std::vector<CachedBuffer> all;
   {

@@ -149,6 +149,15 @@ void finish_image_geometry(Image& im);
 
 // ---- launchers (ldni_kernels.hip) ----
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);
+// The arrays of a view (offsets, depth, normal, tri), in 32-bit words.
+constexpr int kCopyArrays = 4;
+struct CopyArrays {
+  const uint32_t* src[kCopyArrays];
+  uint32_t* dst[kCopyArrays];
+  int64_t words[kCopyArrays];
+  uint32_t block_start[kCopyArrays + 1];  // (set by the launch)
+};
+hipError_t launch_copy_arrays(CopyArrays c, hipStream_t s);
 // per chunk of triangles: gather, validate, normal, candidate rectangles,
 // and the entries and candidates of every tile met, reserved per chunk
 // (tile_cnt, tile_region, tile_ovf cleared before; m.bin_rec/bin_nrec

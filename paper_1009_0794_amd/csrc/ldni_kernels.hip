@@ -1390,6 +1390,35 @@ __global__ void __launch_bounds__(kBlock) fill_u32_kernel(uint32_t* p, uint32_t 
 }
 
 // ---------------------------------------------------------------------------
+// copy of a view's arrays
+// ---------------------------------------------------------------------------
+// All arrays in one launch: a workgroup takes kCopyWords words of one of them,
+// four 16-byte vectors per lane where both sides are aligned.  Small views are
+// bound by the launch, large ones by HBM (a copy of the runtime's per array: 94 us
+// more for 16 views of up to 1024 x 1024 rays, 24 us for one of 2048 x 2048).
+constexpr int kCopyWords = 16 * kBlock;
+
+__global__ void __launch_bounds__(kBlock) copy_arrays_kernel(CopyArrays c) {
+  int k = 0;
+  while (blockIdx.x >= c.block_start[k + 1]) ++k;
+  const int64_t i0 = (int64_t)(blockIdx.x - c.block_start[k]) * kCopyWords;
+  const uint32_t* src = c.src[k] + i0;
+  uint32_t* dst = c.dst[k] + i0;
+  const int n = (int)min((int64_t)kCopyWords, c.words[k] - i0);
+  if (n == kCopyWords && (((uintptr_t)src | (uintptr_t)dst) & 15u) == 0) {
+    const uint4* s4 = reinterpret_cast<const uint4*>(src);
+    uint4* d4 = reinterpret_cast<uint4*>(dst);
+    uint4 x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = s4[q * kBlock + threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d4[q * kBlock + threadIdx.x] = x[q];
+    return;
+  }
+  for (int q = threadIdx.x; q < n; q += kBlock) dst[q] = src[q];
+}
+
+// ---------------------------------------------------------------------------
 // exclusive scan of u32 with u64 accumulation
 // ---------------------------------------------------------------------------
 constexpr int kScanItems = 16;
@@ -2106,6 +2135,14 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s
   unsigned g = grid_for(n, kBlock);
   if (g > 8192) g = 8192;
   hipLaunchKernelGGL(fill_u32_kernel, dim3(g), dim3(kBlock), 0, s, p, value, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_arrays(CopyArrays c, hipStream_t s) {
+  c.block_start[0] = 0;
+  for (int k = 0; k < kCopyArrays; ++k) c.block_start[k + 1] = c.block_start[k] + grid_for(c.words[k], kCopyWords);
+  if (c.block_start[kCopyArrays] == 0) return hipSuccess;
+  hipLaunchKernelGGL(copy_arrays_kernel, dim3(c.block_start[kCopyArrays]), dim3(kBlock), 0, s, c);
   return hipGetLastError();
 }
 
