@@ -349,6 +349,29 @@ ldni_status ldni_node_words(int32_t w, uint64_t *n_words);
 ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], float r, float eps,
                         void *hip_stream, ldni_result **out);
 
+/*
+ * ldni_boolean_begin / ldni_offset_begin / ldni_pending_finish -- the Boolean
+ * operation and the offset above with buffers of the caller's.  The first half
+ * writes offsets (device u32 [w*w + 1] per image, 16-byte aligned), waits for
+ * the sizes and returns them (max_layers: most samples of a pixel; one image for a
+ * Boolean operation, three for an offset).  ldni_pending_finish writes the samples
+ * (device arrays of n_samples per image; the first entries of the three for a
+ * Boolean operation) on the same stream and waits for them: LDNI_ERR_DEVICE if the
+ * write pass disagreed with the count pass.  The inputs must stay as they are until
+ * it returns; it releases the pending call either way.  One that is not finished
+ * must be released with ldni_pending_free (NULL-safe).
+ */
+typedef struct ldni_pending ldni_pending;
+ldni_status ldni_boolean_begin(const ldni_axis_view *a, const ldni_axis_view *b, int32_t op, float eps,
+                               uint32_t *offsets, void *hip_stream, ldni_pending **pending,
+                               uint64_t *n_samples, uint32_t *max_layers);
+ldni_status ldni_offset_begin(const ldni_axis_view views[3], const float bbox[6], float r, float eps,
+                              uint32_t *const offsets[3], void *hip_stream, ldni_pending **pending,
+                              uint64_t n_samples[3], uint32_t max_layers[3]);
+ldni_status ldni_pending_finish(ldni_pending *pending, float *const depth[3], float *const normal[3],
+                                int32_t *const tri[3]);
+void ldni_pending_free(ldni_pending *pending);
+
 /* Largest per-pixel count of each axis of a plan (after begin). */
 ldni_status ldni_plan_max_layers(const ldni_plan *plan, uint32_t max_layers[3]);
 

@@ -352,12 +352,45 @@ def ldni_boolean(a: LDNI, b: LDNI, op, eps: float = 1e-5, stream=None) -> Result
 
 
 def boolean(a: LDNI, b: LDNI, op, eps: float = 1e-5) -> LDNI:
-    """``ldni_boolean`` with the result copied into new torch tensors."""
-    r = ldni_boolean(a, b, op, eps)
+    """``ldni_boolean`` with the result in new torch tensors."""
+    if isinstance(op, str):
+        op = BOOLEAN_OPS[op]
+    dev = a.depth.device
+    va, vb = _view(a), _view(b)
+    if int(a.axis) not in (0, 1, 2):
+        return ldni_boolean(a, b, op, eps)  # (refused there)
+    offs = _new_offsets(va.w, dev)
+    pending, n, ml = ctypes.c_void_p(), (ctypes.c_uint64 * 3)(), (ctypes.c_uint32 * 3)()
+    _lib.check(_lib.lib().ldni_boolean_begin(ctypes.byref(va), ctypes.byref(vb), int(op), float(eps),
+                                             offs.data_ptr(), _stream(dev), ctypes.byref(pending), n, ml))
+    return _finish_pending(pending, n, ml, [a.axis], [offs], va.w, dev)[a.axis]
+
+
+def _new_offsets(w: int, device):
+    """Room for w * w + 1 offsets (none for a w that the library refuses)."""
+    return _torch().empty(w * w + 1 if 1 <= w <= 16384 else 0, dtype=_torch().int32, device=device)
+
+
+def _finish_pending(pending, n, max_layers, axes, offsets, w, device) -> Dict[int, LDNI]:
+    """Write pass of a pending Boolean operation or offset into new tensors;
+    the k-th of ``axes`` is the library's k-th image."""
+    torch = _torch()
+    out = {}
+    ptrs = [(ctypes.c_void_p * 3)() for _ in range(3)]
     try:
-        return _copy_view(r.view(a.axis), a.axis, a.depth.device)
-    finally:
-        r.free()
+        for k, a in enumerate(axes):
+            l = LDNI(a, int(w), int(max_layers[k]), offsets[k],
+                     torch.empty(n[k], dtype=torch.float32, device=device),
+                     torch.empty((n[k], 3), dtype=torch.float32, device=device),
+                     torch.empty(n[k], dtype=torch.int32, device=device))
+            out[a] = l
+            for p, t in zip(ptrs, (l.depth, l.normal, l.tri)):
+                p[k] = t.data_ptr()
+    except BaseException:
+        _lib.lib().ldni_pending_free(pending)
+        raise
+    _lib.check(_lib.lib().ldni_pending_finish(pending, *ptrs))
+    return out
 
 
 def node_words(w: int) -> int:
@@ -409,13 +442,16 @@ def ldni_offset(ldnis, bbox, r: float, eps: float = 1e-5) -> Result:
 
 
 def offset(ldnis, bbox, r: float, eps: float = 1e-5) -> Dict[int, LDNI]:
-    """``ldni_offset`` with the three axes copied into new torch tensors."""
+    """``ldni_offset`` with the three axes in new torch tensors."""
     dev = ldnis[0].depth.device
-    res = ldni_offset(ldnis, bbox, r, eps)
-    try:
-        return {a: _copy_view(res.view(a), a, dev) for a in range(3)}
-    finally:
-        res.free()
+    views = (_lib.AxisView * 3)(*[_view(ldnis[a]) for a in range(3)])
+    bb = (ctypes.c_float * 6)(*[float(x) for x in bbox])
+    offs = [_new_offsets(views[0].w, dev) for _ in range(3)]
+    optr = (ctypes.c_void_p * 3)(*[o.data_ptr() for o in offs])
+    pending, n, ml = ctypes.c_void_p(), (ctypes.c_uint64 * 3)(), (ctypes.c_uint32 * 3)()
+    _lib.check(_lib.lib().ldni_offset_begin(views, bb, float(r), float(eps), optr, _stream(dev),
+                                            ctypes.byref(pending), n, ml))
+    return _finish_pending(pending, n, ml, range(3), offs, views[0].w, dev)
 
 
 def _copy_view(v: _lib.AxisView, axis: int, device) -> LDNI:

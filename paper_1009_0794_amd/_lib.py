@@ -113,6 +113,17 @@ def lib():
     L.ldni_offset.argtypes = [ctypes.POINTER(AxisView), ctypes.POINTER(ctypes.c_float), ctypes.c_float,
                               ctypes.c_float, vp, ctypes.POINTER(vp)]
     L.ldni_offset.restype = st
+    pu32, pu64, pf = ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64), ctypes.c_float
+    L.ldni_boolean_begin.argtypes = [ctypes.POINTER(AxisView), ctypes.POINTER(AxisView), i32, pf, vp, vp,
+                                     ctypes.POINTER(vp), pu64, pu32]
+    L.ldni_boolean_begin.restype = st
+    L.ldni_offset_begin.argtypes = [ctypes.POINTER(AxisView), ctypes.POINTER(pf), pf, pf, ctypes.POINTER(vp), vp,
+                                    ctypes.POINTER(vp), pu64, pu32]
+    L.ldni_offset_begin.restype = st
+    L.ldni_pending_finish.argtypes = [vp, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp)]
+    L.ldni_pending_finish.restype = st
+    L.ldni_pending_free.argtypes = [vp]
+    L.ldni_pending_free.restype = None
     L.ldni_profile_enable.argtypes = [ctypes.c_int]
     L.ldni_profile_enable.restype = st
     L.ldni_profile_read.argtypes = [ctypes.POINTER(KernelStat), i32, ctypes.POINTER(i32)]
@@ -135,4 +146,5 @@ def exported_symbols():
             "ldni_profile_enable", "ldni_profile_read", "ldni_backward", "ldni_batch_create",
             "ldni_batch_run", "ldni_batch_axis", "ldni_batch_free", "ldni_sample_batch",
             "ldni_boolean", "ldni_sample_finish_rgb8", "ldni_classify_nodes", "ldni_node_words",
-            "ldni_offset", "ldni_backward_noalloc", "ldni_axis_copy"]
+            "ldni_offset", "ldni_backward_noalloc", "ldni_axis_copy",
+            "ldni_boolean_begin", "ldni_offset_begin", "ldni_pending_finish", "ldni_pending_free"]

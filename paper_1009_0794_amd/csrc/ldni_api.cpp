@@ -378,6 +378,20 @@ struct ldni_plan {
   uint32_t max_layers[3] = {0, 0, 0};
 };
 
+// A Boolean operation or an offset between its count pass and its write pass.
+struct ldni_pending {
+  hipStream_t stream = nullptr;
+  bool offset = false;  // which of the two argument blocks holds
+  BooleanArgs b{};
+  OffsetArgs o{};
+  void* ws = nullptr;
+  size_t ws_bytes = 0;
+  void* list = nullptr;  // an offset's ray lists
+  size_t list_bytes = 0;
+  uint64_t n[3] = {0, 0, 0};
+  uint32_t max_layers[3] = {0, 0, 0};
+};
+
 struct ldni_result {
   hipStream_t stream = nullptr;
   void* offsets_buf = nullptr;
@@ -458,6 +472,49 @@ ldni_status settle_later(ldni_result* r, FailWord* f, hipStream_t s) {
   return st;
 }
 
+void release_pending(ldni_pending* p) {
+  if (!p) return;
+  cache_put(p->list, p->list_bytes, p->stream);
+  cache_put(p->ws, p->ws_bytes, p->stream);
+  delete p;
+}
+
+// The write pass into the caller's arrays (an image per axis of an offset; the
+// first of a Boolean operation); the pending call is released.  With owner,
+// the result checks the pass's status when it is first read; without, the call
+// waits for it here.
+ldni_status finish_pending(ldni_pending* p, float* const depth[3], float* const normal[3], int32_t* const tri[3],
+                           ldni_result* owner) {
+  for (int d = 0; d < (p->offset ? 3 : 1); ++d) {
+    if (p->n[d] > 0 && (!depth[d] || !normal[d] || !tri[d])) {
+      release_pending(p);
+      return fail(LDNI_ERR_INVALID_ARG, "NULL output buffer for an axis with samples");
+    }
+    (p->offset ? p->o.out_depth[d] : p->b.out_depth) = depth[d];
+    (p->offset ? p->o.out_normal[d] : p->b.out_normal) = normal[d];
+    (p->offset ? p->o.out_tri[d] : p->b.out_tri) = tri[d];
+  }
+  FailWord word;
+  if (!fail_word(&word, owner == nullptr)) {
+    release_pending(p);
+    return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
+  }
+  (p->offset ? p->o.host_fail : p->b.host_fail) = word.host;
+  const hipError_t e =
+      p->offset ? timed("offset_write", p->stream, [&] { return launch_offset_rays(p->o, true, p->stream); })
+                : timed("boolean_write", p->stream, [&] { return launch_boolean(p->b, true, p->stream); });
+  ldni_status st = LDNI_OK;
+  if (e != hipSuccess) {
+    st = hip_fail(e, "write kernel");
+    (void)hipStreamSynchronize(p->stream);  // (the word is not reused under kernels that did start)
+    drop_fail_word(&word);
+  } else {
+    st = settle_later(owner, &word, p->stream);
+  }
+  release_pending(p);
+  return st;
+}
+
 // The result's status, waiting for its write pass if that is still running.
 ldni_status settle(ldni_result* r) {
   if (r->pending) {
@@ -468,6 +525,55 @@ ldni_status settle(ldni_result* r) {
     r->verdict = e != hipSuccess ? hip_fail(e, "waiting for the write pass") : write_verdict(bits);
   }
   return r->verdict;
+}
+
+// A result with its offsets buffer.
+ldni_status new_result(size_t offsets_bytes, hipStream_t stream, ldni_result** out) {
+  int device = 0;
+  HIP_TRY(hipGetDevice(&device), "hipGetDevice");
+  prepare_pool(device);
+  ldni_result* r = new (std::nothrow) ldni_result();
+  if (!r) return fail(LDNI_ERR_OUT_OF_MEMORY, "result");
+  std::memset(r->view, 0, sizeof(r->view));
+  r->stream = stream;
+  const hipError_t e = cache_get(&r->offsets_buf, offsets_bytes, stream, &r->offsets_bytes);
+  if (e != hipSuccess) {
+    r->offsets_buf = nullptr;
+    ldni_free(r);
+    return hip_fail(e, "offsets allocation");
+  }
+  *out = r;
+  return LDNI_OK;
+}
+
+// The write pass of a pending call into sample buffers of the result's, with
+// the n_axes views (all but w and offsets).
+ldni_status finish_result(ldni_pending* p, int n_axes, ldni_result* r, ldni_axis_view* views) {
+  float *depth[3] = {}, *normal[3] = {};
+  int32_t* tri[3] = {};
+  size_t at[3][3], total = 0;
+  for (int d = 0; d < n_axes; ++d) {
+    at[d][0] = total;
+    at[d][1] = align_up(at[d][0] + sizeof(float) * p->n[d]);
+    at[d][2] = align_up(at[d][1] + 3 * sizeof(float) * p->n[d]);
+    total = align_up(at[d][2] + sizeof(int32_t) * p->n[d]);
+  }
+  const hipError_t e = cache_get(&r->samples_buf, std::max<size_t>(total, 256), p->stream, &r->samples_bytes);
+  if (e != hipSuccess) {
+    r->samples_buf = nullptr;
+    release_pending(p);
+    return hip_fail(e, "sample allocation");
+  }
+  char* sb = static_cast<char*>(r->samples_buf);
+  for (int d = 0; d < n_axes; ++d) {
+    ldni_axis_view& v = views[d];
+    v.n_samples = p->n[d];
+    v.max_layers = p->max_layers[d];
+    v.depth = depth[d] = reinterpret_cast<float*>(sb + at[d][0]);
+    v.normal = normal[d] = reinterpret_cast<float*>(sb + at[d][1]);
+    v.tri = tri[d] = reinterpret_cast<int32_t*>(sb + at[d][2]);
+  }
+  return finish_pending(p, depth, normal, tri, r);
 }
 
 }  // namespace
@@ -1159,13 +1265,9 @@ ldni_status ldni_trim(void) {
   return ok ? LDNI_OK : fail(LDNI_ERR_DEVICE, "releasing cached buffers");
 }
 
-ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32_t op, float eps,
-                         int32_t axis, void* hip_stream, ldni_result** out) {
-  if (out) *out = nullptr;
-  if (!out || !a || !b) return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+static ldni_status boolean_check(const ldni_axis_view* a, const ldni_axis_view* b, int32_t op, float eps) {
   if (op < LDNI_UNION || op > LDNI_DIFFERENCE)
     return fail(LDNI_ERR_INVALID_ARG, "op must be LDNI_UNION, LDNI_INTERSECTION or LDNI_DIFFERENCE");
-  if (axis < 0 || axis > 2) return fail(LDNI_ERR_INVALID_ARG, "axis must be 0, 1 or 2");
   if (!(eps >= 0.0f) || !std::isfinite(eps)) return fail(LDNI_ERR_INVALID_ARG, "eps must be finite and >= 0");
   if (a->w < 1 || a->w > 16384 || a->w != b->w)
     return fail(LDNI_ERR_INVALID_ARG, "both views need the same w in [1, 16384]");
@@ -1175,43 +1277,36 @@ ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32
       return fail(LDNI_ERR_INVALID_ARG, "NULL sample array of a view with samples");
     if (v->n_samples > 0xffffffffull) return fail(LDNI_ERR_INVALID_ARG, "a view has 2^32 or more samples");
   }
-  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  return LDNI_OK;
+}
+
+// The count pass of checked arguments, into offsets [w * w + 1].
+static ldni_status boolean_count(const ldni_axis_view* a, const ldni_axis_view* b, int32_t op, float eps,
+                                 uint32_t* offsets, hipStream_t stream, ldni_pending** out) {
   int device = 0;
   HIP_TRY(hipGetDevice(&device), "hipGetDevice");
   prepare_pool(device);
   uint32_t* rb = pinned_readback();
   if (!rb) return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
-  const int32_t w = a->w;
-  const int64_t npix = (int64_t)w * w;
-
-  ldni_result* r = new (std::nothrow) ldni_result();
-  if (!r) return fail(LDNI_ERR_OUT_OF_MEMORY, "result");
-  std::memset(r->view, 0, sizeof(r->view));
-  r->stream = stream;
-  hipError_t e = cache_get(&r->offsets_buf, sizeof(uint32_t) * (size_t)(npix + 1), stream, &r->offsets_bytes);
-  if (e != hipSuccess) {
-    r->offsets_buf = nullptr;
-    ldni_free(r);
-    return hip_fail(e, "offsets allocation");
-  }
-  // workspace: status words ([0] status, [1] max layers), scan partials, the
-  // kept samples' sources (one word per input sample)
-  void* ws = nullptr;
-  size_t ws_bytes = 0;
-  const size_t o_refs = align_up(256 + scan_scratch_bytes(npix, 1));
-  e = cache_get(&ws, o_refs + sizeof(uint32_t) * (size_t)(a->n_samples + b->n_samples), stream, &ws_bytes);
-  if (e != hipSuccess) {
-    ldni_free(r);
-    return hip_fail(e, "workspace allocation");
-  }
+  const int64_t npix = (int64_t)a->w * a->w;
+  ldni_pending* p = new (std::nothrow) ldni_pending();
+  if (!p) return fail(LDNI_ERR_OUT_OF_MEMORY, "result");
+  p->stream = stream;
   auto bail = [&](ldni_status st) {
-    cache_put(ws, ws_bytes, stream);
-    ldni_free(r);
+    release_pending(p);
     return st;
   };
-  uint32_t* status = static_cast<uint32_t*>(ws);
-  uint32_t* counts = static_cast<uint32_t*>(r->offsets_buf);
-  BooleanArgs g{};
+  // workspace: status words ([0] status, [1] max layers), scan partials, the
+  // kept samples' sources (one word per input sample)
+  const size_t o_refs = align_up(256 + scan_scratch_bytes(npix, 1));
+  hipError_t e = cache_get(&p->ws, o_refs + sizeof(uint32_t) * (size_t)(a->n_samples + b->n_samples), stream,
+                           &p->ws_bytes);
+  if (e != hipSuccess) {
+    p->ws = nullptr;
+    return bail(hip_fail(e, "workspace allocation"));
+  }
+  uint32_t* status = static_cast<uint32_t*>(p->ws);
+  BooleanArgs& g = p->b;
   g.a = AxisArrays{a->n_samples, static_cast<const uint32_t*>(a->offsets), static_cast<const float*>(a->depth),
                    static_cast<const float*>(a->normal), static_cast<const int32_t*>(a->tri)};
   g.b = AxisArrays{b->n_samples, static_cast<const uint32_t*>(b->offsets), static_cast<const float*>(b->depth),
@@ -1219,8 +1314,8 @@ ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32
   g.npix = npix;
   g.op = op;
   g.eps = (double)eps;
-  g.counts = counts;
-  g.refs = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + o_refs);
+  g.counts = offsets;
+  g.refs = reinterpret_cast<uint32_t*>(static_cast<char*>(p->ws) + o_refs);
   g.status = status;
 #define BSTEP(expr, what)                                  \
   do {                                                     \
@@ -1230,46 +1325,56 @@ ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32
   BSTEP(launch_fill_u32(status, 0u, 64, stream), "fill");
   BSTEP(timed("boolean_count", stream, [&] { return launch_boolean(g, false, stream); }), "Boolean count kernel");
   BSTEP(timed("boolean_scan", stream, [&] {
-          return launch_scan(counts, counts, npix, static_cast<char*>(ws) + 256, status, stream, status + 1, rb);
+          return launch_scan(offsets, offsets, npix, static_cast<char*>(p->ws) + 256, status, stream, status + 1, rb);
         }), "Boolean scan");
   BSTEP(hipStreamSynchronize(stream), "synchronise");
+#undef BSTEP
   if (rb[0] & kStatusMismatch) return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
   if (rb[3]) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples"));
-  const uint64_t n = rb[1];
-  const uint32_t max_layers = rb[2];
-  size_t o_normal = align_up(sizeof(float) * n), o_tri = align_up(o_normal + sizeof(float) * 3 * n);
-  e = cache_get(&r->samples_buf, o_tri + sizeof(int32_t) * n, stream, &r->samples_bytes);
-  if (e != hipSuccess) {
-    r->samples_buf = nullptr;
-    return bail(hip_fail(e, "sample allocation"));
+  p->n[0] = rb[1];
+  p->max_layers[0] = rb[2];
+  *out = p;
+  return LDNI_OK;
+}
+
+ldni_status ldni_boolean(const ldni_axis_view* a, const ldni_axis_view* b, int32_t op, float eps,
+                         int32_t axis, void* hip_stream, ldni_result** out) {
+  if (out) *out = nullptr;
+  if (!out || !a || !b) return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+  if (axis < 0 || axis > 2) return fail(LDNI_ERR_INVALID_ARG, "axis must be 0, 1 or 2");
+  ldni_status st = boolean_check(a, b, op, eps);
+  if (st != LDNI_OK) return st;
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const int64_t npix = (int64_t)a->w * a->w;
+  ldni_result* r = nullptr;
+  st = new_result(sizeof(uint32_t) * (size_t)(npix + 1), stream, &r);
+  if (st != LDNI_OK) return st;
+  ldni_pending* p = nullptr;
+  st = boolean_count(a, b, op, eps, static_cast<uint32_t*>(r->offsets_buf), stream, &p);
+  if (st == LDNI_OK) st = finish_result(p, 1, r, &r->view[axis]);
+  if (st != LDNI_OK) {
+    ldni_free(r);
+    return st;
   }
-  char* sb = static_cast<char*>(r->samples_buf);
-  g.out_depth = reinterpret_cast<float*>(sb);
-  g.out_normal = reinterpret_cast<float*>(sb + o_normal);
-  g.out_tri = reinterpret_cast<int32_t*>(sb + o_tri);
-  FailWord word;
-  if (!fail_word(&word, false)) return bail(fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer"));
-  g.host_fail = word.host;
-  e = timed("boolean_write", stream, [&] { return launch_boolean(g, true, stream); });
-  if (e != hipSuccess) {
-    drop_fail_word(&word);
-    return bail(hip_fail(e, "Boolean write kernel"));
-  }
-  {
-    const ldni_status st = settle_later(r, &word, stream);
-    if (st != LDNI_OK) return bail(st);
-  }
-#undef BSTEP
-  cache_put(ws, ws_bytes, stream);
-  ldni_axis_view& v = r->view[axis];
-  v.w = w;
-  v.max_layers = max_layers;
-  v.n_samples = n;
-  v.offsets = counts;
-  v.depth = g.out_depth;
-  v.normal = g.out_normal;
-  v.tri = g.out_tri;
+  r->view[axis].w = a->w;
+  r->view[axis].offsets = static_cast<uint32_t*>(r->offsets_buf);
   *out = r;
+  return LDNI_OK;
+}
+
+ldni_status ldni_boolean_begin(const ldni_axis_view* a, const ldni_axis_view* b, int32_t op, float eps,
+                               uint32_t* offsets, void* hip_stream, ldni_pending** pending, uint64_t* n_samples,
+                               uint32_t* max_layers) {
+  if (pending) *pending = nullptr;
+  if (!pending || !a || !b || !n_samples || !max_layers) return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+  ldni_status st = boolean_check(a, b, op, eps);
+  if (st != LDNI_OK) return st;
+  if (!offsets || reinterpret_cast<uintptr_t>(offsets) % 16 != 0)
+    return fail(LDNI_ERR_INVALID_ARG, "offsets buffer NULL or not 16-byte aligned");
+  st = boolean_count(a, b, op, eps, offsets, static_cast<hipStream_t>(hip_stream), pending);
+  if (st != LDNI_OK) return st;
+  *n_samples = (*pending)->n[0];
+  *max_layers = (*pending)->max_layers[0];
   return LDNI_OK;
 }
 
@@ -1378,10 +1483,7 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
   return st;
 }
 
-ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], float r, float eps, void* hip_stream,
-                        ldni_result** out) {
-  if (out) *out = nullptr;
-  if (!out || !views || !bbox) return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+static ldni_status offset_check(const ldni_axis_view views[3], const float bbox[6], float r, float eps) {
   if (!std::isfinite(r) || r == 0.0f) return fail(LDNI_ERR_INVALID_ARG, "r must be finite and not zero");
   if (!(eps >= 0.0f) || !std::isfinite(eps)) return fail(LDNI_ERR_INVALID_ARG, "eps must be finite and >= 0");
   const int32_t w = views[0].w;
@@ -1400,7 +1502,14 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
     n_total += v.n_samples;
   }
   if (n_total >= kMaxSpheres) return fail(LDNI_ERR_INVALID_ARG, "2^30 or more samples in the three views");
-  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  return LDNI_OK;
+}
+
+// The count pass of checked arguments, into offsets [w * w + 1] per axis.
+static ldni_status offset_count(const ldni_axis_view views[3], const float bbox[6], float r, float eps,
+                                uint32_t* const offsets[3], hipStream_t stream, ldni_pending** out) {
+  const int32_t w = views[0].w;
+  const uint64_t n_total = views[0].n_samples + views[1].n_samples + views[2].n_samples;
   int device = 0;
   HIP_TRY(hipGetDevice(&device), "hipGetDevice");
   prepare_pool(device);
@@ -1409,16 +1518,14 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   const int64_t npix = (int64_t)w * w;
   const int64_t n_rays = 3 * npix;
 
-  ldni_result* res = new (std::nothrow) ldni_result();
-  if (!res) return fail(LDNI_ERR_OUT_OF_MEMORY, "result");
-  std::memset(res->view, 0, sizeof(res->view));
-  res->stream = stream;
-  hipError_t e = cache_get(&res->offsets_buf, 3 * sizeof(uint32_t) * (size_t)(npix + 1), stream, &res->offsets_bytes);
-  if (e != hipSuccess) {
-    res->offsets_buf = nullptr;
-    ldni_free(res);
-    return hip_fail(e, "offsets allocation");
-  }
+  ldni_pending* pend = new (std::nothrow) ldni_pending();
+  if (!pend) return fail(LDNI_ERR_OUT_OF_MEMORY, "result");
+  pend->stream = stream;
+  pend->offset = true;
+  auto bail = [&](ldni_status st) {
+    release_pending(pend);
+    return st;
+  };
   // workspace: status, ray counts and cursors, ray starts, scan scratch, centres
   const size_t o_count = 256;
   const size_t o_cursor = align_up(o_count + sizeof(uint32_t) * (size_t)n_rays);
@@ -1437,23 +1544,13 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   const bool use_saved = n_saved >= 16;
   const size_t saved_bytes = use_saved ? sizeof(uint64_t) * n_saved * 3 * (size_t)npix : 0;
   const size_t o_saved = align_up(o_centres + 3 * sizeof(double) * (size_t)std::max<uint64_t>(n_total, 1));
-  void* ws = nullptr;
-  size_t ws_bytes = 0;
-  e = cache_get(&ws, o_saved + (use_saved ? saved_bytes : 0), stream, &ws_bytes);
+  hipError_t e = cache_get(&pend->ws, o_saved + (use_saved ? saved_bytes : 0), stream, &pend->ws_bytes);
   if (e != hipSuccess) {
-    ldni_free(res);
-    return hip_fail(e, "workspace allocation");
+    pend->ws = nullptr;
+    return bail(hip_fail(e, "workspace allocation"));
   }
-  void* list = nullptr;
-  size_t list_bytes = 0;
-  auto bail = [&](ldni_status st) {
-    cache_put(list, list_bytes, stream);
-    cache_put(ws, ws_bytes, stream);
-    ldni_free(res);
-    return st;
-  };
-  char* wb = static_cast<char*>(ws);
-  OffsetArgs g{};
+  char* wb = static_cast<char*>(pend->ws);
+  OffsetArgs& g = pend->o;
   uint64_t base = 0;
   for (int d = 0; d < 3; ++d) {
     const ldni_axis_view& v = views[d];
@@ -1467,7 +1564,7 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
                          std::ldexp((double)w + 1.0, -48)) + 1e-6;
     g.base[d] = base;
     base += v.n_samples;
-    g.counts[d] = static_cast<uint32_t*>(res->offsets_buf) + d * (npix + 1);
+    g.counts[d] = offsets[d];
     g.out_offsets[d] = g.counts[d];
   }
   g.w = w;
@@ -1523,12 +1620,12 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   if (rb[0] & kStatusMismatch)
     return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
   if (rb[0] & kStatusOverflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more sphere hits on the rays"));
-  e = cache_get(&list, sizeof(uint32_t) * (size_t)std::max<uint32_t>(rb[1], 1), stream, &list_bytes);
+  e = cache_get(&pend->list, sizeof(uint32_t) * (size_t)std::max<uint32_t>(rb[1], 1), stream, &pend->list_bytes);
   if (e != hipSuccess) {
-    list = nullptr;
+    pend->list = nullptr;
     return bail(hip_fail(e, "ray list allocation"));
   }
-  g.list = static_cast<uint32_t*>(list);
+  g.list = static_cast<uint32_t*>(pend->list);
   OSTEP(timed("offset_bin", stream, [&] { return launch_offset_bin(g, true, stream); }), "binning kernel");
   OSTEP(timed("offset_count", stream, [&] { return launch_offset_rays(g, false, stream); }), "offset count kernel");
   uint32_t* max_slot = g.status + 8;  // [8..10]: largest count per axis
@@ -1538,55 +1635,74 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
   if (rb[0] & kStatusMismatch)
     return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
   if (rb[3] | rb[6] | rb[9]) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples on one axis"));
-  const uint64_t n_out[3] = {rb[1], rb[4], rb[7]};
-  const uint32_t max_layers[3] = {rb[2], rb[5], rb[8]};
-  size_t o_ax[3][3], total = 0;
-  for (int d = 0; d < 3; ++d) {
-    o_ax[d][0] = total;
-    o_ax[d][1] = align_up(o_ax[d][0] + sizeof(float) * n_out[d]);
-    o_ax[d][2] = align_up(o_ax[d][1] + 3 * sizeof(float) * n_out[d]);
-    total = align_up(o_ax[d][2] + sizeof(int32_t) * n_out[d]);
-  }
-  e = cache_get(&res->samples_buf, std::max<size_t>(total, 256), stream, &res->samples_bytes);
-  if (e != hipSuccess) {
-    res->samples_buf = nullptr;
-    return bail(hip_fail(e, "sample allocation"));
-  }
-  char* sb = static_cast<char*>(res->samples_buf);
-  for (int d = 0; d < 3; ++d) {
-    g.out_depth[d] = reinterpret_cast<float*>(sb + o_ax[d][0]);
-    g.out_normal[d] = reinterpret_cast<float*>(sb + o_ax[d][1]);
-    g.out_tri[d] = reinterpret_cast<int32_t*>(sb + o_ax[d][2]);
-  }
-  FailWord word;
-  if (!fail_word(&word, false)) return bail(fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer"));
-  g.host_fail = word.host;
-  g.most_out = std::max(max_layers[0], std::max(max_layers[1], max_layers[2]));
-  e = timed("offset_write", stream, [&] { return launch_offset_rays(g, true, stream); });
-  if (e != hipSuccess) {
-    drop_fail_word(&word);
-    return bail(hip_fail(e, "offset write kernel"));
-  }
-  {
-    const ldni_status st = settle_later(res, &word, stream);
-    if (st != LDNI_OK) return bail(st);
-  }
 #undef OSTEP
-  cache_put(list, list_bytes, stream);
-  cache_put(ws, ws_bytes, stream);
   for (int d = 0; d < 3; ++d) {
-    ldni_axis_view& v = res->view[d];
-    v.w = w;
-    v.max_layers = max_layers[d];
-    v.n_samples = n_out[d];
-    v.offsets = g.counts[d];
-    v.depth = g.out_depth[d];
-    v.normal = g.out_normal[d];
-    v.tri = g.out_tri[d];
+    pend->n[d] = rb[1 + 3 * d];
+    pend->max_layers[d] = rb[2 + 3 * d];
+    g.most_out = std::max(g.most_out, pend->max_layers[d]);
+  }
+  *out = pend;
+  return LDNI_OK;
+}
+
+ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], float r, float eps, void* hip_stream,
+                        ldni_result** out) {
+  if (out) *out = nullptr;
+  if (!out || !views || !bbox) return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+  ldni_status st = offset_check(views, bbox, r, eps);
+  if (st != LDNI_OK) return st;
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const int64_t n_off = (int64_t)views[0].w * views[0].w + 1;
+  ldni_result* res = nullptr;
+  st = new_result(3 * sizeof(uint32_t) * (size_t)n_off, stream, &res);
+  if (st != LDNI_OK) return st;
+  uint32_t* offsets[3];
+  for (int d = 0; d < 3; ++d) offsets[d] = static_cast<uint32_t*>(res->offsets_buf) + d * n_off;
+  ldni_pending* p = nullptr;
+  st = offset_count(views, bbox, r, eps, offsets, stream, &p);
+  if (st == LDNI_OK) st = finish_result(p, 3, res, res->view);
+  if (st != LDNI_OK) {
+    ldni_free(res);
+    return st;
+  }
+  for (int d = 0; d < 3; ++d) {
+    res->view[d].w = views[0].w;
+    res->view[d].offsets = offsets[d];
   }
   *out = res;
   return LDNI_OK;
 }
+
+ldni_status ldni_offset_begin(const ldni_axis_view views[3], const float bbox[6], float r, float eps,
+                              uint32_t* const offsets[3], void* hip_stream, ldni_pending** pending,
+                              uint64_t n_samples[3], uint32_t max_layers[3]) {
+  if (pending) *pending = nullptr;
+  if (!pending || !views || !bbox || !offsets || !n_samples || !max_layers)
+    return fail(LDNI_ERR_INVALID_ARG, "NULL argument");
+  ldni_status st = offset_check(views, bbox, r, eps);
+  if (st != LDNI_OK) return st;
+  for (int d = 0; d < 3; ++d)
+    if (!offsets[d] || reinterpret_cast<uintptr_t>(offsets[d]) % 16 != 0)
+      return fail(LDNI_ERR_INVALID_ARG, "offsets buffer NULL or not 16-byte aligned");
+  st = offset_count(views, bbox, r, eps, offsets, static_cast<hipStream_t>(hip_stream), pending);
+  if (st != LDNI_OK) return st;
+  for (int d = 0; d < 3; ++d) {
+    n_samples[d] = (*pending)->n[d];
+    max_layers[d] = (*pending)->max_layers[d];
+  }
+  return LDNI_OK;
+}
+
+ldni_status ldni_pending_finish(ldni_pending* p, float* const depth[3], float* const normal[3], int32_t* const tri[3]) {
+  if (!p) return fail(LDNI_ERR_INVALID_ARG, "NULL pending call");
+  if (!depth || !normal || !tri) {
+    release_pending(p);
+    return fail(LDNI_ERR_INVALID_ARG, "NULL output array");
+  }
+  return finish_pending(p, depth, normal, tri, nullptr);
+}
+
+void ldni_pending_free(ldni_pending* p) { release_pending(p); }
 
 void ldni_free(ldni_result* r) {
   if (!r) return;
