@@ -795,9 +795,10 @@ __global__ __launch_bounds__(kOffBlock) void offset_write_kernel(OffsetArgs g) {
 }
 
 // 64-bit words of LDS for a wave's cells: enter and leave keys (n + 4 each), a
-// bit and a 16-bit list entry per cell.
+// bit and a 16-bit list entry per cell.  They hold the sorted events afterwards.
 __host__ __device__ constexpr int union_words(int n_cells) {
-  return 2 * (n_cells + 4) + (n_cells / 64 + 1) + (n_cells / 4 + 1);
+  const int cells = 2 * (n_cells + 4) + (n_cells / 64 + 1) + (n_cells / 4 + 1);
+  return cells > kUnionEvents ? cells : kUnionEvents;
 }
 
 // The count pass of a ray, one wave: most of the spheres that hit a ray lie
@@ -819,19 +820,21 @@ __host__ __device__ constexpr int union_words(int n_cells) {
 // reading them all, more by wave_sort) and swept as in sweep_ray.  A ray with
 // more than kUnionEvents of them is listed for offset_rest_kernel.
 // Bound by the latency of a ray's dependent loads (starts, list, centres) at the
-// 20 waves that its LDS leaves a CU.  On the flower, r = 2 pixels: 0.27 ms at w =
-// 256 and 0.075 at 128, where sweeping every ray over all its events (one LDS
-// sort of up to 1,024 keys a window) took 1.60 and 0.74 ms.  Cells of three
-// quarters of a radius: 0.31 and 0.096 (more short chords); 128 or 256 events:
-// 0.27 / 0.36 ms at w = 256, but with 128 one polar ray of w = 128 is left to the
-// sweep, 0.02 ms.
-__global__ __launch_bounds__(kOffBlock) void offset_union_kernel(OffsetArgs g) {
+// 25 waves that its LDS leaves a CU; a workgroup is one wave, so that a ray's LDS
+// is free for the next as soon as it is done.  On the flower, r = 2 pixels: 0.196
+// ms at w = 256 and 0.058 at 128 (with LDS of its own for the sorted events, 20
+// waves: 0.24 and 0.063; with four rays a workgroup as well: 0.27 and 0.077), where
+// sweeping every ray over all its events (one LDS sort of up to 1,024 keys a
+// window) took 1.60 and 0.74 ms.  With four rays a workgroup, cells of three
+// quarters of a radius took 0.31 and 0.096 (more short chords), and 256 events
+// 0.36 ms at w = 256; with 160 one polar ray of w = 128 is left to the sweep,
+// 0.02 ms.
+__global__ __launch_bounds__(64) void offset_union_kernel(OffsetArgs g) {
   extern __shared__ uint64_t s_union[];
-  __shared__ uint64_t s_buf[kOffWaves][2][kUnionEvents];
-  __shared__ uint32_t s_rbit[kOffWaves][kUnionEvents / 32 + 2];
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ uint64_t buf[kUnionEvents];
+  __shared__ uint32_t s_rbit[kUnionEvents / 32 + 2];
   const uint32_t lane = lane_id();
-  const int64_t ray = ray_of_wave(g, (int64_t)blockIdx.x * kOffWaves + wv);
+  const int64_t ray = ray_of_wave(g, blockIdx.x);
   if (ray < 0) return;
   const int64_t npix = (int64_t)g.w * g.w;
   const int a = (int)(ray / npix);
@@ -857,13 +860,12 @@ __global__ __launch_bounds__(kOffBlock) void offset_union_kernel(OffsetArgs g) {
   const double r2 = g.r * g.r, lo_a = g.lo[a];
   // cell c at index c + 1, empty cells before the first and behind the last
   const int n_cells = g.n_cells, n_slots = n_cells + 4;
-  uint64_t* enter = s_union + (size_t)wv * union_words(n_cells);
+  uint64_t* enter = s_union;
   uint64_t* leave = enter + n_slots;
   uint64_t* taken = leave + n_slots;                             // bit c: cell c holds a chord
   uint16_t* cells = reinterpret_cast<uint16_t*>(taken + n_cells / 64 + 1);  // the cells that do, in any order
   uint32_t n_taken = 0;
-  uint64_t* buf = s_buf[wv][0];
-  uint64_t* buf2 = s_buf[wv][1];
+  uint64_t* buf2 = s_union;  // (once the cells are no longer needed)
   uint32_t n = 0;  // keys in buf
   const uint64_t below = (1ull << lane) - 1ull;
 
@@ -1110,7 +1112,7 @@ __global__ __launch_bounds__(kOffBlock) void offset_union_kernel(OffsetArgs g) {
     wave_sort(buf, n);
   }
   // the sweep of sweep_ray, over one window that holds all events
-  uint32_t* rbit = s_rbit[wv];
+  uint32_t* rbit = s_rbit;
   int carry_h = 0, carry_s = 0, carry_first = -1;
   uint32_t n_emit = 0;
   for (uint32_t c0 = 0; c0 < n; c0 += 64) {
@@ -1225,8 +1227,8 @@ hipError_t launch_offset_rays(const OffsetArgs& g, bool write, hipStream_t s) {
   } else if (write) {
     hipLaunchKernelGGL(offset_ray_kernel<true>, grid, dim3(kOffBlock), 0, s, g);
   } else if (g.n_cells > 0) {
-    const size_t lds = kOffWaves * sizeof(uint64_t) * (size_t)union_words(g.n_cells);
-    hipLaunchKernelGGL(offset_union_kernel, grid, dim3(kOffBlock), lds, s, g);
+    const size_t lds = sizeof(uint64_t) * (size_t)union_words(g.n_cells);
+    hipLaunchKernelGGL(offset_union_kernel, dim3((unsigned)rays), dim3(64), lds, s, g);
     hipLaunchKernelGGL(offset_rest_kernel<false>, rest, dim3(kOffBlock), 0, s, g);
   } else {
     hipLaunchKernelGGL(offset_ray_kernel<false>, grid, dim3(kOffBlock), 0, s, g);
