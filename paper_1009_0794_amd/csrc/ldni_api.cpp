@@ -783,6 +783,7 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
       im.stage_qs = p->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(p->stage) + stage_cap)
                              : nullptr;
       im.stage_cap = p->stage ? stage_cap : 0;
+      im.stage_stream = stage_streams(im.stage_cap);
       im.stage_layers = stage_layers;
     }
   }
@@ -1810,6 +1811,7 @@ hipError_t batch_upload(ldni_batch* b) {
     im.stage_qs = b->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(b->stage) + b->stage_cap)
                            : nullptr;
     im.stage_cap = b->stage ? b->stage_cap : 0;
+    im.stage_stream = stage_streams(im.stage_cap);
     im.stage_layers = b->stage_layers;
   }
   b->dev.items = b->items;

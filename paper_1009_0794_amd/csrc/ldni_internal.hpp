@@ -81,6 +81,7 @@ struct Image {
   uint64_t* stage_key;               // (depth key, triangle) of each hit
   uint32_t* stage_qs;                // tile pixel | (slot within the pixel << 10)
   uint64_t stage_cap;                // entries in the buffer (below 2^32 - 1)
+  int32_t stage_stream;              // staged hits by-pass the caches (stage_streams)
   uint32_t stage_layers;             // a tile's region holds at most this many entries per pixel
   // [n_tiles + 1] the tile's candidates, each triangle's rounded up to whole
   // 4-entry groups (counted by setup); the region scan turns them into the
@@ -172,6 +173,12 @@ int max_place_items_per_tile(int tile_pix, uint32_t stage_layers);
 // Entries per pixel a tile may reserve in the staging buffer: the deepest
 // pixel seen, rounded up to a power of two, within [64, 1024].
 uint32_t stage_layers_for(uint32_t max_layers_seen);
+// Whether a staging buffer of that many entries (12 bytes each) is written and
+// read with non-temporal accesses: one larger than the 256 MiB Infinity Cache
+// would only push other data out of it (scene64 at w = 2048, 0.5 GB of hits:
+// sampling pass 398 -> 375 us, place pass 390 -> 370 us), while the place pass
+// finds smaller ones there (flower at w = 512, 19 MB: 37.5 us, 39.3 around it).
+constexpr bool stage_streams(uint64_t entries) { return entries > (256ull << 20) / 12; }
 int place_stage_cap(int tile_pix);
 // Pixel counts -> offsets of all images and the place items (16 bytes each, in
 // launch order), from the bands that the sampling pass left; to pinned host

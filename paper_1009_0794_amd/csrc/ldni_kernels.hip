@@ -951,8 +951,17 @@ __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t*
         const uint32_t pos = first + i;
         if (pos < region_size) {
           const size_t at = (size_t)region_first + pos;
-          im.stage_key[at] = sample_key(dep, __float_as_int(z.w));
-          im.stage_qs[at] = (uint32_t)q | (slot << 10);
+          const uint64_t key = sample_key(dep, __float_as_int(z.w));
+          const uint32_t qs = (uint32_t)q | (slot << 10);
+          if (im.stage_stream) {
+            asm volatile("");  // (without the two the compiler makes plain stores of both)
+            __builtin_nontemporal_store(key, &im.stage_key[at]);
+            __builtin_nontemporal_store(qs, &im.stage_qs[at]);
+            asm volatile("");
+          } else {
+            im.stage_key[at] = key;
+            im.stage_qs[at] = qs;
+          }
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1259,11 +1268,21 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
     // pixel offsets are scanned, so the two reads overlap.
     uint32_t rq[kPer];
     uint64_t rk[kPer];
+    if (im.stage_stream) {
+      asm volatile("");  // (without it the compiler makes plain loads of both)
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const uint32_t i = threadIdx.x + u * kBlock;
-      rq[u] = i < hits ? qs[i] : 0xffffffffu;
-      rk[u] = i < hits ? keys[i] : 0;
+      for (int u = 0; u < kPer; ++u) {
+        const uint32_t i = threadIdx.x + u * kBlock;
+        rq[u] = i < hits ? __builtin_nontemporal_load(qs + i) : 0xffffffffu;
+        rk[u] = i < hits ? __builtin_nontemporal_load(keys + i) : 0;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const uint32_t i = threadIdx.x + u * kBlock;
+        rq[u] = i < hits ? qs[i] : 0xffffffffu;
+        rk[u] = i < hits ? keys[i] : 0;
+      }
     }
     tile_prefix(im, g, s_off, s_pre, nullptr, s_wave);
     if (s_pre[npix] != hits) {  // staging and counts disagree
