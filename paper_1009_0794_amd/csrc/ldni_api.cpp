@@ -1606,17 +1606,12 @@ static ldni_status offset_count(const ldni_axis_view views[3], const float bbox[
     hipError_t e_ = (expr);                                \
     if (e_ != hipSuccess) return bail(hip_fail(e_, what)); \
   } while (0)
-  OSTEP(launch_fill_u32(g.status, 0u, 64, stream), "fill");
-  OSTEP(launch_fill_u32(g.ray_count, 0u, 2 * n_rays + 64, stream), "fill");  // counts and cursors
+  OSTEP(launch_fill_u32(g.status, 0u, 64 + 2 * n_rays + 64, stream), "fill");  // status, counts and cursors
   OSTEP(timed("offset_centres", stream, [&] { return launch_offset_centres(g, stream); }), "centre kernel");
   OSTEP(timed("offset_bin", stream, [&] { return launch_offset_bin(g, false, stream); }), "binning kernel");
   OSTEP(launch_scan(g.ray_count, g.ray_start, n_rays, scr, g.status, stream), "ray list scan");
-  OSTEP(launch_offset_deep(g, stream), "deep ray list");
-  {
-    const uint32_t* src[3] = {g.status, g.ray_start + n_rays, g.status + 16};
-    OSTEP(launch_gather(src, 3, rb, stream), "readback");
-    OSTEP(hipStreamSynchronize(stream), "synchronise");
-  }
+  OSTEP(launch_offset_deep(g, rb, stream), "deep ray list");
+  OSTEP(hipStreamSynchronize(stream), "synchronise");
   g.n_deep = std::min<uint32_t>(rb[2], (uint32_t)n_rays);
   if (rb[0] & kStatusMismatch)
     return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));

@@ -400,13 +400,10 @@ struct OffsetArgs {
 };
 hipError_t launch_offset_centres(const OffsetArgs& g, hipStream_t s);
 hipError_t launch_offset_bin(const OffsetArgs& g, bool scatter, hipStream_t s);
-// the list of deep rays (after the ray-list scan)
-hipError_t launch_offset_deep(const OffsetArgs& g, hipStream_t s);
+// the list of deep rays (after the ray-list scan); status, list total and number
+// of deep rays to the pinned words host[0..2]
+hipError_t launch_offset_deep(const OffsetArgs& g, uint32_t* host, hipStream_t s);
 hipError_t launch_offset_rays(const OffsetArgs& g, bool write, hipStream_t s);
-
-// Copies n <= kMaxGather scattered device words to pinned host memory.
-constexpr int kMaxGather = 32;
-hipError_t launch_gather(const uint32_t* const* src, int n, uint32_t* host_dst, hipStream_t s);
 
 // Exclusive scan of n u32 values into out[0..n] (out[n] = total).  Totals of
 // 2^32 or more raise kStatusOverflow.  scratch: scan_scratch_bytes(n, 1).

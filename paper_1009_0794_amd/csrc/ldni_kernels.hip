@@ -2118,18 +2118,6 @@ __global__ void scan_report_kernel(ScanSegs sg, const uint32_t* status, uint32_t
   __threadfence_system();
 }
 
-struct GatherArgs {
-  const uint32_t* src[kMaxGather];
-  int n;
-};
-
-// Copies a few scattered device words into pinned host memory in one launch.
-__global__ void gather_kernel(GatherArgs g, uint32_t* dst) {
-  const int k = threadIdx.x;
-  if (k < g.n) dst[k] = *g.src[k];
-  __threadfence_system();
-}
-
 inline unsigned grid_for(int64_t n, int per_block) {
   return (unsigned)((n + per_block - 1) / per_block);
 }
@@ -2261,15 +2249,6 @@ hipError_t launch_place(const ImageSet& set, const void* items, uint32_t n_items
     hipLaunchKernelGGL(walk_kernel<kSmallTilePix>, dim3(wgrid), dim3(kBlock), 0, s, set, list, n_walk, counter);
   else
     hipLaunchKernelGGL(walk_kernel<kMaxTilePix>, dim3(wgrid), dim3(kBlock), 0, s, set, list, n_walk, counter);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather(const uint32_t* const* src, int n, uint32_t* host_dst, hipStream_t s) {
-  if (n < 0 || n > kMaxGather) return hipErrorInvalidValue;
-  GatherArgs g;
-  g.n = n;
-  for (int k = 0; k < kMaxGather; ++k) g.src[k] = k < n ? src[k] : nullptr;
-  hipLaunchKernelGGL(gather_kernel, dim3(1), dim3(64), 0, s, g, host_dst);
   return hipGetLastError();
 }
 

@@ -1194,24 +1194,31 @@ hipError_t launch_offset_bin(const OffsetArgs& g, bool scatter, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kOffBlock) void offset_deep_kernel(OffsetArgs g) {
-  const int64_t ray = (int64_t)blockIdx.x * kOffBlock + threadIdx.x;
-  if (ray >= 3 * (int64_t)g.w * g.w) return;
+// The workgroup that is done last reports the status, the lists' total and the
+// number of deep rays to pinned memory (the atomics have returned by then).
+__global__ __launch_bounds__(kOffBlock) void offset_deep_kernel(OffsetArgs g, uint32_t* host) {
+  const int64_t ray = (int64_t)blockIdx.x * kOffBlock + threadIdx.x, n_rays = 3 * (int64_t)g.w * g.w;
   // (one atomic per wave: they queue at the counter)
-  const bool deep = g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep;
+  const bool deep = ray < n_rays && g.ray_start[ray + 1] - g.ray_start[ray] > (uint32_t)kOffsetDeep;
   const uint64_t m = __ballot(deep);
-  if (m == 0) return;
-  uint32_t at = 0;
-  const int lead = __ffsll((unsigned long long)m) - 1;
-  if ((int)lane_id() == lead) at = atomicAdd(&g.status[16], (uint32_t)__popcll(m));
-  at = (uint32_t)__shfl((int)at, lead, 64);
-  if (deep) g.deep[at + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = (uint32_t)ray;
+  if (m != 0) {
+    uint32_t at = 0;
+    const int lead = __ffsll((unsigned long long)m) - 1;
+    if ((int)lane_id() == lead) at = atomicAdd(&g.status[16], (uint32_t)__popcll(m));
+    at = (uint32_t)__shfl((int)at, lead, 64);
+    if (deep) g.deep[at + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = (uint32_t)ray;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0 || atomicAdd(&g.status[19], 1u) + 1u != gridDim.x) return;
+  host[0] = g.status[0];
+  host[1] = g.ray_start[n_rays];
+  host[2] = atomicAdd(&g.status[16], 0u);
 }
 
-hipError_t launch_offset_deep(const OffsetArgs& g, hipStream_t s) {
+hipError_t launch_offset_deep(const OffsetArgs& g, uint32_t* host, hipStream_t s) {
   const int64_t rays = 3 * (int64_t)g.w * g.w;
   hipLaunchKernelGGL(offset_deep_kernel, dim3((unsigned)((rays + kOffBlock - 1) / kOffBlock)), dim3(kOffBlock), 0, s,
-                     g);
+                     g, host);
   return hipGetLastError();
 }
 
