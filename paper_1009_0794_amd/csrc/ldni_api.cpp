@@ -1323,14 +1323,18 @@ static ldni_status boolean_count(const ldni_axis_view* a, const ldni_axis_view* 
     hipError_t e_ = (expr);                                \
     if (e_ != hipSuccess) return bail(hip_fail(e_, what)); \
   } while (0)
-  BSTEP(launch_fill_u32(status, 0u, 64, stream), "fill");
+  // (the count pass clears the status words and raises a mismatch in the pinned
+  // word: a launch less)
+  *static_cast<volatile uint32_t*>(rb + kFailReadback) = 0u;
+  g.host_fail = rb + kFailReadback;
   BSTEP(timed("boolean_count", stream, [&] { return launch_boolean(g, false, stream); }), "Boolean count kernel");
   BSTEP(timed("boolean_scan", stream, [&] {
           return launch_scan(offsets, offsets, npix, static_cast<char*>(p->ws) + 256, status, stream, status + 1, rb);
         }), "Boolean scan");
   BSTEP(hipStreamSynchronize(stream), "synchronise");
 #undef BSTEP
-  if (rb[0] & kStatusMismatch) return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
+  if (*static_cast<volatile uint32_t*>(rb + kFailReadback) & kStatusMismatch)
+    return bail(fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples"));
   if (rb[3]) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more result samples"));
   p->n[0] = rb[1];
   p->max_layers[0] = rb[2];

@@ -155,7 +155,8 @@ __device__ __forceinline__ WavePixels wave_pixels(const BooleanArgs& g, int64_t 
     w.b0 = g.b.offsets[w.p];
     w.b1 = g.b.offsets[w.p + 1];
     ok = w.a0 <= w.a1 && w.a1 <= g.a.n && w.b0 <= w.b1 && w.b1 <= g.b.n;
-    if (!ok && count_pass) atomicOr(g.status, kStatusMismatch);
+    if (!ok && count_pass)
+      __hip_atomic_store(g.host_fail, (uint32_t)kStatusMismatch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   // consecutive pixels must also chain (each starts where the previous ends)
   const uint32_t pa1 = (uint32_t)__shfl_up((int)w.a1, 1, 64), pb1 = (uint32_t)__shfl_up((int)w.b1, 1, 64);
@@ -243,6 +244,8 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g
   // samples of the pixels before it
   __shared__ uint32_t s_first[kBoolWaves][3][66];
   __shared__ uint32_t s_n[kBoolWaves][64];         // kept samples of the pixels
+  // the status words of the launches behind this one (it has none itself)
+  if (blockIdx.x == 0 && threadIdx.x < 64) g.status[threadIdx.x] = 0u;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t p0 = ((int64_t)blockIdx.x * kBoolWaves + wave) * 64;
   if (p0 >= g.npix) return;

@@ -308,8 +308,8 @@ struct BooleanArgs {
                           // scanned in place into the result offsets (write pass)
   uint32_t* refs;         // [a.n + b.n]: sources of the kept samples (count pass), per
                           // 64 pixels from the first's samples in a and b on
-  uint32_t* status;       // kStatusMismatch: offsets of an input out of order
-  uint32_t* host_fail;    // pinned word for the write pass's status bits
+  uint32_t* status;       // 64 words, cleared by the count pass
+  uint32_t* host_fail;    // pinned word for a pass's status bits
   float* out_depth;
   float* out_normal;
   int32_t* out_tri;
