@@ -131,7 +131,8 @@ ldni_status ldni_result_axis(const ldni_result *r, int axis, ldni_axis_view *vie
 
 /* Copies the arrays of a view (offsets [w*w + 1], depth [n], normal [n][3] or
  * the codes [n] of a view with 8-bit normals, tri [n]) into device memory of the
- * caller's, behind the work on hip_stream.  LDNI_ERR_INVALID_ARG for NULL
+ * caller's, behind the work on hip_stream, with a kernel there: the view, the
+ * memory and the stream are of one device.  LDNI_ERR_INVALID_ARG for NULL
  * offsets, or NULL sample arrays where the view has samples. */
 ldni_status ldni_axis_copy(const ldni_axis_view *view, uint32_t *offsets, float *depth, void *normal,
                            int32_t *tri, void *hip_stream);

@@ -294,10 +294,12 @@ def sample_diff(verts, tris, bbox, w: int, axes="xyz") -> Dict[int, LDNI]:
 # ---- library-owned results -------------------------------------------------
 
 class Result:
-    """Owner of an ``ldni_result``; frees it when collected."""
+    """Owner of an ``ldni_result``; frees it when collected.  ``device``: where
+    its memory lives (None: on the device asked for in ``to_torch``)."""
 
-    def __init__(self, handle: ctypes.c_void_p):
+    def __init__(self, handle: ctypes.c_void_p, device=None):
         self.handle = handle
+        self.device = device
 
     def view(self, axis: int) -> _lib.AxisView:
         v = _lib.AxisView()
@@ -305,10 +307,19 @@ class Result:
         return v
 
     def to_torch(self, axis: int, device=None) -> LDNI:
-        """Copy one axis into new torch tensors (device-to-device)."""
+        """Copy one axis into new torch tensors (device-to-device; on another
+        device than the result's, a copy there is moved by torch)."""
         torch = _torch()
         dev = torch.device("cuda") if device is None else torch.device(device)
-        return _copy_view(self.view(axis), axis, dev)
+        if dev.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {dev}")
+        here = torch.cuda.current_device()
+        own = dev if self.device is None else self.device
+        if _index(own, here) == _index(dev, here):
+            return _copy_view(self.view(axis), axis, dev)
+        l = _copy_view(self.view(axis), axis, own)
+        l.offsets, l.depth, l.normal, l.tri = (t.to(dev) for t in (l.offsets, l.depth, l.normal, l.tri))
+        return l
 
     def free(self):
         if self.handle:
@@ -331,7 +342,7 @@ def ldni_sample(verts, tris, bbox, w: int, axes="xyz", stream=None, normals="f32
     _lib.check(_lib.lib().ldni_sample(verts.data_ptr(), verts.shape[0], tris.data_ptr(),
                                       tris.shape[0], _bbox(bbox), int(w),
                                       axis_mask(axes) | _normals_flag(normals), st, ctypes.byref(h)))
-    return Result(h)
+    return Result(h, verts.device)
 
 
 BOOLEAN_OPS = {"union": 0, "intersection": 1, "difference": 2}
@@ -348,7 +359,7 @@ def ldni_boolean(a: LDNI, b: LDNI, op, eps: float = 1e-5, stream=None) -> Result
     va, vb = _view(a), _view(b)
     _lib.check(_lib.lib().ldni_boolean(ctypes.byref(va), ctypes.byref(vb), int(op), float(eps),
                                        int(a.axis), st, ctypes.byref(h)))
-    return Result(h)
+    return Result(h, a.depth.device)
 
 
 def boolean(a: LDNI, b: LDNI, op, eps: float = 1e-5) -> LDNI:
@@ -438,7 +449,7 @@ def ldni_offset(ldnis, bbox, r: float, eps: float = 1e-5) -> Result:
     h = ctypes.c_void_p()
     _lib.check(_lib.lib().ldni_offset(views, bb, float(r), float(eps), _stream(L[0].depth.device),
                                       ctypes.byref(h)))
-    return Result(h)
+    return Result(h, L[0].depth.device)
 
 
 def offset(ldnis, bbox, r: float, eps: float = 1e-5) -> Dict[int, LDNI]:
@@ -454,10 +465,20 @@ def offset(ldnis, bbox, r: float, eps: float = 1e-5) -> Dict[int, LDNI]:
     return _finish_pending(pending, n, ml, range(3), offs, views[0].w, dev)
 
 
+def _index(device, here: int) -> int:
+    """A device's number (``here``: the current one's)."""
+    return here if device.index is None else device.index
+
+
 def _copy_view(v: _lib.AxisView, axis: int, device) -> LDNI:
-    """Copies a view into new tensors; a view with 8-bit normal codes gives
+    """Copies a view into new tensors on its own device (the copy is a kernel,
+    which reads no other GPU's memory); a view with 8-bit normal codes gives
     an int32 [n] ``normal`` tensor of the codes."""
     torch = _torch()
+    here = torch.cuda.current_device()
+    if _index(device, here) != here:
+        with torch.cuda.device(device):
+            return _copy_view(v, axis, device)
     n = int(v.n_samples)
     rgb8 = bool(v.normal_rgb8)
     out = LDNI(axis, int(v.w), int(v.max_layers),
