@@ -358,7 +358,12 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g
       }
       for (uint32_t i = (uint32_t)lane; i < all; i += 64) mark[i] = 0xffffu;
       wave_sync();
-      bool odd = false;  // a list that is not ascending, or a NaN
+      // Lists that do not ascend, or hold a NaN, are merged one sample after
+      // the other.  There the search for a part's beginning may end elsewhere
+      // than the part before it does: a lane checks the samples it merges, and
+      // the parts must join, so that no sample is left unchecked between them.
+      bool odd = false;
+      uint32_t join = ~0u, end = 0;  // next sample of A where the part begins (inside a pixel), and where it ends
       const uint32_t m1 = min((lane + 1) * per, all);
       uint32_t m = (uint32_t)lane * per;
       if (m < m1) {
@@ -387,6 +392,7 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g
           prev = b_in == 0 || (lo > 0 && pb < pa) ? pa : pb;
           i += lo;
           j += b_in;
+          if (d0 > 0) join = i;
         }
         float za = i < ea ? s[i] : 0.0f, zb = j < eb ? s[j] : 0.0f;
         // a group that began before this part is not ours: it is merged, not marked
@@ -410,6 +416,7 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g
           zb = of_a ? zb : z;
           state ^= of_a ? 2u : 1u;
           ++m;
+          if (m == m1) end = i;
           head = !((i < ea && za == d) || (j < eb && zb == d));
           if (head) {  // the group is complete
             const bool is = (holds >> state) & 1u;
@@ -430,6 +437,8 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g
           }
         }
       }
+      const uint32_t next = (uint32_t)__shfl_down((int)join, 1, 64);
+      odd |= lane < 63 && next != ~0u && next != end;
       wave_sync();
       if (__ballot(odd) != 0) {
         serial(first, bt.last, s + (w.a0 - bt.A0), s + bt.nA + (w.b0 - bt.B0));
