@@ -1442,10 +1442,12 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
     g.h[d] = ((double)bbox[3 + d] - (double)bbox[d]) / (double)w;
     g.inv_h[d] = 1.0 / g.h[d];
     // a node depth f32(f32(lo + (t + 0.5) h) - lo) is within 2^-24 (|lo| +
-    // 2 (w + 1) h) (1 + 2^-20) of (t + 0.5) h, and the estimate of t carries
-    // a float64 error of a few 2^-53 (w + 1); twice their sum, in pixels
-    g.slack[d] = 2.0 * (std::ldexp(std::fabs(g.lo[d]) + 2.0 * ((double)w + 1.0) * g.h[d], -24) *
-                            (1.0 + std::ldexp(1.0, -20)) / g.h[d] +
+    // 2 (w + 1) h) (1 + 2^-20) + 2^-149 (two roundings, subnormal ones
+    // included) of (t + 0.5) h, and the estimate of t carries a float64 error
+    // of a few 2^-53 (w + 1); twice their sum, in pixels
+    g.slack[d] = 2.0 * ((std::ldexp(std::fabs(g.lo[d]) + 2.0 * ((double)w + 1.0) * g.h[d], -24) *
+                             (1.0 + std::ldexp(1.0, -20)) +
+                         std::ldexp(1.0, -149)) / g.h[d] +
                         std::ldexp((double)w + 1.0, -48));
     // fma(s, f32(1 / h), -0.5) in float32 adds at most (2 w + 3) 2^-24 within
     // the grid; twice that, rounded up
@@ -1562,10 +1564,11 @@ static ldni_status offset_count(const ldni_axis_view views[3], const float bbox[
     g.in[d] = AxisArrays{v.n_samples, v.offsets, v.depth, v.normal, v.tri};
     g.lo[d] = (double)bbox[d];
     g.h[d] = ((double)bbox[3 + d] - (double)bbox[d]) / (double)w;
-    // a centre f32(lo + (i + 0.5) h) is within 2^-24 (|lo| + (w + 1) h) of
-    // the real value, and the index estimate carries a float64 error of a
-    // few 2^-53 (w + 1); twice their sum in pixels, plus a millionth
-    g.margin[d] = 2.0 * (std::ldexp(std::fabs(g.lo[d]) + ((double)w + 1.0) * g.h[d], -24) / g.h[d] +
+    // a centre f32(lo + (i + 0.5) h) is within 2^-24 (|lo| + (w + 1) h) +
+    // 2^-150 of the real value, and the index estimate carries a float64 error
+    // of a few 2^-53 (w + 1); twice their sum in pixels, plus a millionth
+    g.margin[d] = 2.0 * ((std::ldexp(std::fabs(g.lo[d]) + ((double)w + 1.0) * g.h[d], -24) + std::ldexp(1.0, -150)) /
+                             g.h[d] +
                          std::ldexp((double)w + 1.0, -48)) + 1e-6;
     g.base[d] = base;
     base += v.n_samples;

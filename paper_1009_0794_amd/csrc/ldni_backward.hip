@@ -364,9 +364,10 @@ hipError_t launch_backward(const BackwardArgs& args, hipStream_t s) {
     im.lo_v = args.bbox[im.v];
     im.h_v = (args.bbox[3 + im.v] - args.bbox[im.v]) / (double)args.w;
     // a centre's float32 rounding (2^-24 of its magnitude, at most
-    // |lo| + (w + 1) h) plus the float64 rounding of the estimate, doubled
+    // |lo| + (w + 1) h, or 2^-150 if subnormal) plus the float64 rounding of
+    // the estimate, doubled
     const auto margin = [&](double lo, double h) {
-      return 2.0 * (std::ldexp(std::fabs(lo) + ((double)args.w + 1.0) * h, -24) / h +
+      return 2.0 * ((std::ldexp(std::fabs(lo) + ((double)args.w + 1.0) * h, -24) + std::ldexp(1.0, -150)) / h +
                     std::ldexp((double)args.w + 1.0, -48)) + 1e-6;
     };
     im.margin_u = margin(im.lo_u, im.h_u);
