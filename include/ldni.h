@@ -164,8 +164,8 @@ ldni_status ldni_trim(void);
  * [n][3] and tri i32 [n] into caller device buffers of at least n_samples[a]
  * elements, waits for the write pass (LDNI_ERR_DEVICE if it disagreed with
  * the count pass), and releases the plan whether or not it succeeds.  A plan not
- * finished must be released with ldni_plan_free.  verts/tris must stay
- * unchanged until finish returns.
+ * finished must be released with ldni_plan_free.  verts, tris and offsets must
+ * stay unchanged until finish returns.
  */
 ldni_status ldni_sample_begin(const float *verts, int64_t n_verts, const int32_t *tris,
                               int64_t n_tris, const float bbox[6], int32_t w, uint32_t axis_mask,
@@ -358,8 +358,10 @@ ldni_status ldni_offset(const ldni_axis_view views[3], const float bbox[6], floa
  * Boolean operation, three for an offset).  ldni_pending_finish writes the samples
  * (device arrays of n_samples per image; the first entries of the three for a
  * Boolean operation) on the same stream and waits for them: LDNI_ERR_DEVICE if the
- * write pass disagreed with the count pass.  The inputs must stay as they are until
- * it returns; it releases the pending call either way.  One that is not finished
+ * write pass disagreed with the count pass.  The inputs and the offsets must stay as
+ * they are until it returns (the write pass takes the samples' places from the
+ * offsets; if they changed it fails, or writes other samples, but nothing beyond
+ * n_samples); it releases the pending call either way.  One that is not finished
  * must be released with ldni_pending_free (NULL-safe).
  */
 typedef struct ldni_pending ldni_pending;

@@ -490,6 +490,7 @@ ldni_status finish_pending(ldni_pending* p, float* const depth[3], float* const 
       release_pending(p);
       return fail(LDNI_ERR_INVALID_ARG, "NULL output buffer for an axis with samples");
     }
+    (p->offset ? p->o.n_out[d] : p->b.n_out) = p->n[d];
     (p->offset ? p->o.out_depth[d] : p->b.out_depth) = depth[d];
     (p->offset ? p->o.out_normal[d] : p->b.out_normal) = normal[d];
     (p->offset ? p->o.out_tri[d] : p->b.out_tri) = tri[d];

@@ -493,7 +493,12 @@ __global__ void __launch_bounds__(kBoolBlock) boolean_write_kernel(BooleanArgs g
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int64_t p0 = ((int64_t)blockIdx.x * kBoolWaves + wave) * 64;
   if (p0 >= g.npix) return;
-  const uint32_t R0 = g.counts[p0], R1 = g.counts[min(p0 + 64, g.npix)];
+  const uint32_t R0 = g.counts[p0], end = g.counts[min(p0 + 64, g.npix)];
+  // (offsets in the caller's memory that changed between the passes do not lead
+  // beyond the outputs, nor leave any of them unwritten unnoticed)
+  const uint32_t R1 = (uint32_t)min((uint64_t)end, g.n_out);
+  if (R0 > R1 || end != R1 || (p0 == 0 && R0 != 0) || (p0 + 64 >= g.npix && end != g.n_out))
+    raise_mismatch(g.status, g.host_fail);
   const uint64_t a0 = g.a.offsets[p0], b0 = g.b.offsets[p0];
   const uint64_t n_refs = g.a.n + g.b.n;
   for (uint32_t k0 = R0; k0 < R1; k0 += 4 * 64) {

@@ -310,6 +310,7 @@ struct BooleanArgs {
                           // 64 pixels from the first's samples in a and b on
   uint32_t* status;       // 64 words, cleared by the count pass
   uint32_t* host_fail;    // pinned word for a pass's status bits
+  uint64_t n_out;         // result samples (write pass): the size of the outputs
   float* out_depth;
   float* out_normal;
   int32_t* out_tri;
@@ -382,7 +383,8 @@ struct OffsetArgs {
   int32_t* out_tri[3];
   uint64_t* saved;   // [3 * w * w][n_saved] kept end-point keys, or null (the write pass recomputes)
   uint32_t n_saved;  // end points kept per ray (at most kOffsetSavedMax)
-  uint32_t most_out; // the write pass: most end points of a ray
+  uint64_t n_out[3]; // the write pass: result samples per axis, the size of its outputs,
+  uint32_t most_out; // and most end points of a ray
   // rays with more than kOffsetDeep spheres, listed (any order) so that the
   // ray passes start them first; n_deep of them (known to the host before
   // the ray passes; status[16] counts them on the device)

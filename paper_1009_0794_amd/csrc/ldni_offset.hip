@@ -428,6 +428,14 @@ __device__ __forceinline__ void write_event(const OffsetArgs& g, int a, int64_t 
   }
 }
 
+// Whether the write pass may take [o0, o1) as the output slot of ray (a, p): the
+// offsets are in the caller's memory, and if they changed between the passes
+// they must not lead beyond the outputs, nor leave any of them unwritten
+// unnoticed.
+__device__ __forceinline__ bool slot_ok(const OffsetArgs& g, int a, int64_t p, uint32_t o0, uint32_t o1) {
+  return o0 <= o1 && o1 <= g.n_out[a] && (p > 0 || o0 == 0) && (p + 1 < (int64_t)g.w * g.w || o1 == g.n_out[a]);
+}
+
 // The per-ray pass: counts (kWrite false) or writes the ray's result.  The
 // ray's events are taken in windows of depth: a window collects the events
 // at or after its lower depth bound into a buffer of kOffsetBuf keys; when a
@@ -473,7 +481,12 @@ __device__ void sweep_ray(const OffsetArgs& g, int64_t ray, RayLds& lds) {
   uint32_t out = 0, cnt = 0;
   if (kWrite) {
     out = g.out_offsets[a][p];
-    cnt = g.out_offsets[a][p + 1] - out;
+    const uint32_t end = g.out_offsets[a][p + 1];
+    if (!slot_ok(g, a, p, out, end)) {
+      if (lane == 0) raise_mismatch(g.status, g.host_fail);
+      return;
+    }
+    cnt = end - out;
     if (cnt == 0) return;
   }
   const uint32_t o0 = H.offsets[p], o1 = H.offsets[p + 1];
@@ -765,12 +778,17 @@ __global__ __launch_bounds__(kOffBlock) void offset_write_kernel(OffsetArgs g) {
   const int a = (int)(group / groups), u = (a + 1) % 3, v = (a + 2) % 3;
   const int64_t p0 = (group - a * groups) * 64;
   const int n = (int)min((int64_t)64, npix - p0);
-  bool deep = false;
+  bool deep = false, bad = false;
   if ((int)lane < n) {
     const uint32_t o0 = g.out_offsets[a][p0 + lane], o1 = g.out_offsets[a][p0 + lane + 1];
     off[lane] = o0;
     if ((int)lane == n - 1) off[n] = o1;
     deep = o1 - o0 > g.n_saved;
+    bad = !slot_ok(g, a, p0 + lane, o0, o1) || (deep && g.most_out <= g.n_saved);  // (nothing takes the rest then)
+  }
+  if (__ballot(bad) != 0) {
+    if (lane == 0) raise_mismatch(g.status, g.host_fail);
+    return;
   }
   const uint64_t m = __ballot(deep);
   if (m != 0) {
@@ -789,8 +807,14 @@ __global__ __launch_bounds__(kOffBlock) void offset_write_kernel(OffsetArgs g) {
     }
     if (off[k + 1] - off[k] > g.n_saved) continue;
     const int64_t p = p0 + k;
-    write_event(g, a, p, centre_of(g, u, (int)(p % g.w)), centre_of(g, v, (int)(p / g.w)),
-                g.saved[(size_t)(a * npix + p) * g.n_saved + (q - off[k])], q);
+    const uint64_t key = g.saved[(size_t)(a * npix + p) * g.n_saved + (q - off[k])];
+    // (an end point that the count pass did not keep: the offsets changed)
+    const uint32_t from = (uint32_t)(key & 0x7fffffffu);
+    if ((key & kSphereOrder) ? from >> 1 >= g.n_spheres : (uint64_t)g.in[a].offsets[p] + from >= g.in[a].n) {
+      raise_mismatch(g.status, g.host_fail);
+      continue;
+    }
+    write_event(g, a, p, centre_of(g, u, (int)(p % g.w)), centre_of(g, v, (int)(p / g.w)), key, q);
   }
 }
 
