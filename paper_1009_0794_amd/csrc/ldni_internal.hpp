@@ -427,8 +427,7 @@ hipError_t launch_scan_segments(const uint32_t* const* in, uint32_t* const* out,
 // tile_cnt), and in the same launches candidate counts -> staging regions
 // (tile_region), each tile's count capped at region_cap and the prefix
 // saturating at 2^32 - 1 (n + 1 slots each).  The counts come from tile_pack
-// and tile_ovf when tile_pack is given, else from tile_cnt and tile_region
-// themselves (in place).  scratch: scan_scratch_bytes(n, 2).
+// and tile_ovf (n each, neither null).  scratch: scan_scratch_bytes(n, 2).
 hipError_t launch_tile_scan(const uint64_t* tile_pack, const uint32_t* tile_ovf, uint32_t* tile_cnt,
                             uint32_t* tile_region, int64_t n, uint32_t region_cap, void* scratch, uint32_t* status,
                             hipStream_t s);

@@ -2384,18 +2384,17 @@ hipError_t launch_scan_segments(const uint32_t* const* in, uint32_t* const* out,
 hipError_t launch_tile_scan(const uint64_t* tile_pack, const uint32_t* tile_ovf, uint32_t* tile_cnt,
                             uint32_t* tile_region, int64_t n, uint32_t region_cap, void* scratch, uint32_t* status,
                             hipStream_t s) {
+  if (!tile_pack || !tile_ovf) return hipErrorInvalidValue;
   if (n <= 0) {
     hipError_t e = launch_fill_u32(tile_cnt, 0u, 1, s);
     return e != hipSuccess ? e : launch_fill_u32(tile_region, 0u, 1, s);
   }
   ScanSegs sg{};
-  sg.in[0] = tile_cnt;
   sg.pack = tile_pack;
   sg.pack_add = tile_ovf;
   sg.out[0] = tile_cnt;
   sg.total[0] = tile_cnt + n;
   sg.cap[0] = 0xffffffffu;
-  sg.in[1] = tile_region;
   sg.out[1] = tile_region;
   sg.total[1] = tile_region + n;
   sg.cap[1] = region_cap;
