@@ -701,7 +701,10 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
     stage_cap &= ~(uint64_t)3;  // whole 4-entry groups: 16-byte aligned pixel/slot words
   }
   const size_t o_items = off;
-  const uint32_t items_cap = (uint32_t)place_items_cap(stage_cap, (uint64_t)n_all);
+  uint32_t items_cap = (uint32_t)place_items_cap(stage_cap, (uint64_t)n_all);
+  // test hook: a table for fewer items
+  if (const char* env = std::getenv("LDNI_PLACE_ITEMS"))
+    items_cap = (uint32_t)std::min<uint64_t>(items_cap, std::strtoull(env, nullptr, 10));
   off = align_up(off + 16 * (size_t)items_cap);
   const size_t o_scan = off;
   off = align_up(off + scan_scratch_bytes(n_all, 2));
@@ -865,7 +868,7 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
       for (int k = 0; k < nimg; ++k) ml = std::max(ml, rb[2 + 3 * k]);
       stage_seen_record(stage_key, StageSeen{demand, ml});
       p->n_walk = rb_more[2];
-      p->n_items = std::min(rb_more[3], items_cap);
+      p->n_items = rb_more[3];
     }
     if (n_tris > 0) {
       const double ratio = std::min(8.0, (double)need / ((double)n_tris * nimg) * 1.1);
@@ -884,6 +887,8 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
   bool overflow = (rb[0] & kStatusOverflow) != 0;
   for (int k = 0; k < nimg; ++k) overflow |= rb[3 + 3 * k] != 0;
   if (overflow) return bail(fail(LDNI_ERR_OVERFLOW, "2^32 or more samples on one axis"));
+  // (the kernel stores no item beyond the table: their samples would be missing)
+  if (p->n_items > items_cap) return bail(fail(LDNI_ERR_DEVICE, "more place items than their table holds"));
   for (int k = 0; k < nimg; ++k) {
     const int a = p->axis_of[k];
     p->n[a] = rb[1 + 3 * k];
