@@ -427,7 +427,9 @@ ldni_status ldni_batch_create(int32_t n_meshes, const ldni_mesh_desc *meshes, ui
 /* Replay the batch's graph on hip_stream and wait for it (one host
  * synchronisation); if the meshes now need larger tile lists or outputs,
  * the buffers grow, the graph is captured again and replayed.  Views from
- * before are invalid afterwards. */
+ * before are invalid afterwards.  Errors as ldni_sample; LDNI_ERR_DEVICE also
+ * when the write pass stored more or fewer samples of a pixel than the count
+ * pass counted (the results must then not be used). */
 ldni_status ldni_batch_run(ldni_batch *b, void *hip_stream);
 
 /* View of one mesh's axis (0..2) after the last run (empty for axes not in

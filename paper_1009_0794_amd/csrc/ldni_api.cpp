@@ -1776,6 +1776,8 @@ struct ldni_batch {
 
 namespace {
 
+constexpr size_t kBatchFail = 2;  // word of host_out in which the write passes raise their status bits
+
 void batch_release_graph(ldni_batch* b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
@@ -1821,6 +1823,7 @@ hipError_t batch_upload(ldni_batch* b) {
     im.stage_cap = b->stage ? b->stage_cap : 0;
     im.stage_stream = stage_streams(im.stage_cap);
     im.stage_layers = b->stage_layers;
+    im.host_fail = b->host_out + kBatchFail;
   }
   b->dev.items = b->items;
   hipError_t e = hipMemcpy(b->dev.images, b->images_h.data(), sizeof(Image) * b->n_img, hipMemcpyHostToDevice);
@@ -1842,6 +1845,8 @@ hipError_t batch_enqueue(ldni_batch* b, hipStream_t s) {
                      b->stage_layers * (uint32_t)(b->small ? 256 : 1024), b->scan_scratch, b->dev.status, s));
   Q(launch_batch_scatter(b->dev, b->tri_block_start.back(), s));
   Q(launch_batch_sample(b->dev, (uint32_t)b->total_tiles, (uint32_t)b->small_tiles, s));
+  // test hook: the first image's counts are lost, so that its write pass disagrees
+  if (env_fault("counts")) Q(launch_fill_u32(b->counts_arena, 0u, (int64_t)b->seg_start[1], s));
   Q(launch_batch_pixel_scan(b->dev, b->counts_arena, b->offsets_arena, (int64_t)b->total_slots,
                             b->scan_scratch, s));
   Q(launch_batch_finish_counts(b->dev, s));
@@ -1893,6 +1898,7 @@ ldni_status ldni_batch_run(ldni_batch* b, void* hip_stream) {
       if (e == hipSuccess) e = batch_capture(b);
       if (e != hipSuccess) return hip_fail(e, "batch graph capture");
     }
+    *static_cast<volatile uint32_t*>(b->host_out + kBatchFail) = 0u;
     HIP_TRY(hipGraphLaunch(b->exec, stream), "batch graph launch");
     HIP_TRY(hipStreamSynchronize(stream), "synchronise");
     const uint32_t* h = b->host_out;
@@ -1926,6 +1932,10 @@ ldni_status ldni_batch_run(ldni_batch* b, void* hip_stream) {
       if (st != LDNI_OK) return st;
       batch_release_graph(b);
       continue;
+    }
+    {  // (only now: every image had its lists and its place in the outputs)
+      const ldni_status st = write_verdict(*static_cast<volatile uint32_t*>(b->host_out + kBatchFail));
+      if (st != LDNI_OK) return st;
     }
     // Tiles that found no room in the staging buffer were walked again, so
     // the results stand; the buffer and the per-pixel cap grow for the next run.
