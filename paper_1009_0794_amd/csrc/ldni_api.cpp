@@ -1422,11 +1422,10 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
   prepare_pool(device);
   uint32_t* rb = pinned_readback();
   if (!rb) return fail(LDNI_ERR_OUT_OF_MEMORY, "pinned readback buffer");
-  // workspace: [0] status word, [128] the number of mixed bricks, [256..) the vote's
-  // partial totals; then per axis and brick its range, kind and start bits,
-  // and the three toggle lists
+  // workspace: the counters ([256..) the vote's partial totals); then per axis
+  // and brick its range, kind and start bits, and the three toggle lists
   const size_t nb = (size_t)(w + 31) / 32, bricks = 3 * nb * nb * nb;
-  const size_t o_range = align_up(256 + 16 * (size_t)kNodeSlots);
+  const size_t o_range = align_up(sizeof(uint32_t) * (size_t)kNodeCounters);
   const size_t o_kind = align_up(o_range + sizeof(uint2) * bricks);
   const size_t o_parity = align_up(o_kind + bricks);
   const size_t o_mixed = align_up(o_parity + 32 * sizeof(uint32_t) * bricks);
@@ -1464,8 +1463,10 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
   g.w = w;
   g.nb = (int32_t)nb;
   g.bits = bits;
-  g.status = reinterpret_cast<uint32_t*>(wb);
-  g.n_mixed = reinterpret_cast<uint32_t*>(wb + 128);
+  *static_cast<volatile uint32_t*>(rb + kFailReadback) = 0u;
+  g.host_fail = rb + kFailReadback;
+  g.n_mixed = reinterpret_cast<uint32_t*>(wb);
+  g.host = rb;
   g.partial = reinterpret_cast<uint64_t*>(wb + 256);
   g.range = reinterpret_cast<uint2*>(wb + o_range);
   g.kind = reinterpret_cast<uint8_t*>(wb + o_kind);
@@ -1477,17 +1478,15 @@ ldni_status ldni_classify_nodes(const ldni_axis_view views[3], const float bbox[
     hipError_t e_ = (expr);                     \
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
-    NSTEP(launch_fill_u32(g.status, 0u, 64 + 4 * (int64_t)kNodeSlots, stream), "fill");
     NSTEP(timed("node_bins", stream, [&] { return launch_node_bins(g, stream); }), "node binning kernel");
     NSTEP(timed("classify_nodes", stream, [&] { return launch_classify_nodes(g, stream); }), "classify kernel");
-    NSTEP(launch_node_stats(g, rb, stream), "node totals");
     NSTEP(hipStreamSynchronize(stream), "synchronise");
 #undef NSTEP
-    if (rb[0] & kStatusMismatch)
+    if (*static_cast<volatile uint32_t*>(rb + kFailReadback) & kStatusMismatch)
       return fail(LDNI_ERR_INVALID_ARG, "the offsets of an input view are not a prefix of its samples");
     if (stats) {
-      stats[0] = (uint64_t)rb[1] | ((uint64_t)rb[2] << 32);
-      stats[1] = (uint64_t)rb[3] | ((uint64_t)rb[4] << 32);
+      stats[0] = (uint64_t)rb[0] | ((uint64_t)rb[1] << 32);
+      stats[1] = (uint64_t)rb[2] | ((uint64_t)rb[3] << 32);
     }
     return LDNI_OK;
   };

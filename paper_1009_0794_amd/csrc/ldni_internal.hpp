@@ -324,7 +324,7 @@ hipError_t launch_boolean(const BooleanArgs& g, bool write, hipStream_t s);
 // pass sorts every axis's toggles by brick: toggles[a] (as
 // many entries as a's samples), and per axis and brick (axis * nb^3
 // + brick number) the range of the list, the kind of its start bits and,
-// where they are mixed, 32 words of them.  partial (zeroed) takes the
+// where they are mixed, 32 words of them.  partial takes the
 // vote's totals, two words in each of kNodeSlots slots.
 struct NodeArgs {
   AxisArrays axis[3];
@@ -332,21 +332,23 @@ struct NodeArgs {
   double lo[3], h[3], inv_h[3], slack[3];
   float inv_hf[3], slackf[3];  // the same for a float32 estimate
   uint32_t* bits;
-  uint32_t* status;   // kStatusMismatch: offsets of an input out of order
-  uint32_t* n_mixed;  // bricks listed in mixed (zeroed)
+  uint32_t* host_fail;  // pinned word for kStatusMismatch: offsets of an input out of order
+  // kNodeCounters words, cleared by the bin pass: bricks listed in mixed, and
+  // (from word 64 on) partial
+  uint32_t* n_mixed;
   uint64_t* partial;
   uint2* range;       // [3 nb^3] (first, number of toggles)
   uint8_t* kind;      // [3 nb^3]
   uint32_t* parity;   // [3 nb^3][32]
   uint16_t* toggles[3];
   uint32_t* mixed;    // [nb^3] bricks that are not one value
+  uint32_t* host;     // four words of pinned memory: nodes inside (low, high), nodes
+                      // whose three votes differ (low, high)
 };
 constexpr uint32_t kNodeSlots = 256;  // (one pair would take an atomic from every workgroup)
+constexpr uint32_t kNodeCounters = 64 + 4 * kNodeSlots;
 hipError_t launch_node_bins(const NodeArgs& g, hipStream_t s);
 hipError_t launch_classify_nodes(const NodeArgs& g, hipStream_t s);
-// totals and status to five words of pinned host memory: status, inside (low,
-// high), nodes whose three votes differ (low, high)
-hipError_t launch_node_stats(const NodeArgs& g, uint32_t* host, hipStream_t s);
 
 // Offsetting (ldni_offset.hip): the three input LDNIs, their box (lo, h per
 // world axis), |r| and eps, the sphere centres (3 doubles per sample,

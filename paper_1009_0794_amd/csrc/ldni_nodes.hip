@@ -43,6 +43,11 @@ constexpr int kNodeBlock = 256;
 constexpr int kNodeWaves = kNodeBlock / 64;
 constexpr int kUniformBlock = 512;
 constexpr int kUniformWaves = kUniformBlock / 64;
+// Grids of up to this many bricks (w <= 256) are voted on brick by brick: without
+// a launch that lists those that are not one value and one that sums the totals.
+// An icosphere at w = 64, 128 and 200: 50.5, 50.6 and 52.4 us with the two launches
+// (and one more, which cleared the counters), 40.6, 40.6 and 42.2 now.
+constexpr uint32_t kNodeAll = 512;
 constexpr int kParityStride = 33;  // LDS words per brick of the start bits (no bank conflicts)
 
 // What a brick's 1024 rays of one axis are at the brick's first node.
@@ -81,15 +86,14 @@ __device__ __forceinline__ int first_node(const NodeArgs& g, int f, float s) {
 // per wave of 64 samples over both passes), half by the latency of a patch's
 // few serial steps: 0.32 ms for the 38.6 M samples of scene64 at w = 2048, 50 us
 // for the flower at w = 333; the span codes it replaced took 0.46 ms and 103 us.
-constexpr int kBinBlock = 512;
-constexpr int kBinWaves = kBinBlock / 64;
 constexpr uint32_t kKept = 3072;
-constexpr int kSegs = kBinBlock / 32;
 
+template <int kBinBlock>
 __global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
+  constexpr int kBinWaves = kBinBlock / 64, kSegs = kBinBlock / 32;
   extern __shared__ uint32_t s_node[];
   __shared__ uint32_t s_off[32][33];  // the rays' first samples
-  __shared__ uint32_t s_bad;          // rows whose offsets decrease
+  __shared__ uint32_t s_falls[kBinWaves];  // rows whose offsets decrease
   __shared__ uint32_t s_at[33];       // samples of the rows before
   __shared__ uint32_t s_keep[kKept];  // brick << 15 | toggle, or ~0
   __shared__ uint32_t s_seg[kSegs][kParityStride];
@@ -111,56 +115,65 @@ __global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
                                : (size_t)pv * nb + (size_t)pu;
   const size_t step = f == 0 ? 1 : f == 1 ? (size_t)nb : nb2;
   const size_t axis0 = (size_t)f * nb2 * nb;
+  auto mismatch = [&] {
+    __hip_atomic_store(g.host_fail, (uint32_t)kStatusMismatch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
 
-  if (tid == 0) s_bad = 0u;
-  uint32_t band = 0;  // first sample of the image's row
-  if (tid < rows) band = ax.offsets[(size_t)(32 * pv + tid) * w];
+  // the counters of the launches behind this one (it has none itself)
+  if (blockIdx.x == 0 && f == 0)
+    for (uint32_t q = tid; q < kNodeCounters; q += kBinBlock) g.n_mixed[q] = 0u;
+  uint32_t falls = 0;  // rows whose offsets decrease
   for (int q = tid; q < 32 * 33; q += kBinBlock) {
     const int r = q / 33, c = q - 33 * r;
     // (rays beyond the grid are empty)
-    s_off[r][c] = r < rows ? ax.offsets[(size_t)(32 * pv + r) * w + 32 * pu + min(c, cols)] : 0u;
+    uint32_t o0 = 0, o1 = 0;
+    if (r < rows) {
+      const uint32_t* o = ax.offsets + (size_t)(32 * pv + r) * w + 32 * pu;
+      o0 = o[min(c, cols)];
+      o1 = o[min(c + 1, cols)];
+    }
+    s_off[r][c] = o0;
+    falls |= o0 > o1 ? 1u << r : 0u;
   }
+  if (__ballot(falls != 0) != 0)
+    for (int o = 32; o >= 1; o >>= 1) falls |= (uint32_t)__shfl_xor((int)falls, o, 64);
+  if (lane == 0) s_falls[wave] = falls;
+  uint32_t band = 0;  // first sample of the image's row
+  if (wave == 1 && lane < rows) band = ax.offsets[(size_t)(32 * pv + lane) * w];
   for (int q = tid; q < nb * (1 + kParityStride); q += kBinBlock) s_node[q] = 0u;
-  __syncthreads();
-  for (int q = tid; q < 1024; q += kBinBlock) {
-    const int r = q >> 5, c = q & 31;
-    if (s_off[r][c] > s_off[r][c + 1]) atomicOr(&s_bad, 1u << r);
-  }
   __syncthreads();
   // a row whose offsets decrease or pass the sample count is an error and
   // counts as empty, and so do all rows that name more samples than there are
-  if (tid < 64) {
-    const int r = tid & 31;
-    const bool ok = s_off[r][32] <= ax.n && !((s_bad >> r) & 1u);
-    uint64_t incl = (ok && tid < 32) ? s_off[r][32] - s_off[r][0] : 0u;
-    uint64_t before = tid < rows ? (uint64_t)s_off[r][0] - band : 0u;
+  if (wave == 0) {
+    const int r = lane & 31;
+    uint32_t bad = 0;
+    for (int k = 0; k < kBinWaves; ++k) bad |= s_falls[k];
+    const bool ok = s_off[r][32] <= ax.n && !((bad >> r) & 1u);
+    uint64_t incl = (ok && lane < 32) ? s_off[r][32] - s_off[r][0] : 0u;
 #pragma unroll
     for (int o = 1; o < 32; o <<= 1) {
       const uint64_t y = __shfl_up((unsigned long long)incl, o, 64);
-      if (tid >= o) incl += y;
+      if (lane >= o) incl += y;
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor((unsigned long long)before, o, 64);
-    const uint64_t total = __shfl((unsigned long long)incl, 31, 64);
-    const bool fits = total <= ax.n;
-    if (tid < 32) {
-      if (!ok || !fits) atomicOr(g.status, kStatusMismatch);
+    const bool fits = __shfl((unsigned long long)incl, 31, 64) <= ax.n;
+    if (lane < 32) {
+      if (!ok || !fits) mismatch();
       s_at[r + 1] = fits ? (uint32_t)incl : 0u;
     }
+    if (lane == 0) s_at[0] = 0u;
+  } else if (wave == 1) {
     // The patch's part of its axis's list: the samples of the band's 32 rows
     // are one range, and the patches of the band share it in their order,
     // each as many entries as it has samples.
-    if (tid == 0) {
-      s_at[0] = 0u;
-      uint64_t base = (uint64_t)band + before;
-      if (base > ax.n || base + total > ax.n) {  // (offsets that decrease somewhere: an empty patch)
-        atomicOr(g.status, kStatusMismatch);
-        base = ~0ull;
-      }
-      s_base = base;
-    }
+    uint64_t before = lane < rows ? (uint64_t)s_off[lane][0] - band : 0u;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor((unsigned long long)before, o, 64);
+    if (lane == 0) s_base = band + before;
   }
   __syncthreads();
+  const uint64_t base = s_base;
+  const bool any = base <= ax.n && base + s_at[32] <= ax.n;  // (else offsets that decrease somewhere: an empty patch)
+  if (!any && tid == 0) mismatch();
   if (s_at[32] == 0u) {  // no sample: all outside
     if (tid < nb) {
       g.range[axis0 + brick0 + (size_t)tid * step] = make_uint2(0u, 0u);
@@ -170,51 +183,62 @@ __global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
   }
 
   // calls on(place in the patch, row, column, brick, node in the brick, live)
-  // for the samples of the row; live: paired and in front of some node
-  auto walk_row = [&](int r, auto&& on) {
-    const uint32_t* off = s_off[r];
-    const uint32_t len = s_at[r + 1] - s_at[r], row0 = off[0];
-    if (len == 0) return;
-    const float* dep = ax.depth + row0;
-    for (uint32_t s0 = 0;; s0 += 256) {  // four loads in flight
-      const uint32_t rest = len - s0;
+  // for the samples of this wave's rows from r on; live: paired and in front of
+  // some node.  Four loads are in flight, and a row's first four are on their
+  // way while the row before it is searched.
+  auto walk = [&](int r, auto&& on) {
+    auto load = [&](int q, uint32_t s0, float (&d)[4]) {
+      const uint32_t rest = s_at[q + 1] - s_at[q] - s0;
+      const float* dep = ax.depth + s_off[q][0] + s0;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) d[j] = 64 * j + lane < rest ? dep[64 * j + lane] : 0.0f;
+    };
+    float next[4] = {};
+    if (r < rows) load(r, 0, next);
+    for (; r < rows; r += kBinWaves) {
+      const uint32_t* off = s_off[r];
+      const uint32_t len = s_at[r + 1] - s_at[r], row0 = off[0];
       float d[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) d[j] = 64u * j + lane < rest ? dep[s0 + 64 * j + lane] : 0.0f;
+      for (int j = 0; j < 4; ++j) d[j] = next[j];
+      if (r + kBinWaves < rows) load(r + kBinWaves, 0, next);
+      for (uint32_t s0 = 0; s0 < len; s0 += 256) {
+        const uint32_t rest = len - s0;
+        if (s0 > 0) load(r, s0, d);
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) {  // two at a time: their chains of LDS reads overlap
-        if (64u * j >= rest) break;
-        uint32_t s[2];
-        int c[2] = {0, 0}, t[2];
+        for (int j = 0; j < 4; j += 2) {  // two at a time: their chains of LDS reads overlap
+          if (64u * j >= rest) break;
+          uint32_t s[2];
+          int c[2] = {0, 0}, t[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) s[i] = min(s0 + 64 * (j + i) + lane, len - 1);
-        // the ray: the last column whose samples start at or before s
+          for (int i = 0; i < 2; ++i) s[i] = min(s0 + 64 * (j + i) + lane, len - 1);
+          // the ray: the last column whose samples start at or before s
 #pragma unroll
-        for (int h = 16; h >= 1; h >>= 1)
+          for (int h = 16; h >= 1; h >>= 1)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) c[i] += off[c[i] + h] <= row0 + s[i] ? h : 0;
+            for (int i = 0; i < 2; ++i) c[i] += off[c[i] + h] <= row0 + s[i] ? h : 0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) t[i] = first_node(g, f, d[j + i]);
+          for (int i = 0; i < 2; ++i) t[i] = first_node(g, f, d[j + i]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const bool here = 64u * (j + i) + lane < rest;
-          const bool live = t[i] < w && row0 + s[i] - off[c[i]] < ((off[c[i] + 1] - off[c[i]]) & ~1u);
-          if (here) on(s_at[r] + s[i], c[i], t[i] >> 5, t[i] & 31, live);
+          for (int i = 0; i < 2; ++i) {
+            const bool here = 64u * (j + i) + lane < rest;
+            const bool live = t[i] < w && row0 + s[i] - off[c[i]] < ((off[c[i] + 1] - off[c[i]]) & ~1u);
+            if (here) on(s_at[r] + s[i], r, c[i], t[i] >> 5, t[i] & 31, live);
+          }
         }
+        if (rest <= 256) break;
       }
-      if (rest <= 256) break;
     }
   };
 
-  for (int r = wave; r < rows; r += kBinWaves)
-    walk_row(r, [&](uint32_t at, int c, int b, int t, bool live) {
-      if (at < kKept) s_keep[at] = live ? (uint32_t)(b << 15 | t | (c << 5) | (r << 10)) : ~0u;
-      if (!live) return;
-      atomicAdd(&s_cur[b], 1u);
-      // x- and z-rays: a word per row, bits along the columns; y-rays: a word
-      // per column (k), bits along the rows (i)
-      if (b + 1 < nb) atomicXor(&s_par[(b + 1) * kParityStride + (f == 1 ? c : r)], 1u << (f == 1 ? r : c));
-    });
+  walk(wave, [&](uint32_t at, int r, int c, int b, int t, bool live) {
+    if (at < kKept) s_keep[at] = live ? (uint32_t)(b << 15 | t | (c << 5) | (r << 10)) : ~0u;
+    if (!live) return;
+    atomicAdd(&s_cur[b], 1u);
+    // x- and z-rays: a word per row, bits along the columns; y-rays: a word
+    // per column (k), bits along the rows (i)
+    if (b + 1 < nb) atomicXor(&s_par[(b + 1) * kParityStride + (f == 1 ? c : r)], 1u << (f == 1 ? r : c));
+  });
   __syncthreads();
 
   // list positions: exclusive prefix of the bricks' counts from the range
@@ -228,8 +252,7 @@ __global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
   }
   if (lane == 63) s_scan[tid >> 6] = incl;
   __syncthreads();
-  const bool any = s_at[32] != 0u && s_base != ~0ull;
-  uint32_t first = (uint32_t)s_base;
+  uint32_t first = (uint32_t)base;
   for (int k = 0; k < wave; ++k) first += s_scan[k];
   first += incl - n_b;
   if (tid < nb) s_cur[tid] = first;
@@ -266,11 +289,11 @@ __global__ void __launch_bounds__(kBinBlock) node_bin_kernel(NodeArgs g) {
     if (x != ~0u) list[atomicAdd(&s_cur[x >> 15], 1u)] = (uint16_t)(x & 0x7fffu);
   }
   if (kept == s_at[32]) return;
-  for (int r = wave; r < rows; r += kBinWaves)
-    if (s_at[r + 1] > kKept)
-      walk_row(r, [&](uint32_t at, int c, int b, int t, bool live) {
-        if (live && at >= kKept) list[atomicAdd(&s_cur[b], 1u)] = (uint16_t)(t | (c << 5) | (r << 10));
-      });
+  int r0 = wave;  // the first row with samples that were not kept
+  while (r0 < rows && s_at[r0 + 1] <= kKept) r0 += kBinWaves;
+  walk(r0, [&](uint32_t at, int r, int c, int b, int t, bool live) {
+    if (live && at >= kKept) list[atomicAdd(&s_cur[b], 1u)] = (uint16_t)(t | (c << 5) | (r << 10));
+  });
 }
 
 // One axis's part of a brick for the vote.
@@ -353,14 +376,15 @@ __global__ void __launch_bounds__(kUniformBlock) uniform_nodes_kernel(NodeArgs g
   }
 }
 
-// The listed bricks, a wave each in turn; lane l holds the 16 words
-// 4 l + 256 m + c (m, c = 0..3): rows k = 8 m + l / 8, j = 4 (l % 8) + c.
+// The listed bricks (kAll: every brick, and the last workgroup reports the
+// totals), a wave each in turn; lane l holds the 16 words 4 l + 256 m + c (m, c = 0..3): rows k = 8 m + l / 8, j = 4 (l % 8) + c.
 // One LDS matrix per wave serves the three axes in turn, four waves per SIMD
 // (123 registers; held to 80 they spill: 0.70 ms for all bricks against 0.47).
 // Bound by the latency of the list reads: 27,000 of scene64's 262,144 bricks
 // at w = 2048 in 0.10 ms.  The vote it replaced transposed a 32 x 32 bit matrix
 // per thread of every brick: 0.93 ms, and 1.05 ms for the flower at w = 333 (now 29
 // us), whose spans with more than two samples it walked.
+template <bool kAll>
 __global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs g) {
   __shared__ uint4 s_mat[kNodeWaves][256];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -419,13 +443,13 @@ __global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs 
   };
 
   const uint32_t wave_no = blockIdx.x * kNodeWaves + wave, stride = gridDim.x * kNodeWaves;
-  const uint32_t n_listed = *g.n_mixed;
+  const uint32_t n_listed = kAll ? n_bricks : *g.n_mixed;
   uint32_t n_inside = 0, n_split = 0;
 #pragma unroll
   for (int m = 0; m < 4; ++m) mat[64 * m + lane] = make_uint4(0u, 0u, 0u, 0u);
   sync();
   for (uint32_t at = wave_no; at < n_listed; at += stride) {
-    const uint32_t brick = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.mixed[at]);
+    const uint32_t brick = kAll ? at : (uint32_t)__builtin_amdgcn_readfirstlane((int)g.mixed[at]);
     const BrickAxis vx = brick_axis(g, brick), vy = brick_axis(g, (size_t)n_bricks + brick),
                     vz = brick_axis(g, 2 * (size_t)n_bricks + brick);
     const BrickAxis x = uniform(vx), y = uniform(vy), z = uniform(vz);
@@ -537,6 +561,28 @@ __global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs 
     n_inside += ni;
     n_split += ns;
   }
+  if (kAll) {
+    // one brick a wave at most: both counts of a wave fit 16 bits, and of a
+    // grid 28; with the workgroups that are done in the upper 8 one atomic per
+    // workgroup adds them up and finds the last, which reports
+    static_assert(kNodeAll * 32768ull <= 1ull << 27 && kNodeAll / kNodeWaves < 256, "the fields of the sum");
+    __shared__ uint32_t s_n[kNodeWaves];
+    uint32_t n = n_inside | n_split << 16;
+    for (int o = 32; o > 0; o >>= 1) n += (uint32_t)__shfl_xor((int)n, o);
+    if (lane == 0) s_n[wave] = n;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long sum = 1ull << 56;
+    for (int q = 0; q < kNodeWaves; ++q) sum += (unsigned long long)(s_n[q] & 0xffffu) | (unsigned long long)(s_n[q] >> 16) << 28;
+    sum += atomicAdd((unsigned long long*)g.partial, sum);
+    if (sum >> 56 != gridDim.x) return;
+    constexpr uint32_t field = (1u << 28) - 1u;
+    g.host[0] = (uint32_t)sum & field;
+    g.host[1] = 0u;
+    g.host[2] = (uint32_t)(sum >> 28) & field;
+    g.host[3] = 0u;
+    return;
+  }
   // (a lane sees fewer than 2^32 nodes: 512 of each brick)
   uint64_t a = n_inside, b = n_split;
   for (int o = 32; o > 0; o >>= 1) {
@@ -548,63 +594,61 @@ __global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs 
   if (lane == 0 && b != 0) atomicAdd(slot + 1, (unsigned long long)b);
 }
 
-// Sums the (inside, split) counts of the kNodeSlots slots and writes the status word and
-// both sums (low, high word each) to pinned host memory (one block).
-__global__ void __launch_bounds__(kNodeBlock) node_stats_kernel(const uint64_t* partial, uint32_t n, const uint32_t* status,
-                                                                uint32_t* host) {
+// Sums the counts of the kNodeSlots slots and writes both (low, high word
+// each) to pinned host memory (one block).
+__global__ void __launch_bounds__(kNodeBlock) node_stats_kernel(const uint64_t* partial, uint32_t* host) {
+  static_assert(kNodeSlots == kNodeBlock, "a slot per thread");
   __shared__ uint64_t s_sum[2][kNodeWaves];
-  uint64_t a = 0, b = 0;
-  for (uint32_t q = threadIdx.x; q < n; q += kNodeBlock) {
-    a += partial[2 * q];
-    b += partial[2 * q + 1];
-  }
+  uint64_t a = partial[2 * threadIdx.x], b = partial[2 * threadIdx.x + 1];
   for (int o = 32; o > 0; o >>= 1) {
-    a += __shfl_xor(a, o);
-    b += __shfl_xor(b, o);
+    a += __shfl_xor((unsigned long long)a, o);
+    b += __shfl_xor((unsigned long long)b, o);
   }
   if ((threadIdx.x & 63) == 0) {
     s_sum[0][threadIdx.x >> 6] = a;
     s_sum[1][threadIdx.x >> 6] = b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t sa = 0, sb = 0;
-    for (int q = 0; q < kNodeWaves; ++q) {
-      sa += s_sum[0][q];
-      sb += s_sum[1][q];
-    }
-    host[0] = *status;
-    host[1] = (uint32_t)sa;
-    host[2] = (uint32_t)(sa >> 32);
-    host[3] = (uint32_t)sb;
-    host[4] = (uint32_t)(sb >> 32);
+  if (threadIdx.x != 0) return;
+  a = b = 0;
+  for (int q = 0; q < kNodeWaves; ++q) {
+    a += s_sum[0][q];
+    b += s_sum[1][q];
   }
-  __threadfence_system();
+  host[0] = (uint32_t)a;
+  host[1] = (uint32_t)(a >> 32);
+  host[2] = (uint32_t)b;
+  host[3] = (uint32_t)(b >> 32);
 }
 
 }  // namespace
 
 hipError_t launch_node_bins(const NodeArgs& g, hipStream_t s) {
   const uint32_t lds = sizeof(uint32_t) * (uint32_t)g.nb * (1 + kParityStride);  // 34 KB at w = 8192
-  hipLaunchKernelGGL(node_bin_kernel, dim3((uint32_t)g.nb * g.nb, 3), dim3(kBinBlock), lds, s, g);
+  const uint32_t patches = (uint32_t)g.nb * g.nb;
+  // 1,024 threads a patch, two rows a wave, where all patches are resident at
+  // once (two per CU): what counts then is a patch's own time.  Calls on an
+  // icosphere at w = 64 and the flower at 333: 40.6 and 106 us, with 512 threads
+  // 43.4 and 108; one at w = 2048 485 and 437 us.
+  if (3 * patches <= 512) hipLaunchKernelGGL(node_bin_kernel<1024>, dim3(patches, 3), dim3(1024), lds, s, g);
+  else hipLaunchKernelGGL(node_bin_kernel<512>, dim3(patches, 3), dim3(512), lds, s, g);
   return hipGetLastError();
 }
 
 hipError_t launch_classify_nodes(const NodeArgs& g, hipStream_t s) {
   const uint32_t bricks = (uint32_t)g.nb * g.nb * g.nb;
+  const uint32_t blocks = (bricks + kNodeWaves - 1) / kNodeWaves;
+  if (bricks <= kNodeAll) {
+    hipLaunchKernelGGL(classify_nodes_kernel<true>, dim3(blocks), dim3(kNodeBlock), 0, s, g);
+    return hipGetLastError();
+  }
   // bricks per wave: up to 64, fewer where that leaves under 4096 waves (16 per CU)
   const uint32_t per = bricks / 4096 < 1 ? 1 : bricks / 4096 > 64 ? 64 : bricks / 4096;
   const uint32_t group = per * kUniformWaves;
   hipLaunchKernelGGL(uniform_nodes_kernel, dim3((bricks + group - 1) / group), dim3(kUniformBlock), 0, s, g, per);
   // as many workgroups as stay resident (four per CU), at most one wave a brick
-  const uint32_t blocks = (bricks + kNodeWaves - 1) / kNodeWaves;
-  hipLaunchKernelGGL(classify_nodes_kernel, dim3(blocks < 1024 ? blocks : 1024), dim3(kNodeBlock), 0, s, g);
-  return hipGetLastError();
-}
-
-hipError_t launch_node_stats(const NodeArgs& g, uint32_t* host, hipStream_t s) {
-  hipLaunchKernelGGL(node_stats_kernel, dim3(1), dim3(kNodeBlock), 0, s, g.partial, kNodeSlots, g.status,
-                     host);
+  hipLaunchKernelGGL(classify_nodes_kernel<false>, dim3(blocks < 1024 ? blocks : 1024), dim3(kNodeBlock), 0, s, g);
+  hipLaunchKernelGGL(node_stats_kernel, dim3(1), dim3(kNodeBlock), 0, s, g.partial, g.host);
   return hipGetLastError();
 }
 
