@@ -329,6 +329,13 @@ ldni_status validate(const float* verts, int64_t n_verts, const int32_t* tris, i
   return LDNI_OK;
 }
 
+// Whether a staging buffer by-passes the caches.
+bool streams(uint64_t entries) {
+  // test hook: from more entries than this on
+  if (const char* env = std::getenv("LDNI_STREAM_ENTRIES")) return entries > std::strtoull(env, nullptr, 10);
+  return stage_streams(entries);
+}
+
 // ---- optional kernel timing ----
 struct ProfRecord {
   const char* name;
@@ -787,7 +794,7 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
       im.stage_qs = p->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(p->stage) + stage_cap)
                              : nullptr;
       im.stage_cap = p->stage ? stage_cap : 0;
-      im.stage_stream = stage_streams(im.stage_cap);
+      im.stage_stream = streams(im.stage_cap);
       im.stage_layers = stage_layers;
     }
   }
@@ -1820,7 +1827,7 @@ hipError_t batch_upload(ldni_batch* b) {
     im.stage_qs = b->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(b->stage) + b->stage_cap)
                            : nullptr;
     im.stage_cap = b->stage ? b->stage_cap : 0;
-    im.stage_stream = stage_streams(im.stage_cap);
+    im.stage_stream = streams(im.stage_cap);
     im.stage_layers = b->stage_layers;
     im.host_fail = b->host_out + kBatchFail;
   }
