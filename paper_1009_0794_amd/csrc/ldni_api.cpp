@@ -794,9 +794,9 @@ ldni_status ldni_sample_begin(const float* verts, int64_t n_verts, const int32_t
       im.stage_qs = p->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(p->stage) + stage_cap)
                              : nullptr;
       im.stage_cap = p->stage ? stage_cap : 0;
-      im.stage_stream = streams(im.stage_cap);
       im.stage_layers = stage_layers;
     }
+    set.stage_stream = streams(p->stage ? stage_cap : 0);
   }
   void* scan_scratch = ws + o_scan;
   set.place_cap = place_stage_cap(tw * th);
@@ -1827,11 +1827,11 @@ hipError_t batch_upload(ldni_batch* b) {
     im.stage_qs = b->stage ? reinterpret_cast<uint32_t*>(static_cast<uint64_t*>(b->stage) + b->stage_cap)
                            : nullptr;
     im.stage_cap = b->stage ? b->stage_cap : 0;
-    im.stage_stream = streams(im.stage_cap);
     im.stage_layers = b->stage_layers;
     im.host_fail = b->host_out + kBatchFail;
   }
   b->dev.items = b->items;
+  b->dev.stage_stream = streams(b->stage ? b->stage_cap : 0);
   hipError_t e = hipMemcpy(b->dev.images, b->images_h.data(), sizeof(Image) * b->n_img, hipMemcpyHostToDevice);
   if (e != hipSuccess) return e;
   return hipMemcpy(b->dev.meshes, b->meshes_h.data(), sizeof(BatchMesh) * b->n_meshes, hipMemcpyHostToDevice);

@@ -66,8 +66,6 @@ struct Image {
   uint32_t* counts;     // [w*w] samples per pixel
   uint32_t* max_layers; // [1] largest per-pixel count (batches)
   uint32_t* tile_max;   // [n_tiles] largest count of each tile (batches), or null
-  Band* band;           // [nty] what the sampling pass adds up per row of tiles
-                        // (zeroed; the images' one after the other), or null
   // outputs
   uint32_t* offsets;  // [w*w + 1]
   float* depth;       // [n]
@@ -75,13 +73,11 @@ struct Image {
   uint32_t* normal_rgb8;  // [n] 8-bit normal codes, or null for float normals
   int32_t* tri;       // [n]
   uint32_t* status;   // shared status word
-  uint32_t* host_fail;  // pinned word that a write pass raises status bits in, or null
   // Hits of the sampling pass, grouped by tile.  With stage_key null every
   // tile with hits is walked again by the place pass.
   uint64_t* stage_key;               // (depth key, triangle) of each hit
   uint32_t* stage_qs;                // tile pixel | (slot within the pixel << 10)
   uint64_t stage_cap;                // entries in the buffer (below 2^32 - 1)
-  int32_t stage_stream;              // staged hits by-pass the caches (stage_streams)
   uint32_t stage_layers;             // a tile's region holds at most this many entries per pixel
   // [n_tiles + 1] the tile's candidates, each triangle's rounded up to whole
   // 4-entry groups (counted by setup); the region scan turns them into the
@@ -93,6 +89,9 @@ struct Image {
   uint32_t* tile_hits;               // [n_tiles] hits of the tile
   uint32_t* walk_list;               // set-wide tile numbers the write pass walks again
   uint32_t* walk_count;              // entries of walk_list (shared by the set)
+  Band* band;           // [nty] what the sampling pass of a single mesh adds up per row of tiles
+                        // (zeroed; the images' one after the other)
+  uint32_t* host_fail;  // pinned word that a write pass raises status bits in
 };
 
 // tile_stage value of a tile whose hits did not fit its staging region
@@ -107,6 +106,7 @@ struct ImageSet {
   int32_t n;
   uint32_t tile_start[kMaxImages + 1];  // prefix of tile counts
   int32_t place_cap;  // stage capacity of the place pass
+  bool stage_stream;  // staged hits by-pass the caches (stage_streams)
 };
 
 // Mesh-level setup: per triangle gather, validate, face normal, candidate
@@ -136,12 +136,17 @@ constexpr int kBinSlots = 1024;
 constexpr int64_t kBinSplitChunks = 256;
 int bin_split(int64_t n_tris, int nimg);
 
-// Raises the mismatch bit in the device status word and, in a write pass, in
-// the pinned word that the host reads once the pass is over.
+// Raises the mismatch bit of a write pass in the pinned word that the host
+// reads once the pass is over.
+__device__ __forceinline__ void raise_write(uint32_t* host_fail) {
+  __hip_atomic_store(host_fail, (uint32_t)kStatusMismatch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same in a pass that counts or writes: in the device status word and, if
+// it writes, in the pinned word.
 __device__ __forceinline__ void raise_mismatch(uint32_t* status, uint32_t* host_fail) {
   atomicOr(status, (uint32_t)kStatusMismatch);
-  if (host_fail != nullptr)
-    __hip_atomic_store(host_fail, (uint32_t)kStatusMismatch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (host_fail != nullptr) raise_write(host_fail);
 }
 
 // Fills the derived fields of an image (inverse steps, centre slack, tile
@@ -244,6 +249,7 @@ struct BatchDevice {
   uint32_t* walk_list;
   uint32_t* walk_count;
   const uint32_t* region_total;     // staging entries the regions of the batch ask for
+  bool stage_stream;                // staged hits by-pass the caches (stage_streams)
 };
 
 // setup and tile counts, then (after the tile scan) the scatter: chunks of

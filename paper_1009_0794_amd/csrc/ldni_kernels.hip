@@ -209,7 +209,8 @@ __device__ __forceinline__ int image_of_block(const ImageSet& set, uint32_t b) {
 // vertices, store them and its unit face normal, and its candidate rectangle
 // on every image (also returned in r).  geometry: this call stores the vertices
 // and the normal (several calls with other images may share a triangle).
-template <class ImageAt>
+// kOne: nimg is 1 (so that no image's number is a variable).
+template <bool kOne, class ImageAt>
 __device__ void setup_one(const MeshSetup& m, int k0, int nimg, ImageAt&& image_at, int64_t t, bool live,
                           bool geometry, Rect* r) {
   int32_t ia = 0, ib = 0, ic = 0;
@@ -280,7 +281,7 @@ __device__ void setup_one(const MeshSetup& m, int k0, int nimg, ImageAt&& image_
     for (int d = 0; d < 3; ++d) {
       if (!((need >> d) & 1u)) continue;
       int k = 0;  // an image that images axis d, with its centre formula for it
-      if (nimg > 1) while (image_at(k).u != d && image_at(k).v != d) ++k;
+      if (!kOne) while (image_at(k).u != d && image_at(k).v != d) ++k;
       const Image& im = image_at(k);
       const bool as_u = im.u == d;
       const double lo = as_u ? im.lo_u : im.lo_v, h = as_u ? im.h_u : im.h_v;
@@ -409,7 +410,7 @@ __device__ void bin_rect_chunk(const Image& im, uint32_t kimg, int64_t t, bool l
 // into the table, then the reservations and their records.
 // (k0: number of the first of the nimg images among the mesh's; chunk: where the
 // records go)
-template <class ImageAt>
+template <bool kOne, class ImageAt>
 __device__ void setup_count_chunk(const MeshSetup& m, int k0, int nimg, ImageAt&& image_at, int64_t t0, int64_t t1,
                                   uint32_t chunk, BinLds& h) {
   for (int i = threadIdx.x; i < kBinSlots; i += kBinBlock) {
@@ -423,7 +424,7 @@ __device__ void setup_count_chunk(const MeshSetup& m, int k0, int nimg, ImageAt&
     const int64_t t = tb + threadIdx.x;
     const bool live = t < t1;
     Rect r[kMaxImages];
-    setup_one(m, k0, nimg, [&](int k) -> const Image& { return image_at(k0 + k); }, t, live, k0 == 0, r);
+    setup_one<kOne>(m, k0, nimg, [&](int k) -> const Image& { return image_at(k0 + k); }, t, live, k0 == 0, r);
 #pragma unroll
     for (int k = 0; k < kMaxImages; ++k)
       if (k < nimg) bin_rect_chunk<false>(image_at(k0 + k), (uint32_t)(k0 + k), t, live, r[k], h);
@@ -494,7 +495,7 @@ __global__ void __launch_bounds__(kBinBlock) setup_kernel(MeshSetup m, ImageSet 
   __shared__ BinLds h;
   const int64_t t0 = (int64_t)blockIdx.x * kBinChunkTris;
   for_images<kSplit>(set, [&](int k0, int nimg, uint32_t chunk) {
-    setup_count_chunk(m, k0, nimg, [&](int k) -> const Image& { return set.img[k]; }, t0,
+    setup_count_chunk<kSplit>(m, k0, nimg, [&](int k) -> const Image& { return set.img[k]; }, t0,
                       min(t0 + kBinChunkTris, m.n_tris), chunk, h);
   });
 }
@@ -600,6 +601,7 @@ __device__ __forceinline__ bool covered_sign(float au, float bu, float cu, float
 struct EntryRect {
   int x0, y0, width, y1;
 };
+template <bool kWrite>
 __device__ __forceinline__ EntryRect entry_rect(const Image& im, const TileGeom& g, int2 ent) {
   const uint32_t gm = (uint32_t)ent.y;
   EntryRect r;
@@ -608,7 +610,8 @@ __device__ __forceinline__ EntryRect entry_rect(const Image& im, const TileGeom&
   r.width = ((gm >> 16) & 255) + 1;
   r.y1 = r.y0 + (int)(gm >> 24) + 1;
   if ((uint32_t)ent.x >= (uint64_t)im.n_tris || r.x0 + r.width > g.cw || r.y1 > g.ch) {
-    raise_mismatch(im.status, im.host_fail);
+    if (kWrite) raise_write(im.host_fail);
+    else atomicOr(im.status, (uint32_t)kStatusMismatch);
     r.x0 = 0;
     r.y0 = 0;
     r.width = 1;
@@ -639,7 +642,7 @@ __device__ void tile_candidates(const Image& im, const TileGeom& g, int r0, int 
     if (k < m) {
       const int2 ent = im.tile_list[base + k];
       const int32_t t = ent.x;
-      const EntryRect r = entry_rect(im, g, ent);
+      const EntryRect r = entry_rect<true>(im, g, ent);
       const int py0 = max(r.y0, r0), py1 = min(r.y1, r1);
       const int width = r.width;
       if (py1 > py0) nc = width * (py1 - py0);
@@ -778,7 +781,7 @@ struct SampleLds {
 // key and arrival slot with every lane busy, storing them to consecutive
 // entries of the tile's staging region.  The region is sized by the tile's
 // candidate count (pixels of the clipped rectangles), which bounds its hits.
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t* plan, uint32_t n_total,
                             int place_cap) {
   using Lds = SampleLds<kTilePix>;
@@ -846,7 +849,7 @@ __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t*
       float2 cc = make_float2(0.f, 0.f);
       if (k < m) {
         const int2 ent = im.tile_list[cbase + k];
-        const EntryRect r = entry_rect(im, g, ent);
+        const EntryRect r = entry_rect<false>(im, g, ent);
         if (r.y1 > r.y0) {
           nc = r.width * (r.y1 - r.y0);
           gm = r.x0 | (r.y0 << 8) | ((r.width - 1) << 16);
@@ -953,11 +956,9 @@ __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t*
           const size_t at = (size_t)region_first + pos;
           const uint64_t key = sample_key(dep, __float_as_int(z.w));
           const uint32_t qs = (uint32_t)q | (slot << 10);
-          if (im.stage_stream) {
-            asm volatile("");  // (without the two the compiler makes plain stores of both)
+          if (kStream) {
             __builtin_nontemporal_store(key, &im.stage_key[at]);
             __builtin_nontemporal_store(qs, &im.stage_qs[at]);
-            asm volatile("");
           } else {
             im.stage_key[at] = key;
             im.stage_qs[at] = qs;
@@ -1001,7 +1002,7 @@ __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t*
     // The tile's samples and place items, added up per row of tiles for the
     // offsets pass (to one address for the whole image the atomics would queue
     // up).
-    if (im.band != nullptr && hits > 0) {
+    if (!plan && hits > 0) {
       Band* bd = im.band + g.ty;
       atomicAdd((unsigned long long*)&bd->samples, (unsigned long long)hits);
       atomicAdd((unsigned long long*)&bd->items, (unsigned long long)(K >= 2 ? (uint64_t)K << 32 : (uint64_t)K));
@@ -1010,10 +1011,10 @@ __device__ void sample_tile(const Image& im, int tile, uint32_t gtile, uint32_t*
 }
 
 // (small tiles: at most 72 VGPRs, seven workgroups per CU)
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __global__ void __launch_bounds__(kBlock, sample_wgs_per_cu<kTilePix>()) sample_kernel(ImageSet set) {
   const int k = image_of_block(set, blockIdx.x);
-  sample_tile<kTilePix>(set.img[k], (int)(blockIdx.x - set.tile_start[k]), blockIdx.x, nullptr, 0u, set.place_cap);
+  sample_tile<kTilePix, kStream>(set.img[k], (int)(blockIdx.x - set.tile_start[k]), blockIdx.x, nullptr, 0u, set.place_cap);
 }
 
 // ---------------------------------------------------------------------------
@@ -1202,7 +1203,7 @@ __device__ void write_tile(const Image& im, int tile, int part = 0, int parts = 
                               if (q < q0 || q >= q1) return;
                               const uint32_t slot = atomicAdd(&s_cur[q], 1u);
                               if (slot >= s_pre[q + 1] - s_pre[q]) {  // count/write disagree
-                                raise_mismatch(im.status, im.host_fail);
+                                raise_write(im.host_fail);
                                 return;
                               }
                               const float4 z = L.z[e];
@@ -1246,7 +1247,7 @@ struct PlaceItem {
 // at its pixel's slot in LDS (the slot came with the hit), then ranks and
 // stores the keys like write_tile.  A single pixel deeper than the stage is
 // stored unsorted straight to its output range and sorted there.
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t hits, int part,
                            int parts) {
   constexpr int kStageCap = stage_cap(kTilePix);
@@ -1268,25 +1269,20 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
     // pixel offsets are scanned, so the two reads overlap.
     uint32_t rq[kPer];
     uint64_t rk[kPer];
-    if (im.stage_stream) {
-      asm volatile("");  // (without it the compiler makes plain loads of both)
 #pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const uint32_t i = threadIdx.x + u * kBlock;
+    for (int u = 0; u < kPer; ++u) {
+      const uint32_t i = threadIdx.x + u * kBlock;
+      if (kStream) {
         rq[u] = i < hits ? __builtin_nontemporal_load(qs + i) : 0xffffffffu;
         rk[u] = i < hits ? __builtin_nontemporal_load(keys + i) : 0;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const uint32_t i = threadIdx.x + u * kBlock;
+      } else {
         rq[u] = i < hits ? qs[i] : 0xffffffffu;
         rk[u] = i < hits ? keys[i] : 0;
       }
     }
     tile_prefix(im, g, s_off, s_pre, nullptr, s_wave);
     if (s_pre[npix] != hits) {  // staging and counts disagree
-      if (threadIdx.x == 0) raise_mismatch(im.status, im.host_fail);
+      if (threadIdx.x == 0) raise_write(im.host_fail);
       return;
     }
 #pragma unroll
@@ -1295,7 +1291,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
       const int q = (int)(rq[u] & 1023u);
       const uint32_t slot = rq[u] >> 10;
       if (q >= npix || slot >= s_pre[q + 1] - s_pre[q]) {
-        raise_mismatch(im.status, im.host_fail);
+        raise_write(im.host_fail);
         continue;
       }
       s_keys[s_pre[q] + slot] = rk[u];
@@ -1308,7 +1304,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
 
   tile_prefix(im, g, s_off, s_pre, nullptr, s_wave);
   if (s_pre[npix] != hits) {
-    if (threadIdx.x == 0) raise_mismatch(im.status, im.host_fail);
+    if (threadIdx.x == 0) raise_write(im.host_fail);
     return;
   }
   int q0 = 0;
@@ -1345,7 +1341,7 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
           const uint32_t slot = xs[u] >> 10;
           if (i >= hits || q < q0 || q >= q1) continue;
           if (slot >= s_pre[q + 1] - s_pre[q]) {
-            raise_mismatch(im.status, im.host_fail);
+            raise_write(im.host_fail);
             continue;
           }
           const uint64_t key = ks[u];
@@ -1373,11 +1369,11 @@ __device__ void place_tile(const Image& im, int tile, uint32_t first, uint32_t h
 }
 
 // One workgroup per place item.
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __global__ void __launch_bounds__(kBlock) place_kernel(ImageSet set, const PlaceItem* items) {
   const PlaceItem it = items[xcd_runs<kPlaceRun>(blockIdx.x, gridDim.x)];
   const int k = image_of_block(set, it.gtile);
-  place_tile<kTilePix>(set.img[k], (int)(it.gtile - set.tile_start[k]), it.first, it.hits,
+  place_tile<kTilePix, kStream>(set.img[k], (int)(it.gtile - set.tile_start[k]), it.first, it.hits,
                        (int)(it.part_parts & 0xffffu), (int)(it.part_parts >> 16));
 }
 
@@ -1891,7 +1887,7 @@ __global__ void __launch_bounds__(kBinBlock) batch_setup_kernel(BatchDevice B) {
   const uint32_t chunk = blockIdx.x - B.tri_block_start[mi];
   const int64_t t0 = (int64_t)chunk * kBinChunkTris;
   __shared__ BinLds h;
-  setup_count_chunk(bm.m, 0, bm.nimg, [&](int k) -> const Image& { return B.images[bm.img[k]]; }, t0,
+  setup_count_chunk<false>(bm.m, 0, bm.nimg, [&](int k) -> const Image& { return B.images[bm.img[k]]; }, t0,
                     min(t0 + kBinChunkTris, bm.m.n_tris), chunk, h);
 }
 
@@ -1928,7 +1924,7 @@ struct ItemGrabber {
 // Tiles [t0, t1) of the batch (the images of one tile class), work counter
 // `counter`, place runs of at most place_cap keys.
 // (the occupancy of sample_kernel)
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __global__ void __launch_bounds__(kBlock, sample_wgs_per_cu<kTilePix>())
     batch_sample_kernel(BatchDevice B, uint32_t n_tiles, uint32_t t0, uint32_t t1, int counter, int place_cap) {
   __shared__ uint32_t s_item;
@@ -1937,7 +1933,7 @@ __global__ void __launch_bounds__(kBlock, sample_wgs_per_cu<kTilePix>())
     const uint32_t item = t0 + grab(&B.work[counter], &s_item);
     if (item >= t1) break;
     const int k = __builtin_amdgcn_readfirstlane(segment_of(B.tile_start, B.n_images, item));
-    sample_tile<kTilePix>(B.images[k], (int)(item - B.tile_start[k]), item, B.plan, n_tiles, place_cap);
+    sample_tile<kTilePix, kStream>(B.images[k], (int)(item - B.tile_start[k]), item, B.plan, n_tiles, place_cap);
     __syncthreads();  // the next item reuses the tile's LDS
   }
 }
@@ -1970,7 +1966,7 @@ __global__ void __launch_bounds__(kBlock) batch_plan_items_kernel(BatchDevice B,
 // in tile order, so the class's items are two ranges.
 // (the occupancy the persistent grid is sized for: seven workgroups per CU
 // for small tiles, three for large ones)
-template <int kTilePix>
+template <int kTilePix, bool kStream>
 __global__ void __launch_bounds__(kBlock, kTilePix <= kSmallTilePix ? 7 : 3)
     batch_place_kernel(BatchDevice B, uint32_t n_tiles, uint32_t t0, uint32_t t1, int counter) {
   __shared__ uint32_t s_item;
@@ -1987,7 +1983,7 @@ __global__ void __launch_bounds__(kBlock, kTilePix <= kSmallTilePix ? 7 : 3)
     const int k = __builtin_amdgcn_readfirstlane(segment_of(B.tile_start, B.n_images, it.gtile));
     const Image& im = B.images[k];
     if (im.depth == nullptr) continue;  // the image did not fit the output arena
-    place_tile<kTilePix>(im, (int)(it.gtile - B.tile_start[k]), it.first, it.hits,
+    place_tile<kTilePix, kStream>(im, (int)(it.gtile - B.tile_start[k]), it.first, it.hits,
                          (int)(it.part_parts & 0xffffu), (int)(it.part_parts >> 16));
     // place_tile may return with waves still storing from its LDS stage
     // (one-run tiles): the next item reuses it
@@ -2182,10 +2178,10 @@ static bool small_tiles(const ImageSet& set) {
 hipError_t launch_sample(const ImageSet& set, hipStream_t s) {
   const uint32_t blocks = set.tile_start[set.n];
   if (blocks == 0) return hipSuccess;
-  if (small_tiles(set))
-    hipLaunchKernelGGL(sample_kernel<kSmallTilePix>, dim3(blocks), dim3(kBlock), 0, s, set);
-  else
-    hipLaunchKernelGGL(sample_kernel<kMaxTilePix>, dim3(blocks), dim3(kBlock), 0, s, set);
+  const auto kernel = small_tiles(set)
+                          ? (set.stage_stream ? sample_kernel<kSmallTilePix, true> : sample_kernel<kSmallTilePix, false>)
+                          : (set.stage_stream ? sample_kernel<kMaxTilePix, true> : sample_kernel<kMaxTilePix, false>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, set);
   return hipGetLastError();
 }
 
@@ -2233,10 +2229,10 @@ hipError_t launch_place(const ImageSet& set, const void* items, uint32_t n_items
   const bool small = small_tiles(set);
   const PlaceItem* it = static_cast<const PlaceItem*>(items);
   if (n_items > 0) {
-    if (small)
-      hipLaunchKernelGGL(place_kernel<kSmallTilePix>, dim3(n_items), dim3(kBlock), 0, s, set, it);
-    else
-      hipLaunchKernelGGL(place_kernel<kMaxTilePix>, dim3(n_items), dim3(kBlock), 0, s, set, it);
+    const auto kernel = small
+                            ? (set.stage_stream ? place_kernel<kSmallTilePix, true> : place_kernel<kSmallTilePix, false>)
+                            : (set.stage_stream ? place_kernel<kMaxTilePix, true> : place_kernel<kMaxTilePix, false>);
+    hipLaunchKernelGGL(kernel, dim3(n_items), dim3(kBlock), 0, s, set, it);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -2266,10 +2262,10 @@ hipError_t launch_batch_scatter(const BatchDevice& b, uint32_t chunks, hipStream
 
 hipError_t launch_batch_sample(const BatchDevice& b, uint32_t n_tiles, uint32_t n_small, hipStream_t s) {
   if (n_small > 0)
-    hipLaunchKernelGGL(batch_sample_kernel<kSmallTilePix>, dim3(persistent_grid(n_small, sample_wgs_per_cu<kSmallTilePix>())), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((b.stage_stream ? batch_sample_kernel<kSmallTilePix, true> : batch_sample_kernel<kSmallTilePix, false>), dim3(persistent_grid(n_small, sample_wgs_per_cu<kSmallTilePix>())), dim3(kBlock), 0, s,
                        b, n_tiles, 0u, n_small, 0, place_stage_cap(kSmallTilePix));
   if (n_tiles > n_small)
-    hipLaunchKernelGGL(batch_sample_kernel<kMaxTilePix>, dim3(persistent_grid(n_tiles - n_small, sample_wgs_per_cu<kMaxTilePix>())), dim3(kBlock),
+    hipLaunchKernelGGL((b.stage_stream ? batch_sample_kernel<kMaxTilePix, true> : batch_sample_kernel<kMaxTilePix, false>), dim3(persistent_grid(n_tiles - n_small, sample_wgs_per_cu<kMaxTilePix>())), dim3(kBlock),
                        0, s, b, n_tiles, n_small, n_tiles, 3, place_stage_cap(kMaxTilePix));
   return hipGetLastError();
 }
@@ -2281,10 +2277,10 @@ hipError_t launch_batch_place(const BatchDevice& b, uint32_t n_tiles, uint32_t n
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_plan_items_kernel, dim3(grid_for(n_tiles, kBlock)), dim3(kBlock), 0, s, b, n_tiles);
   if (n_small > 0)
-    hipLaunchKernelGGL(batch_place_kernel<kSmallTilePix>, dim3(persistent_grid(2 * n_small, 7)), dim3(kBlock), 0,
+    hipLaunchKernelGGL((b.stage_stream ? batch_place_kernel<kSmallTilePix, true> : batch_place_kernel<kSmallTilePix, false>), dim3(persistent_grid(2 * n_small, 7)), dim3(kBlock), 0,
                        s, b, n_tiles, 0u, n_small, 1);
   if (n_tiles > n_small)
-    hipLaunchKernelGGL(batch_place_kernel<kMaxTilePix>, dim3(persistent_grid(2 * (n_tiles - n_small), 3)),
+    hipLaunchKernelGGL((b.stage_stream ? batch_place_kernel<kMaxTilePix, true> : batch_place_kernel<kMaxTilePix, false>), dim3(persistent_grid(2 * (n_tiles - n_small), 3)),
                        dim3(kBlock), 0, s, b, n_tiles, n_small, n_tiles, 4);
   // tiles walked again: one build for all (the large one as soon as any
   // image has large tiles)
