@@ -226,15 +226,16 @@ __device__ __forceinline__ void wave_sync() {
 // samples, so these ranges never overlap).
 //
 // The samples of a batch, merged pixel by pixel, are cut into 64 equal parts,
-// one per lane: a lane finds where its part begins (the pixel by its merged
+// one per lane (the merge-path partition: Green, McColl, Bader, "GPU Merge Path",
+// ICS 2012): a lane finds where its part begins (the pixel by its merged
 // start, the place in both lists by a search along the merge's diagonal, and
 // with them the parities so far), merges up to 16 samples, and decides the
 // groups that begin in its part.  A change of the result state is marked at
 // the group's place in the merged order, so the marks in order are the end
 // points, enters and exits in turn (a pixel has an even number), and each pair
 // decides by its thickness.
-// Bound by VALU issue and the LDS reads of the merge: the union of two scene64
-// LDNIs at w = 2048 (25.7 M samples) takes 0.235 ms against 0.305 with a pixel
+// Bound by the latency of the merge's dependent LDS reads (VALU issue 33 %): the union of two scene64
+// LDNIs at w = 2048 (25.7 M samples) takes 0.236 ms against 0.305 with a pixel
 // per lane throughout, the flower minus a torus at w = 500 36 us against 108
 // (its polar pixels hold 160 samples, and a lane merged them while 63 waited).
 __global__ void __launch_bounds__(kBoolBlock) boolean_count_kernel(BooleanArgs g) {

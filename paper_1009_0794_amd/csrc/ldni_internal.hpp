@@ -183,6 +183,8 @@ uint32_t stage_layers_for(uint32_t max_layers_seen);
 // would only push other data out of it (scene64 at w = 2048, 0.5 GB of hits:
 // sampling pass 398 -> 375 us, place pass 390 -> 370 us), while the place pass
 // finds smaller ones there (flower at w = 512, 19 MB: 37.5 us, 39.3 around it).
+// A batch of 16 meshes gains 3 %; one of 256 with 3.5 GB of hits gains in its
+// sampling pass what it loses in its place pass (0.1 ms of 12.6).
 constexpr bool stage_streams(uint64_t entries) { return entries > (256ull << 20) / 12; }
 int place_stage_cap(int tile_pix);
 // Pixel counts -> offsets of all images and the place items (16 bytes each, in
@@ -369,7 +371,12 @@ constexpr int kOffsetEmit = 128;              // end points of one ray's result 
 constexpr int kOffsetSavedMax = 128;          // most end points per ray the count pass keeps for the write pass
 constexpr int kOffsetDeep = 512;              // a ray with more spheres than this is started first
 constexpr int kUnionEvents = 192;             // events of a ray that the count pass takes after merging chords
-constexpr int kUnionCells = 768;              // most depth cells of a ray (12 KB of LDS per wave)
+// Most depth cells of a ray, 15.2 KB of LDS per wave: beyond 768 cells of half a
+// radius they are of three quarters of one, and beyond 768 of those every ray is
+// swept over all its events.  Offsets of a torus by 2 pixels: w = 768 3.4 ms (most
+// 384 cells: 6.1, 1,536: 3.8), w = 1000 6.4 (9.3, 7.2), w = 1100 8.2 (11.4, 10.0); at
+// w = 1300, where the sweep begins, 16.0 ms against 15.7 with cells.
+constexpr int kUnionCells = 768;
 constexpr uint32_t kMaxSpheres = 1u << 30;    // sphere numbers fit 30 bits of the sort key
 struct OffsetArgs {
   AxisArrays in[3];

@@ -2261,12 +2261,16 @@ hipError_t launch_batch_scatter(const BatchDevice& b, uint32_t chunks, hipStream
 }
 
 hipError_t launch_batch_sample(const BatchDevice& b, uint32_t n_tiles, uint32_t n_small, hipStream_t s) {
-  if (n_small > 0)
-    hipLaunchKernelGGL((b.stage_stream ? batch_sample_kernel<kSmallTilePix, true> : batch_sample_kernel<kSmallTilePix, false>), dim3(persistent_grid(n_small, sample_wgs_per_cu<kSmallTilePix>())), dim3(kBlock), 0, s,
-                       b, n_tiles, 0u, n_small, 0, place_stage_cap(kSmallTilePix));
-  if (n_tiles > n_small)
-    hipLaunchKernelGGL((b.stage_stream ? batch_sample_kernel<kMaxTilePix, true> : batch_sample_kernel<kMaxTilePix, false>), dim3(persistent_grid(n_tiles - n_small, sample_wgs_per_cu<kMaxTilePix>())), dim3(kBlock),
-                       0, s, b, n_tiles, n_small, n_tiles, 3, place_stage_cap(kMaxTilePix));
+  if (n_small > 0) {
+    const auto kernel = b.stage_stream ? batch_sample_kernel<kSmallTilePix, true> : batch_sample_kernel<kSmallTilePix, false>;
+    hipLaunchKernelGGL(kernel, dim3(persistent_grid(n_small, sample_wgs_per_cu<kSmallTilePix>())), dim3(kBlock), 0, s, b,
+                       n_tiles, 0u, n_small, 0, place_stage_cap(kSmallTilePix));
+  }
+  if (n_tiles > n_small) {
+    const auto kernel = b.stage_stream ? batch_sample_kernel<kMaxTilePix, true> : batch_sample_kernel<kMaxTilePix, false>;
+    hipLaunchKernelGGL(kernel, dim3(persistent_grid(n_tiles - n_small, sample_wgs_per_cu<kMaxTilePix>())), dim3(kBlock), 0,
+                       s, b, n_tiles, n_small, n_tiles, 3, place_stage_cap(kMaxTilePix));
+  }
   return hipGetLastError();
 }
 
@@ -2276,12 +2280,15 @@ hipError_t launch_batch_place(const BatchDevice& b, uint32_t n_tiles, uint32_t n
   hipError_t e = launch_scan(b.plan, b.plan, 2 * (int64_t)n_tiles, scratch, nullptr, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_plan_items_kernel, dim3(grid_for(n_tiles, kBlock)), dim3(kBlock), 0, s, b, n_tiles);
-  if (n_small > 0)
-    hipLaunchKernelGGL((b.stage_stream ? batch_place_kernel<kSmallTilePix, true> : batch_place_kernel<kSmallTilePix, false>), dim3(persistent_grid(2 * n_small, 7)), dim3(kBlock), 0,
-                       s, b, n_tiles, 0u, n_small, 1);
-  if (n_tiles > n_small)
-    hipLaunchKernelGGL((b.stage_stream ? batch_place_kernel<kMaxTilePix, true> : batch_place_kernel<kMaxTilePix, false>), dim3(persistent_grid(2 * (n_tiles - n_small), 3)),
-                       dim3(kBlock), 0, s, b, n_tiles, n_small, n_tiles, 4);
+  if (n_small > 0) {
+    const auto kernel = b.stage_stream ? batch_place_kernel<kSmallTilePix, true> : batch_place_kernel<kSmallTilePix, false>;
+    hipLaunchKernelGGL(kernel, dim3(persistent_grid(2 * n_small, 7)), dim3(kBlock), 0, s, b, n_tiles, 0u, n_small, 1);
+  }
+  if (n_tiles > n_small) {
+    const auto kernel = b.stage_stream ? batch_place_kernel<kMaxTilePix, true> : batch_place_kernel<kMaxTilePix, false>;
+    hipLaunchKernelGGL(kernel, dim3(persistent_grid(2 * (n_tiles - n_small), 3)), dim3(kBlock), 0, s, b, n_tiles, n_small,
+                       n_tiles, 4);
+  }
   // tiles walked again: one build for all (the large one as soon as any
   // image has large tiles)
   if (n_tiles == n_small)

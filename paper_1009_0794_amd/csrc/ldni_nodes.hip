@@ -82,10 +82,12 @@ __device__ __forceinline__ int first_node(const NodeArgs& g, int f, float s) {
 // sample per lane (with a ray per lane, a 333^3 grid whose deepest ray has 160
 // samples took 296 us here).  A first pass over the samples counts the toggles
 // per brick and keeps the first kKept of them in LDS, a second places them
-// (and reads what was not kept again).  Half bound by VALU issue (170 instructions
+// (and reads what was not kept again).  Half bound by VALU issue (53 %; 180 instructions
 // per wave of 64 samples over both passes), half by the latency of a patch's
-// few serial steps: 0.32 ms for the 38.6 M samples of scene64 at w = 2048, 50 us
-// for the flower at w = 333; the span codes it replaced took 0.46 ms and 103 us.
+// few serial steps, some 10 us: 0.33 ms for the 38.6 M samples of scene64 at
+// w = 2048, 50 us for the flower at w = 333; the span codes it replaced took
+// 0.46 ms and 103 us.  On one patch an axis (w = 32) it is longer than they were, 9
+// against 4 us, and the call as long (41 us).
 constexpr uint32_t kKept = 3072;
 
 template <int kBinBlock>
@@ -382,7 +384,7 @@ __global__ void __launch_bounds__(kUniformBlock) uniform_nodes_kernel(NodeArgs g
 // (123 registers; held to 80 they spill: 0.70 ms for all bricks against 0.47).
 // Bound by the latency of the list reads: 27,000 of scene64's 262,144 bricks
 // at w = 2048 in 0.10 ms.  The vote it replaced transposed a 32 x 32 bit matrix
-// per thread of every brick: 0.93 ms, and 1.05 ms for the flower at w = 333 (now 29
+// per thread of every brick: 0.93 ms, and 1.05 ms for the flower at w = 333 (now 30
 // us), whose spans with more than two samples it walked.
 template <bool kAll>
 __global__ void __launch_bounds__(kNodeBlock, 4) classify_nodes_kernel(NodeArgs g) {
